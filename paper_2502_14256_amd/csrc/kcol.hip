@@ -5,23 +5,22 @@
 // ALU-bound: the points are either read once or regenerated in registers.
 #include <type_traits>
 
-#include "kfactor.hpp"
+#include "nettile.hpp"
 
 namespace ldk {
 
 // ---------------------------------------------------------------------------
 // Regenerating lattice variant.  Block: replication r = blockIdx.y; points
-// i = tile0 + t + KC_THREADS l (l < KC_ITERS), tile0 a multiple of KC_TILE,
-// so the bits of t, l and tile0 are disjoint and
-//   natural: bitreverse(i) g = bitreverse(tile0 + t) g + bitreverse3(l) (g << 53),
+// i = tile0 + t + KC_THREADS l (l < IT), tile0 a multiple of KC_THREADS IT,
+// so the bits of t, l and tile0 are disjoint and (LI = log2 IT)
+//   natural: bitreverse(i) g = bitreverse(tile0 + t) g + bitreverse_LI(l) (g << (56 - LI)),
 //   linear:  (i g) << (64-m) = ((tile0 + t) g) << (64-m) + l ((g << 8) << (64-m)).
 // The anchor is point 0, so delta = z(i) - z(0) = z(i): the shift cancels.
 // ---------------------------------------------------------------------------
-template <typename R, int ALPHA, int ORDER, bool FULL>
-__device__ __forceinline__ void lattice_tile(const KcolArgs &a, int64_t first, R (&prod)[KC_ITERS])
+template <typename R, int ALPHA, int ORDER, int IT>
+__device__ __forceinline__ void lattice_tile(const KcolArgs &a, int64_t first, R (&prod)[IT])
 {
-    static_assert(KC_ITERS == 8 && KC_LOG_THREADS == 8, "offset table assumes 8 x 256");
-    constexpr uint64_t br3[8] = {0, 4, 2, 6, 1, 5, 3, 7};
+    constexpr int LI = log2_of(IT);
     const int d = a.ps.d, m = a.ps.m_max;
     const uint64_t bfirst = ORDER == LDK_NATURAL ? brev64((uint64_t)first) : (uint64_t)first;
     for (int j = 0; j < d; ++j) {
@@ -32,7 +31,7 @@ __device__ __forceinline__ void lattice_tile(const KcolArgs &a, int64_t first, R
         uint64_t base, G;
         if constexpr (ORDER == LDK_NATURAL) {
             base = bfirst * g;
-            G = g << 53;
+            G = g << (56 - LI);
         } else {
             base = m == 0 ? 0 : ((bfirst * g) << (64 - m));
             G = m <= 8 ? 0 : ((g << 8) << (64 - m));
@@ -41,50 +40,49 @@ __device__ __forceinline__ void lattice_tile(const KcolArgs &a, int64_t first, R
         // share the low half of delta and differ in the high half only
         const R lo_p = lo_part<R>((uint32_t)base);
 #pragma unroll
-        for (int l = 0; l < KC_ITERS; ++l) {
+        for (int l = 0; l < IT; ++l) {
             R x;
             if constexpr (ORDER == LDK_NATURAL)
-                x = unit_hl<R>((uint32_t)(base >> 32) + (uint32_t)br3[l] * (uint32_t)(G >> 32), lo_p);
+                x = unit_hl<R>((uint32_t)(base >> 32) +
+                                   brev_const((uint32_t)l, LI) * (uint32_t)(G >> 32),
+                               lo_p);
             else
                 x = unit<R>(base + (uint64_t)l * G);
-            const R f = si_weighted<R, ALPHA>(x, c0, c1, c2, c3);
-            if (FULL) {
-                prod[l] *= f;
-            } else {
-                const int64_t i = first + (int64_t)l * KC_THREADS;
-                if (i >= a.n_min && i < a.n_max) prod[l] *= f;
-            }
+            prod[l] *= si_weighted<R, ALPHA>(x, c0, c1, c2, c3);
         }
     }
 }
 
-// Column tile bx of replication r (KC_TILE points from tile_base + bx KC_TILE).
-template <typename R, int ALPHA, int ORDER>
-__device__ __forceinline__ void kcol_lattice_block(const KcolArgs &a, int64_t tile_base,
-                                                   R *__restrict__ out, int64_t bx, int r)
+// Column tile bx of replication r (KC_THREADS IT points from tile_base +
+// bx KC_THREADS IT).  Points outside the window are formed and not stored.
+template <typename R, int IT>
+__device__ __forceinline__ void store_column(const KcolArgs &a, int64_t first, int r, const R (&prod)[IT],
+                                             R *__restrict__ out)
 {
     const int64_t cnt = a.n_max - a.n_min;
-    const int64_t tile0 = tile_base + bx * KC_TILE;
-    const int64_t first = tile0 + threadIdx.x;
-    R prod[KC_ITERS];
 #pragma unroll
-    for (int l = 0; l < KC_ITERS; ++l) prod[l] = (R)a.zeta;
-    if (tile0 >= a.n_min && tile0 + KC_TILE <= a.n_max)
-        lattice_tile<R, ALPHA, ORDER, true>(a, first, prod);
-    else
-        lattice_tile<R, ALPHA, ORDER, false>(a, first, prod);
-#pragma unroll
-    for (int l = 0; l < KC_ITERS; ++l) {
+    for (int l = 0; l < IT; ++l) {
         const int64_t i = first + (int64_t)l * KC_THREADS;
         if (i >= a.n_min && i < a.n_max) out[(size_t)r * cnt + (i - a.n_min)] = prod[l];
     }
 }
+template <typename R, int ALPHA, int ORDER, int IT>
+__device__ __forceinline__ void kcol_lattice_block(const KcolArgs &a, int64_t tile_base,
+                                                   R *__restrict__ out, int64_t bx, int r)
+{
+    const int64_t first = tile_base + bx * (KC_THREADS * IT) + threadIdx.x;
+    R prod[IT];
+#pragma unroll
+    for (int l = 0; l < IT; ++l) prod[l] = (R)a.zeta;
+    lattice_tile<R, ALPHA, ORDER, IT>(a, first, prod);
+    store_column<R, IT>(a, first, r, prod, out);
+}
 
-template <typename R, int ALPHA, int ORDER>
+template <typename R, int ALPHA, int ORDER, int IT>
 __global__ __launch_bounds__(KC_THREADS) void k_kcol_lattice(KcolArgs a, int64_t tile_base,
                                                             R *__restrict__ out)
 {
-    kcol_lattice_block<R, ALPHA, ORDER>(a, tile_base, out, blockIdx.x, blockIdx.y);
+    kcol_lattice_block<R, ALPHA, ORDER, IT>(a, tile_base, out, blockIdx.x, blockIdx.y);
 }
 
 // Point words and first column of a lattice in one launch.  The column
@@ -97,7 +95,7 @@ __global__ __launch_bounds__(KC_THREADS) void k_kcol_lattice(KcolArgs a, int64_t
 // (column blocks first: 52 us against 48 here), or not at all beside them
 // (two streams: the point launch takes every slot).
 static_assert(GEN_THREADS == KC_THREADS, "one block shape for both halves");
-template <typename R, int ALPHA, int ORDER>
+template <typename R, int ALPHA, int ORDER, int IT>
 __global__ __launch_bounds__(KC_THREADS) void k_points_kcol_lattice(KcolArgs a, int64_t tile_base,
                                                                    int64_t kc_tiles,
                                                                    R *__restrict__ k1, GenGrid g,
@@ -110,8 +108,8 @@ __global__ __launch_bounds__(KC_THREADS) void k_points_kcol_lattice(KcolArgs a, 
     // count floor((b+1) kc / total) of column blocks up to b steps at b
     const int64_t before = b * kc_blocks / total, upto = (b + 1) * kc_blocks / total;
     if (upto != before) {
-        kcol_lattice_block<R, ALPHA, ORDER>(a, tile_base, k1, before % kc_tiles,
-                                            (int)(before / kc_tiles));
+        kcol_lattice_block<R, ALPHA, ORDER, IT>(a, tile_base, k1, before % kc_tiles,
+                                                (int)(before / kc_tiles));
         return;
     }
     const int64_t q = b - upto;
@@ -121,95 +119,58 @@ __global__ __launch_bounds__(KC_THREADS) void k_points_kcol_lattice(KcolArgs a, 
 }
 
 // ---------------------------------------------------------------------------
-// Regenerating net variant.  The scrambled columns of a chunk of dimensions
-// sit in LDS (built from S rows staged in LDS); the step from point
-// i = tile0 + t + KC_THREADS l to the next one flips index bits
-// s .. s + ctz((tile0 >> s) + l + 1) (s = log2 KC_THREADS), a block-uniform
-// table read.  The anchor is point 0 (z = 0), so delta = z(i).
+// Regenerating net variant (see nettile.hpp): per chunk of dimensions the
+// block forms the tables, then every thread its IT points per dimension.  The
+// anchor is point 0 (z = 0), so delta = z(i).
 // ---------------------------------------------------------------------------
-template <typename R, int ALPHA, bool FULL>
-__device__ __forceinline__ void net_tile(const KcolArgs &a, NetLds &L, int r, int64_t tile0,
-                                         int64_t first, R (&prod)[KC_ITERS])
-{
-    constexpr int s = KC_LOG_THREADS;
-    const int d = a.ps.d, t = threadIdx.x;
-    const bool gray = a.ps.order == LDK_GRAY;
-    const uint64_t code_tile = gray ? gray_code((uint64_t)tile0) : (uint64_t)tile0;
-    const uint32_t code_t = gray ? (uint32_t)gray_code((uint64_t)t) : (uint32_t)t;
-    for (int jc = 0; jc < d; jc += KC_DIM_CHUNK) {
-        const int DB = min(KC_DIM_CHUNK, d - jc);
-        build_net_chunk(a, L, r, jc, DB, code_tile);
-        for (int jj = 0; jj < DB; ++jj) {
-            const int j = jc + jj;
-            const R gam = (R)a.gamma[j];
-            const int alpha = ALPHA ? ALPHA : alpha_of(a, j);
-            uint64_t z = L.zb[jj] ^ L.nib[jj][0][code_t & 15] ^ L.nib[jj][1][(code_t >> 4) & 15];
-#pragma unroll
-            for (int l = 0; l < KC_ITERS; ++l) {
-                R k;
-                if constexpr (ALPHA != 0)
-                    k = dsi_factor<R, ALPHA>(z, L.tab);
-                else
-                    k = dsi_factor_any<R>(alpha, z, L.tab);
-                const R f = dsi_weighted(gam, k);
-                if (FULL) {
-                    prod[l] *= f;
-                } else {
-                    const int64_t i = first + (int64_t)l * KC_THREADS;
-                    if (i >= a.n_min && i < a.n_max) prod[l] *= f;
-                }
-                // step to the next point; past the last index of the net the
-                // step columns are zero and z just repeats (such points are
-                // masked), so the step needs no bounds test
-                const uint64_t nb = ((uint64_t)tile0 >> s) + (uint64_t)l + 1;
-                if (l + 1 < KC_ITERS) z ^= L.step[jj][ctz64(nb)];
-            }
-        }
-    }
-}
-
-// Column tile bx of replication r of a net (every thread of the block calls it).
-template <typename R, int ALPHA>
-__device__ __forceinline__ void kcol_net_block(const KcolArgs &a, NetLds &L, int64_t tile_base,
+template <typename R, int ALPHA, int IT>
+__device__ __forceinline__ void kcol_net_block(const KcolArgs &a, NetLds<R, IT> &L, int64_t tile_base,
                                                R *__restrict__ out, int64_t bx, int r)
 {
-    const int64_t cnt = a.n_max - a.n_min;
-    const int64_t tile0 = tile_base + bx * KC_TILE;
-    const int64_t first = tile0 + threadIdx.x;
-    fill_dsi_tables(L.tab, threadIdx.x, KC_THREADS);
-    R prod[KC_ITERS];
+    using Z = typename net_word<R>::type;
+    const int t = threadIdx.x, d = a.ps.d;
+    const int64_t tile0 = tile_base + bx * (KC_THREADS * IT);
+    fill_net_lds<R, ALPHA>(L);
+    R prod[IT];
 #pragma unroll
-    for (int l = 0; l < KC_ITERS; ++l) prod[l] = (R)a.zeta;
-    if (tile0 >= a.n_min && tile0 + KC_TILE <= a.n_max)
-        net_tile<R, ALPHA, true>(a, L, r, tile0, first, prod);
-    else
-        net_tile<R, ALPHA, false>(a, L, r, tile0, first, prod);
+    for (int l = 0; l < IT; ++l) prod[l] = (R)a.zeta;
+    for (int jc = 0; jc < d; jc += NT_DIMS) {
+        const int DB = min(NT_DIMS, d - jc);
+        build_net_lds(a, L, r, jc, DB, tile0);
+        for (int jj = 0; jj < DB; ++jj) {
+            const R gam = L.gam[jj];
+            Z z[IT];
+            int c[IT];
+            net_points<IT>(L.t, jj, L.t.w[jj][L.NW - 1], z);
+            lead_index(z, c);
+            const int alpha = ALPHA ? ALPHA : alpha_of(a, jc + jj);
 #pragma unroll
-    for (int l = 0; l < KC_ITERS; ++l) {
-        const int64_t i = first + (int64_t)l * KC_THREADS;
-        if (i >= a.n_min && i < a.n_max) out[(size_t)r * cnt + (i - a.n_min)] = prod[l];
+            for (int l = 0; l < IT; ++l)
+                prod[l] *= dsi_weighted(gam, dsi_word<R, ALPHA>(z[l], c[l], alpha, L.lead, L.tab));
+        }
     }
+    store_column<R, IT>(a, tile0 + t, r, prod, out);
 }
 
-template <typename R, int ALPHA>
+template <typename R, int ALPHA, int IT>
 __global__ __launch_bounds__(KC_THREADS) void k_kcol_net(KcolArgs a, int64_t tile_base,
                                                         R *__restrict__ out)
 {
-    __shared__ NetLds L;
-    kcol_net_block<R, ALPHA>(a, L, tile_base, out, blockIdx.x, blockIdx.y);
+    __shared__ NetLds<R, IT> L;
+    kcol_net_block<R, ALPHA, IT>(a, L, tile_base, out, blockIdx.x, blockIdx.y);
 }
 
 // Point words and first column of a net in one launch: column blocks and
 // point-word blocks interleaved as for lattices (the column regenerates the
 // points and never reads the words), one LDS region shared by the two
 // block kinds.
-template <typename R, int ALPHA>
+template <typename R, int ALPHA, int IT>
 __global__ __launch_bounds__(KC_THREADS) void k_points_kcol_net(KcolArgs a, int64_t tile_base,
                                                                int64_t kc_tiles, R *__restrict__ k1,
                                                                GenGrid g, uint64_t *__restrict__ pts)
 {
     __shared__ union {
-        NetLds k;
+        NetLds<R, IT> k;
         GenNetLds g;
     } L;
     const int64_t b = blockIdx.x;
@@ -217,7 +178,7 @@ __global__ __launch_bounds__(KC_THREADS) void k_points_kcol_net(KcolArgs a, int6
     const int64_t total = kc_blocks + g.tiles * g.chunks * g.R;
     const int64_t before = b * kc_blocks / total, upto = (b + 1) * kc_blocks / total;
     if (upto != before) {
-        kcol_net_block<R, ALPHA>(a, L.k, tile_base, k1, before % kc_tiles, (int)(before / kc_tiles));
+        kcol_net_block<R, ALPHA, IT>(a, L.k, tile_base, k1, before % kc_tiles, (int)(before / kc_tiles));
         return;
     }
     const int64_t q = b - upto;
@@ -256,72 +217,79 @@ __global__ __launch_bounds__(KC_THREADS) void k_kcol_points(KcolArgs a, R *__res
     out[(size_t)r * cnt + (i - a.n_min)] = prod;
 }
 
-template <typename R, int ALPHA>
-void launch_regen(const KcolArgs &a, int64_t tile_base, dim3 grid, hipStream_t s, void *out)
+template <typename R, int ALPHA, int IT>
+void launch_column(const KcolArgs &a, int64_t tile_base, int64_t tiles, hipStream_t s, void *k1)
 {
+    const dim3 grid((unsigned)tiles, (unsigned)a.ps.R), block(KC_THREADS);
     if (a.ps.kind == LDK_DNET_B2)
-        hipLaunchKernelGGL((k_kcol_net<R, ALPHA>), grid, dim3(KC_THREADS), 0, s, a, tile_base, (R *)out);
-    else if (a.ps.order == LDK_LINEAR)
-        hipLaunchKernelGGL((k_kcol_lattice<R, ALPHA, LDK_LINEAR>), grid, dim3(KC_THREADS), 0, s, a,
-                           tile_base, (R *)out);
-    else
-        hipLaunchKernelGGL((k_kcol_lattice<R, ALPHA, LDK_NATURAL>), grid, dim3(KC_THREADS), 0, s, a,
-                           tile_base, (R *)out);
-}
-
-template <typename R, int ALPHA>
-void launch_points_kcol(const KcolArgs &a, int64_t tile_base, int64_t kc_tiles, const GenGrid &g,
-                        unsigned blocks, hipStream_t s, void *k1, uint64_t *pts)
-{
-    if (a.ps.kind == LDK_DNET_B2)
-        hipLaunchKernelGGL((k_points_kcol_net<R, ALPHA>), dim3(blocks), dim3(KC_THREADS), 0, s, a,
-                           tile_base, kc_tiles, (R *)k1, g, pts);
-    else if (a.ps.order == LDK_LINEAR)
-        hipLaunchKernelGGL((k_points_kcol_lattice<R, ALPHA, LDK_LINEAR>), dim3(blocks),
-                           dim3(KC_THREADS), 0, s, a, tile_base, kc_tiles, (R *)k1, g, pts);
-    else
-        hipLaunchKernelGGL((k_points_kcol_lattice<R, ALPHA, LDK_NATURAL>), dim3(blocks),
-                           dim3(KC_THREADS), 0, s, a, tile_base, kc_tiles, (R *)k1, g, pts);
-}
-
-template <typename R>
-void launch_points_kcol_alpha(int alpha, const KcolArgs &a, int64_t tile_base, int64_t kc_tiles,
-                              const GenGrid &g, unsigned blocks, hipStream_t s, void *k1,
-                              uint64_t *pts)
-{
-    switch (alpha) {  // lattice orders 1..3 and net orders 1..4; mixed orders 0
-    case 1: launch_points_kcol<R, 1>(a, tile_base, kc_tiles, g, blocks, s, k1, pts); break;
-    case 2: launch_points_kcol<R, 2>(a, tile_base, kc_tiles, g, blocks, s, k1, pts); break;
-    case 3: launch_points_kcol<R, 3>(a, tile_base, kc_tiles, g, blocks, s, k1, pts); break;
-    case 4:
-        if (a.ps.kind == LDK_DNET_B2) {
-            hipLaunchKernelGGL((k_points_kcol_net<R, 4>), dim3(blocks), dim3(KC_THREADS), 0, s, a,
-                               tile_base, kc_tiles, (R *)k1, g, pts);
-            break;
-        }
-        [[fallthrough]];
-    default: launch_points_kcol<R, 0>(a, tile_base, kc_tiles, g, blocks, s, k1, pts);
+        hipLaunchKernelGGL((k_kcol_net<R, ALPHA, IT>), grid, block, 0, s, a, tile_base, (R *)k1);
+    else if constexpr (ALPHA < 4) {
+        if (a.ps.order == LDK_LINEAR)
+            hipLaunchKernelGGL((k_kcol_lattice<R, ALPHA, LDK_LINEAR, IT>), grid, block, 0, s, a,
+                               tile_base, (R *)k1);
+        else
+            hipLaunchKernelGGL((k_kcol_lattice<R, ALPHA, LDK_NATURAL, IT>), grid, block, 0, s, a,
+                               tile_base, (R *)k1);
     }
 }
 
-template <typename R>
-void launch_regen_alpha(int kind, int alpha, const KcolArgs &a, int64_t tile_base, dim3 grid,
-                        hipStream_t s, void *out)
+template <typename R, int ALPHA, int IT>
+void launch_points_column(const KcolArgs &a, int64_t tile_base, int64_t tiles, const GenGrid &g,
+                          hipStream_t s, void *k1, uint64_t *pts)
 {
-    // lattice orders 1..3 and net orders 1..4 get specialised kernels; mixed
-    // orders (alpha = 0) read the per-dimension code
+    const dim3 grid((unsigned)(tiles * a.ps.R + g.tiles * g.chunks * g.R)), block(KC_THREADS);
+    if (a.ps.kind == LDK_DNET_B2)
+        hipLaunchKernelGGL((k_points_kcol_net<R, ALPHA, IT>), grid, block, 0, s, a, tile_base, tiles,
+                           (R *)k1, g, pts);
+    else if constexpr (ALPHA < 4) {
+        if (a.ps.order == LDK_LINEAR)
+            hipLaunchKernelGGL((k_points_kcol_lattice<R, ALPHA, LDK_LINEAR, IT>), grid, block, 0, s, a,
+                               tile_base, tiles, (R *)k1, g, pts);
+        else
+            hipLaunchKernelGGL((k_points_kcol_lattice<R, ALPHA, LDK_NATURAL, IT>), grid, block, 0, s,
+                               a, tile_base, tiles, (R *)k1, g, pts);
+    }
+}
+
+// Calls f with the order as a compile-time constant: lattice orders 1..3 and
+// net orders 1..4 get specialised kernels, mixed orders (0) read the
+// per-dimension code.
+template <typename F>
+void with_alpha(int alpha, F &&f)
+{
     switch (alpha) {
-    case 1: launch_regen<R, 1>(a, tile_base, grid, s, out); break;
-    case 2: launch_regen<R, 2>(a, tile_base, grid, s, out); break;
-    case 3: launch_regen<R, 3>(a, tile_base, grid, s, out); break;
-    case 4:
-        if (kind == LDK_DNET_B2) {
-            hipLaunchKernelGGL((k_kcol_net<R, 4>), grid, dim3(KC_THREADS), 0, s, a, tile_base, (R *)out);
-            break;
-        }
-        [[fallthrough]];
-    default: launch_regen<R, 0>(a, tile_base, grid, s, out);
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    default: f(std::integral_constant<int, 0>()); break;
     }
+}
+template <typename F>
+void with_iters(int it, F &&f)
+{
+    switch (it) {
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    case 8: f(std::integral_constant<int, 8>()); break;
+    default: f(std::integral_constant<int, 16>()); break;
+    }
+}
+
+// Points per thread, by the number of points R cnt: as many as still leave
+// about four blocks per compute unit (tables and per-dimension constants
+// serve more points), one where the launch would otherwise leave compute
+// units idle or hang on one block's chain of dimensions.  Measured (us for 1 /
+// 4 / 8 / 16 points per thread, order 2, FP64): net 2^16 x d = 16: 8.7 / 10.3
+// / 13.3 / 20.3; 2^18 x 32: 21.6 / 19.5 / 24.8 / 38.5; 2^20 x 32: 64 / 28.8 /
+// 26.9 / 40; 2^22 x 64: 401 / 168 / 140 / 139 (FP32 206 / 81 / 62 / 59);
+// lattice 2^16 x 16: 3.9 / 4.8 / 5.7 / 7.6; 2^18 x 32: 7.5 / 7.5 / 9.1 /
+// 12.4; 2^20 x 32: 18.6 / 13.4 / 12.7 / 13.5; 2^22 x 64: 107 / 70 / 64 / 62.
+// (Before: 8 always, with per-block scrambling in one thread per column.)
+int kcol_iters(const PointsetArgs &p, int64_t cnt)
+{
+    const int64_t pts = (int64_t)p.R * cnt, one = (int64_t)1 << (p.kind == LDK_LATTICE ? 19 : 18);
+    return pts < one ? 1 : pts < (1 << 20) ? 4 : pts < (1 << 22) ? 8 : 16;
 }
 
 }  // namespace ldk
@@ -400,15 +368,18 @@ extern "C" int ldk_kernel_column(const ldk_kernel *k, const ldk_pointset *ps, co
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }
-    // tiles aligned to absolute multiples of KC_TILE
-    const int64_t tile_base = (n_min / KC_TILE) * KC_TILE;
-    const int64_t tiles = (n_max - tile_base + KC_TILE - 1) / KC_TILE;
+    // tiles aligned to absolute multiples of their size
+    const int it = kcol_iters(p, n_max - n_min);
+    const int64_t tile = (int64_t)KC_THREADS * it;
+    const int64_t tile_base = (n_min / tile) * tile;
+    const int64_t tiles = (n_max - tile_base + tile - 1) / tile;
     if (tiles > 0x7fffffff) return LDK_ENOTSUP;
-    dim3 grid((unsigned)tiles, (unsigned)p.R);
-    if (dtype == LDK_F64)
-        launch_regen_alpha<double>(p.kind, uniform, a, tile_base, grid, s, out);
-    else
-        launch_regen_alpha<float>(p.kind, uniform, a, tile_base, grid, s, out);
+    with_alpha(uniform, [&](auto al) {
+        with_iters(it, [&](auto n) {
+            if (dtype == LDK_F64) launch_column<double, al(), n()>(a, tile_base, tiles, s, out);
+            else launch_column<float, al(), n()>(a, tile_base, tiles, s, out);
+        });
+    });
     LDK_LAUNCH_CHECK();
     return LDK_OK;
 }
@@ -427,18 +398,22 @@ extern "C" int ldk_points_column(const ldk_kernel *k, const ldk_pointset *ps, in
     if (n_min < 0 || n_max < n_min || n_max > lim) return LDK_EINVAL;
     if (n_max == n_min) return LDK_OK;  // empty window: the outputs may be NULL
     if (!pts || !k1) return LDK_EINVAL;
-    const int64_t tile_base = (n_min / KC_TILE) * KC_TILE;
-    const int64_t kc_tiles = (n_max - tile_base + KC_TILE - 1) / KC_TILE;
+    const int it = kcol_iters(p, n_max - n_min);
+    const int64_t tile = (int64_t)KC_THREADS * it;
+    const int64_t tile_base = (n_min / tile) * tile;
+    const int64_t kc_tiles = (n_max - tile_base + tile - 1) / tile;
     const GenGrid g = gen_grid(p, n_min, n_max, pts);
     const int64_t blocks = kc_tiles * p.R + g.tiles * g.chunks * g.R;
     if (blocks > 0x7fffffff) return LDK_ENOTSUP;
     hipStream_t s = as_stream(stream);
-    if (dtype == LDK_F64)
-        launch_points_kcol_alpha<double>(uniform, a, tile_base, kc_tiles, g, (unsigned)blocks, s, k1,
-                                         pts);
-    else
-        launch_points_kcol_alpha<float>(uniform, a, tile_base, kc_tiles, g, (unsigned)blocks, s, k1,
-                                        pts);
+    with_alpha(uniform, [&](auto al) {
+        with_iters(it, [&](auto n) {
+            if (dtype == LDK_F64)
+                launch_points_column<double, al(), n()>(a, tile_base, kc_tiles, g, s, k1, pts);
+            else
+                launch_points_column<float, al(), n()>(a, tile_base, kc_tiles, g, s, k1, pts);
+        });
+    });
     LDK_LAUNCH_CHECK();
     return LDK_OK;
 }

@@ -11,8 +11,7 @@ namespace ldk {
 namespace {
 constexpr int KC_THREADS = 256;
 constexpr int KC_LOG_THREADS = 8;
-constexpr int KC_ITERS = 8;       // points per thread (spaced KC_THREADS apart)
-constexpr int KC_DIM_CHUNK = 8;   // dimensions whose net tables sit in LDS at once (12 KiB)
+constexpr int KC_ITERS = 8;       // points per thread (spaced KC_THREADS apart) of the gradient
 constexpr int KC_TILE = KC_THREADS * KC_ITERS;
 constexpr int KC_CODE_WORDS = LDK_MAX_D / 32;  // 2-bit order codes, 32 per word
 }  // namespace
@@ -161,6 +160,37 @@ __device__ __forceinline__ float unit_hl<float>(uint32_t hi, float)
     return (float)opaque32(hi) * 0x1p-32f;
 }
 
+// K of a point whose digits give x, beta = b and t1 = 2^-beta (all 0 at the
+// point 0); hi = the top 32 digits.  ALPHA = 0: the order is `alpha`.
+template <typename R, int ALPHA>
+__device__ __forceinline__ R dsi_from_lead(uint32_t hi, R x, R b, R t1, int alpha, const DsiTables &tab)
+{
+    if constexpr (ALPHA == 0) {
+        switch (alpha) {
+        case 1: return dsi_from_lead<R, 1>(hi, x, b, t1, 1, tab);
+        case 2: return dsi_from_lead<R, 2>(hi, x, b, t1, 2, tab);
+        case 3: return dsi_from_lead<R, 3>(hi, x, b, t1, 3, tab);
+        default: return dsi_from_lead<R, 4>(hi, x, b, t1, 4, tab);
+        }
+    } else if constexpr (ALPHA == 1) {
+        return (R)1 - (R)3 * t1;
+    } else if constexpr (ALPHA == 2) {
+        return (R)1.5 - (R)2.5 * t1 - b * x;
+    } else if constexpr (ALPHA == 3) {
+        const R t2 = t1 * t1;
+        return ((b * x - (R)5 * ((R)1 - t1)) * x + (R)(43.0 / 18.0) * ((R)1 - t2)) - (R)1;
+    } else {
+        const R t2 = t1 * t1, t3 = t2 * t1;
+        const R ones = ((R)tab.t[0][hi >> 25] + (R)tab.t[1][(hi >> 18) & 127]) +
+                       (R)tab.t[2][(hi >> 11) & 127];
+        const R series = (R)(8.0 / 7.0) - (R)2 * ones;
+        const R poly = ((-(R)(2.0 / 3.0) * b * x + (R)5 * ((R)1 - t1)) * x -
+                        (R)(43.0 / 9.0) * ((R)1 - t2)) * x;
+        return poly + ((R)(701.0 / 294.0) * ((R)1 - t3) - (R)1) +
+               b * (series * (R)(1.0 / 48.0) - (R)(1.0 / 42.0));
+    }
+}
+
 template <typename R, int ALPHA>
 __device__ __forceinline__ R dsi_factor(uint64_t delta, const DsiTables &tab)
 {
@@ -182,26 +212,8 @@ __device__ __forceinline__ R dsi_factor(uint64_t delta, const DsiTables &tab)
         beta = nz ? clz64(delta) + 1 : 0;
     }
     const R x = unit<R>(delta);  // 0 at delta = 0
-    const R b = (R)beta;
     const R t1 = nz ? pow2_neg_r<R>(beta) : (R)0;
-    if constexpr (ALPHA == 1) {
-        return (R)1 - (R)3 * t1;
-    } else if constexpr (ALPHA == 2) {
-        return (R)1.5 - (R)2.5 * t1 - b * x;
-    } else if constexpr (ALPHA == 3) {
-        const R t2 = t1 * t1;
-        return ((b * x - (R)5 * ((R)1 - t1)) * x + (R)(43.0 / 18.0) * ((R)1 - t2)) - (R)1;
-    } else {
-        const R t2 = t1 * t1, t3 = t2 * t1;
-        const uint32_t hi = (uint32_t)(delta >> 32);
-        const R ones = ((R)tab.t[0][hi >> 25] + (R)tab.t[1][(hi >> 18) & 127]) +
-                       (R)tab.t[2][(hi >> 11) & 127];
-        const R series = (R)(8.0 / 7.0) - (R)2 * ones;
-        const R poly = ((-(R)(2.0 / 3.0) * b * x + (R)5 * ((R)1 - t1)) * x -
-                        (R)(43.0 / 9.0) * ((R)1 - t2)) * x;
-        return poly + ((R)(701.0 / 294.0) * ((R)1 - t3) - (R)1) +
-               b * (series * (R)(1.0 / 48.0) - (R)(1.0 / 42.0));
-    }
+    return dsi_from_lead<R, ALPHA>((uint32_t)(delta >> 32), x, (R)beta, t1, ALPHA, tab);
 }
 template <typename R>
 __device__ __forceinline__ R dsi_factor_any(int alpha, uint64_t delta, const DsiTables &tab)
@@ -229,21 +241,6 @@ __device__ __forceinline__ int alpha_of(const KcolArgs &a, int j)
     return 1 + (int)((a.acode[j >> 5] >> (2 * (j & 31))) & 3u);
 }
 
-// Net tables of a chunk of dimensions.  The start point of thread t is
-// z(code(tile0 + t)) = z(code(tile0)) ^ z(code(t)) (the index bits of tile0 and
-// t are disjoint, also after Gray coding), read as one block-uniform word
-// zb[jj] and two 16-entry nibble tables of z over the low 8 index bits.
-struct NetLds {
-    uint64_t ct[KC_DIM_CHUNK][64];  // scrambled columns S_j C_j
-    union {
-        uint64_t step[KC_DIM_CHUNK][64];  // XOR steps between a thread's points
-        uint64_t srow[KC_DIM_CHUNK][65];  // rows of S_j (dead once ct is built)
-    };
-    uint64_t nib[KC_DIM_CHUNK][2][16];  // z of (nibble h of the low index byte)
-    uint64_t zb[KC_DIM_CHUNK];          // z(code(tile0))
-    DsiTables tab;
-};
-
 // SI weight without the leading 1: gamma K_a(x) = e0 + c1 w + c2 w^2 + c3 w^3
 // (w = x^2 - x), so that small gamma K keeps its relative accuracy.
 __device__ __forceinline__ SiPoly si_tpoly(int alpha, double gamma)
@@ -261,54 +258,5 @@ __device__ __forceinline__ SiPoly si_tpoly(int alpha, double gamma)
 int prepare_kernel_args(const ldk_kernel *k, const ldk_pointset *ps, const uint64_t *pts,
                         const uint64_t *x0, int64_t n_min, int64_t n_max, int dtype, KcolArgs *out,
                         int *uniform_alpha);
-
-// Tables of dimensions jc .. jc+DB-1 for the block whose first point index
-// has code code_tile: scrambled columns, XOR steps, nibble tables and the
-// block's base point (see NetLds).  Every thread of the block must call it.
-__device__ __forceinline__ void build_net_chunk(const KcolArgs &a, NetLds &L, int r, int jc, int DB,
-                                                uint64_t code_tile)
-{
-    constexpr int s = KC_LOG_THREADS;
-    const int d = a.ps.d, m = a.ps.m_max, t = threadIdx.x;
-    const bool gray = a.ps.order == LDK_GRAY;
-    __syncthreads();  // tables of the previous chunk are no longer read
-    if (a.ps.lms) {
-        for (int w = t; w < DB * 64; w += KC_THREADS)
-            L.srow[w >> 6][w & 63] = a.ps.lms[((size_t)r * d + jc + (w >> 6)) * 64 + (w & 63)];
-        __syncthreads();
-    }
-    // columns k >= m are zero; the DB m scrambled columns take one item
-    // each, so no lane idles through a scrambling loop (the S rows are
-    // padded: the lanes of a wave read rows of different dimensions)
-    for (int w = t; w < DB * 64; w += KC_THREADS)
-        if ((w & 63) >= m) L.ct[w >> 6][w & 63] = 0;
-    for (int w = t; w < DB * m; w += KC_THREADS) {
-        const int jj = w / m, k = w - jj * m;
-        const uint64_t col = net_gen_column(a.ps, r, jc + jj, k);
-        L.ct[jj][k] = a.ps.lms ? lms_column(L.srow[jj], col) : col;
-    }
-    __syncthreads();  // srow is dead from here on; step reuses its storage
-    for (int w = t; w < DB * 64; w += KC_THREADS) {
-        const int jj = w >> 6, c = w & 63;
-        uint64_t v = 0;
-        if (s + c < m) {
-            if (gray) {
-                v = L.ct[jj][s + c] ^ L.ct[jj][s - 1];
-            } else {
-                for (int k = s; k <= s + c; ++k) v ^= L.ct[jj][k];
-            }
-        }
-        L.step[jj][c] = v;
-    }
-    for (int w = t; w < DB * 32; w += KC_THREADS) {
-        const int jj = w >> 5, h = (w >> 4) & 1, v = w & 15;
-        uint64_t z = 0;
-        for (int k = 0; k < 4; ++k)
-            if ((v >> k) & 1) z ^= L.ct[jj][4 * h + k];
-        L.nib[jj][h][v] = z;
-    }
-    if (t < DB) L.zb[t] = net_point(L.ct[t], m, code_tile);
-    __syncthreads();
-}
 
 }  // namespace ldk

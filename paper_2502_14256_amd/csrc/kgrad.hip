@@ -2,17 +2,19 @@
 // marginal-likelihood gradient (a = dL/dk1):
 //   d k1_i / d log gamma_j = zeta t_ij prod_{l != j} f_il,   t = gamma K, f = 1 + t,
 //   d k1_i / d log zeta    = k1_i = zeta prod_l f_il.
-// ALU-bound like the kernel column.  Each block takes KC_TILE points of one
-// replication and sweeps the dimensions twice: the first sweep forms every
-// point's product of nonzero factors P and counts its exact zeros; the second
-// re-evaluates t_ij and takes the product of the other factors as P / f_ij
-// (no zero), P (the one zero is f_ij) or 0.  Per dimension, the point sum is
-// reduced across the wavefront in FP64 and parked in lane j mod 64; every 64
-// dimensions the block adds its waves in LDS and writes one partial per tile,
-// and a second kernel adds the tiles in a fixed order.  Given the forward
-// column k1 (formed by the kernel column from bit-identical factors), the
-// first sweep is skipped: the product of the other factors is k1_i / f_ij.
-#include "kfactor.hpp"
+// ALU-bound like the kernel column.  Two sweeps over the dimensions in
+// general: the first forms every point's product of nonzero factors P and
+// counts its exact zeros; the second re-evaluates t_ij and takes the product
+// of the other factors as P / f_ij (no zero), P (the one zero is f_ij) or 0.
+// Given the forward column k1 (formed by the kernel column from bit-identical
+// factors), the product of the other factors is k1_i / f_ij, so a dimension
+// needs nothing of the others: the work is split over groups of dimensions as
+// well as over the points (k_kernel_grad_k1).  The sums over points are FP64:
+// per tile of KC_TILE points a thread adds its KC_ITERS terms in the factor
+// precision, the rest in FP64 in a fixed order.
+#include <type_traits>
+
+#include "nettile.hpp"
 
 namespace ldk {
 
@@ -23,9 +25,10 @@ struct KgradArgs {
     KcolArgs k;
     const double *a;  // [R][cnt], dL/dk1
     const void *k1;   // [R][cnt] forward column (kernel-column dtype), or nullptr
-    double *part;     // [R][tiles][d + 1]
+    double *part;     // [R][parts][d + 1]
     int64_t tile_base;
     int64_t tiles;
+    int dims_per_block;  // k_kernel_grad_k1
 };
 
 // One DPP lane move of a double (both halves), lanes the control leaves
@@ -64,96 +67,103 @@ __device__ __forceinline__ double wave_sum(double v)
 // range where the reciprocal overflows), FP64 takes the correctly rounded
 // quotient.
 __device__ __forceinline__ float quot(float p, float f) { return p * __builtin_amdgcn_rcpf(f); }
-__device__ __forceinline__ double quot(double p, double f) { return p / f; }
+// FP64: the hardware's estimate (2^-24 relative), one Newton step (2^-48),
+// and one correction of the quotient from its exact remainder, which leaves
+// half an ulp and a 2^-96 term (the divide's own steps without its second
+// Newton step and its scaling of operands near the ends of the exponent
+// range: f is 0, handled by the callers, or at least an ulp of 1).
+__device__ __forceinline__ double quot(double p, double f)
+{
+    double r = __builtin_amdgcn_rcp(f);
+    r = fma_r(r, fma_r(-f, r, 1.0), r);
+    const double q = p * r;
+    return fma_r(fma_r(-f, q, p), r, q);
+}
 
-// ---- dimension sweeps: call visit(j, t[KC_ITERS], f[KC_ITERS]) for j = 0 .. d-1
-// in order, t[l] = gamma_j K_j(delta) and f[l] = 1 + t[l] of point
+// ---- dimension sweeps: call visit(j, l0, t[KC_ITERS], f[KC_ITERS]) for the
+// dimensions ja .. jb - 1 in order and l0 = 0, KC_ITERS, .. below IT, t[l] = gamma_j K_j(delta) and f[l] = 1 + t[l] of point
 // tile0 + threadIdx.x + KC_THREADS l, f formed exactly as the kernel column
 // forms it ----
 
-template <typename R, int ALPHA, int ORDER, typename Visit>
-__device__ __forceinline__ void lattice_sweep(const KcolArgs &a, int64_t first, Visit &&visit)
-{
-    static_assert(KC_ITERS == 8 && KC_LOG_THREADS == 8, "offset table assumes 8 x 256");
-    constexpr uint64_t br3[8] = {0, 4, 2, 6, 1, 5, 3, 7};
-    const int d = a.ps.d, m = a.ps.m_max;
-    const uint64_t bfirst = ORDER == LDK_NATURAL ? brev64((uint64_t)first) : (uint64_t)first;
-    for (int j = 0; j < d; ++j) {
+// t and f of the KC_ITERS points l0 .. l0 + KC_ITERS - 1 of a thread (its
+// points are first + KC_THREADS l, l < IT, first = tile0 + threadIdx.x with
+// tile0 a multiple of KC_THREADS IT).  Sg / Sc: the t and f polynomials.
+template <typename R, int ALPHA, int ORDER, int IT>
+struct LatticeDim {
+    R e0, c0, c1, c2, c3, lo_p;
+    uint64_t base, G;
+    __device__ __forceinline__ LatticeDim(const KcolArgs &a, uint64_t bfirst, int j)
+    {
+        const int m = a.ps.m_max;
         const uint64_t g = a.ps.gen[j];
         const int alpha = ALPHA ? ALPHA : alpha_of(a, j);
         const SiPoly cf = si_tpoly(alpha, a.gamma[j]);
-        const R e0 = (R)cf.c0, c1 = (R)cf.c1, c2 = (R)cf.c2, c3 = (R)cf.c3;
-        const R c0 = (R)si_poly(alpha, a.gamma[j]).c0;
-        uint64_t base, G;
+        e0 = (R)cf.c0, c1 = (R)cf.c1, c2 = (R)cf.c2, c3 = (R)cf.c3;
+        c0 = (R)si_poly(alpha, a.gamma[j]).c0;
         if constexpr (ORDER == LDK_NATURAL) {
             base = bfirst * g;
-            G = g << 53;
+            G = g << (56 - log2_of(IT));
         } else {
             base = m == 0 ? 0 : ((bfirst * g) << (64 - m));
             G = m <= 8 ? 0 : ((g << 8) << (64 - m));
         }
-        R t[KC_ITERS], f[KC_ITERS];
-        const R lo_p = lo_part<R>((uint32_t)base);  // shared low half (natural order)
+        lo_p = lo_part<R>((uint32_t)base);  // shared low half (natural order)
+    }
+    __device__ __forceinline__ void factors(int l0, R (&t)[KC_ITERS], R (&f)[KC_ITERS]) const
+    {
 #pragma unroll
         for (int l = 0; l < KC_ITERS; ++l) {
             R x;
             if constexpr (ORDER == LDK_NATURAL)
-                x = unit_hl<R>((uint32_t)(base >> 32) + (uint32_t)br3[l] * (uint32_t)(G >> 32), lo_p);
+                x = unit_hl<R>((uint32_t)(base >> 32) +
+                                   brev_const((uint32_t)(l0 + l), log2_of(IT)) * (uint32_t)(G >> 32),
+                               lo_p);
             else
-                x = unit<R>(base + (uint64_t)l * G);
+                x = unit<R>(base + (uint64_t)(l0 + l) * G);
             t[l] = si_weighted<R, ALPHA>(x, e0, c1, c2, c3);
             f[l] = si_weighted<R, ALPHA>(x, c0, c1, c2, c3);
         }
-        visit(j, t, f);
     }
-}
+};
 
-template <typename R, int ALPHA, typename Visit>
-__device__ __forceinline__ void net_sweep(const KcolArgs &a, NetLds &L, int r, int64_t tile0,
-                                          Visit &&visit)
-{
-    constexpr int s = KC_LOG_THREADS;
-    const int d = a.ps.d, t = threadIdx.x;
-    const bool gray = a.ps.order == LDK_GRAY;
-    const uint64_t code_tile = gray ? gray_code((uint64_t)tile0) : (uint64_t)tile0;
-    const uint32_t code_t = gray ? (uint32_t)gray_code((uint64_t)t) : (uint32_t)t;
-    for (int jc = 0; jc < d; jc += KC_DIM_CHUNK) {
-        const int DB = min(KC_DIM_CHUNK, d - jc);
-        build_net_chunk(a, L, r, jc, DB, code_tile);
-        for (int jj = 0; jj < DB; ++jj) {
-            const int j = jc + jj;
-            const R gam = (R)a.gamma[j];
-            const int alpha = ALPHA ? ALPHA : alpha_of(a, j);
-            uint64_t z = L.zb[jj] ^ L.nib[jj][0][code_t & 15] ^ L.nib[jj][1][(code_t >> 4) & 15];
-            R tv[KC_ITERS], fv[KC_ITERS];
+// The same for dimension jc + jj of net tables in LDS.
+template <typename R, int ALPHA, int IT>
+struct NetDim {
+    using Z = typename net_word<R>::type;
+    const NetLds<R, IT> &L;
+    R gam;
+    int alpha;
+    Z z[IT];
+    __device__ __forceinline__ NetDim(const KcolArgs &a, const NetLds<R, IT> &L_, int jc, int jj) : L(L_)
+    {
+        gam = L.gam[jj];
+        alpha = ALPHA ? ALPHA : alpha_of(a, jc + jj);
+        net_points<IT>(L.t, jj, L.t.w[jj][L.NW - 1], z);
+    }
+    __device__ __forceinline__ void factors(int l0, R (&t)[KC_ITERS], R (&f)[KC_ITERS]) const
+    {
+        Z zl[KC_ITERS];
+        int c[KC_ITERS];
 #pragma unroll
-            for (int l = 0; l < KC_ITERS; ++l) {
-                R k;
-                if constexpr (ALPHA != 0)
-                    k = dsi_factor<R, ALPHA>(z, L.tab);
-                else
-                    k = dsi_factor_any<R>(alpha, z, L.tab);
-                tv[l] = gam * k;
-                fv[l] = dsi_weighted(gam, k);
-                // step to the next point; past the last index of the net the
-                // step columns are zero and z just repeats (such points are
-                // masked), so the step needs no bounds test
-                const uint64_t nb = ((uint64_t)tile0 >> s) + (uint64_t)l + 1;
-                if (l + 1 < KC_ITERS) z ^= L.step[jj][ctz64(nb)];
-            }
-            visit(j, tv, fv);
+        for (int l = 0; l < KC_ITERS; ++l) zl[l] = z[l0 + l];
+        lead_index(zl, c);
+#pragma unroll
+        for (int l = 0; l < KC_ITERS; ++l) {
+            const R k = dsi_word<R, ALPHA>(zl[l], c[l], alpha, L.lead, L.tab);
+            t[l] = gam * k;
+            f[l] = dsi_weighted(gam, k);
         }
     }
-}
+};
 
 // Points read from memory (any order; anchors x0 or row 0).
 template <typename R, bool NET, typename Visit>
-__device__ __forceinline__ void points_sweep(const KcolArgs &a, const DsiTables &tab, int r,
-                                             int64_t first, Visit &&visit)
+__device__ __forceinline__ void points_sweep(const KcolArgs &a, const DsiTables &tab, int r, int ja,
+                                             int jb, int64_t first, Visit &&visit)
 {
     const int d = a.ps.d;
     const int64_t cnt = a.n_max - a.n_min;
-    for (int j = 0; j < d; ++j) {
+    for (int j = ja; j < jb; ++j) {
         const uint64_t u0 = a.x0 ? a.x0[(size_t)r * d + j] : a.pts[(size_t)r * cnt * d + j];
         const int alpha = alpha_of(a, j);
         const SiPoly cf = NET ? SiPoly{} : si_tpoly(alpha, a.gamma[j]);
@@ -175,91 +185,123 @@ __device__ __forceinline__ void points_sweep(const KcolArgs &a, const DsiTables 
                 f[l] = si_weighted<R, 0>(x, c0, (R)cf.c1, (R)cf.c2, (R)cf.c3);
             }
         }
-        visit(j, t, f);
+        visit(j, 0, t, f);
     }
 }
 
 // Source selector: SRC 0 lattice natural, 1 lattice linear, 2 net, 3 points
-// (lattice), 4 points (net).
-template <typename R, int ALPHA, int SRC, typename Visit>
-__device__ __forceinline__ void sweep(const KcolArgs &a, NetLds &L, int r, int64_t tile0,
-                                      int64_t first, Visit &&visit)
+// (lattice), 4 points (net).  Net tables are formed per chunk of NT_DIMS.
+template <typename R, int ALPHA, int SRC, int IT, typename Visit>
+__device__ __forceinline__ void sweep(const KcolArgs &a, NetLds<R, IT> &L, int r, int ja, int jb,
+                                      int64_t tile0, Visit &&visit)
 {
-    if constexpr (SRC == 0) lattice_sweep<R, ALPHA, LDK_NATURAL>(a, first, visit);
-    else if constexpr (SRC == 1) lattice_sweep<R, ALPHA, LDK_LINEAR>(a, first, visit);
-    else if constexpr (SRC == 2) net_sweep<R, ALPHA>(a, L, r, tile0, visit);
-    else points_sweep<R, SRC == 4>(a, L.tab, r, first, visit);
+    const int64_t first = tile0 + threadIdx.x;
+    if constexpr (SRC >= 3) {
+        static_assert(IT == KC_ITERS, "given points: one group of points per thread");
+        points_sweep<R, SRC == 4>(a, L.tab, r, ja, jb, first, visit);
+    } else if constexpr (SRC == 2) {
+        for (int jc = ja; jc < jb; jc += NT_DIMS) {
+            const int DB = min(NT_DIMS, jb - jc);
+            build_net_lds(a, L, r, jc, DB, tile0);
+            for (int jj = 0; jj < DB; ++jj) {
+                const NetDim<R, ALPHA, IT> dim(a, L, jc, jj);
+#pragma unroll
+                for (int l0 = 0; l0 < IT; l0 += KC_ITERS) {
+                    R t[KC_ITERS], f[KC_ITERS];
+                    dim.factors(l0, t, f);
+                    visit(jc + jj, l0, t, f);
+                }
+            }
+        }
+    } else {
+        constexpr int ORDER = SRC == 1 ? LDK_LINEAR : LDK_NATURAL;
+        const uint64_t bfirst = ORDER == LDK_NATURAL ? brev64((uint64_t)first) : (uint64_t)first;
+        for (int j = ja; j < jb; ++j) {
+            const LatticeDim<R, ALPHA, ORDER, IT> dim(a, bfirst, j);
+#pragma unroll
+            for (int l0 = 0; l0 < IT; l0 += KC_ITERS) {
+                R t[KC_ITERS], f[KC_ITERS];
+                dim.factors(l0, t, f);
+                visit(j, l0, t, f);
+            }
+        }
+    }
 }
 
-template <typename R, int ALPHA, int SRC, bool K1>
+// One block: the tile of KC_THREADS IT points blockIdx.x of replication
+// blockIdx.y, dimensions z D .. z D + D - 1 (z = blockIdx.z, D =
+// dims_per_block; every dimension when K1 is false); block z = 0 also sums
+// the log zeta term.  The wavefront reduction of a dimension's sum (22
+// instructions) is paid once per IT points of a thread.
+template <typename R, int ALPHA, int SRC, bool K1, int IT>
 __global__ __launch_bounds__(KC_THREADS) void k_kernel_grad(KgradArgs g)
 {
-    __shared__ NetLds L;
+    __shared__ NetLds<R, IT> L;
     __shared__ double red[KG_WAVES][64];
     const KcolArgs &a = g.k;
     const int r = blockIdx.y, d = a.ps.d;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t cnt = a.n_max - a.n_min;
-    const int64_t tile0 = g.tile_base + (int64_t)blockIdx.x * KC_TILE;
+    const int64_t tile0 = g.tile_base + (int64_t)blockIdx.x * (KC_THREADS * IT);
     const int64_t first = tile0 + threadIdx.x;
-    if constexpr (SRC >= 2) {
+    const int ja = K1 ? (int)blockIdx.z * g.dims_per_block : 0;
+    const int jb = K1 ? min(ja + g.dims_per_block, d) : d;
+    if constexpr (SRC == 2) {
+        fill_net_lds<R, ALPHA>(L);
+    } else if constexpr (SRC == 4) {
         fill_dsi_tables(L.tab, threadIdx.x, KC_THREADS);
         __syncthreads();
     }
-    R pnz[KC_ITERS], av[KC_ITERS];
-    int nz[KC_ITERS];
+    R pnz[IT], av[IT];
+    int nz[IT];
     uint32_t valid = 0;
+    int zero = 0;
 #pragma unroll
-    for (int l = 0; l < KC_ITERS; ++l) {
+    for (int l = 0; l < IT; ++l) {
         const int64_t i = first + (int64_t)l * KC_THREADS;
         const bool in = i >= a.n_min && i < a.n_max;
+        const size_t at = (size_t)r * cnt + (i - a.n_min);
         valid |= (uint32_t)in << l;
-        av[l] = in ? (R)g.a[(size_t)r * cnt + (i - a.n_min)] : (R)0;
+        av[l] = in ? (R)g.a[at] : (R)0;
         pnz[l] = (R)1;
+        if constexpr (K1) pnz[l] = in ? static_cast<const R *>(g.k1)[at] : (R)1;
+        zero |= pnz[l] == (R)0;
         nz[l] = 0;
     }
     // With the forward column given, k1_i = zeta prod_l f_il already holds
     // the product, formed from the same factors bit for bit, so one sweep
-    // suffices: zeta t_ij prod_{l != j} f_il = t_ij (k1_i / f_ij).  A block
-    // with a zero k1_i (a zero factor, or underflow) takes the two sweeps.
-    bool from_k1 = false;
-    if constexpr (K1) {
-        int zero = 0;
-#pragma unroll
-        for (int l = 0; l < KC_ITERS; ++l) {
-            const int64_t i = first + (int64_t)l * KC_THREADS;
-            if ((valid >> l) & 1u) {
-                pnz[l] = static_cast<const R *>(g.k1)[(size_t)r * cnt + (i - a.n_min)];
-                zero |= pnz[l] == (R)0;
-            }
-        }
-        from_k1 = !__syncthreads_or(zero);
-        if (!from_k1) {
-#pragma unroll
-            for (int l = 0; l < KC_ITERS; ++l) pnz[l] = (R)1;
-        }
-    }
+    // over the block's own dimensions suffices: zeta t_ij prod_{l != j} f_il
+    // = t_ij (k1_i / f_ij).  A block with a zero k1_i (a zero factor, or
+    // underflow) forms the products itself.
+    const bool from_k1 = K1 && !__syncthreads_or(zero);
     if (!from_k1) {
-        // sweep 1: product of the nonzero factors and the number of zero factors
-        sweep<R, ALPHA, SRC>(a, L, r, tile0, first,
-                             [&](int, const R(&)[KC_ITERS], const R(&f)[KC_ITERS]) {
+        // product of the nonzero factors and the number of zero factors
+#pragma unroll
+        for (int l = 0; l < IT; ++l) pnz[l] = (R)1;
+        sweep<R, ALPHA, SRC, IT>(a, L, r, 0, d, tile0,
+                                 [&](int, int l0, const R(&)[KC_ITERS], const R(&f)[KC_ITERS]) {
 #pragma unroll
             for (int l = 0; l < KC_ITERS; ++l) {
-                if (f[l] == (R)0) ++nz[l];
-                else pnz[l] *= f[l];
+                if (f[l] == (R)0) ++nz[l0 + l];
+                else pnz[l0 + l] *= f[l];
             }
         });
     }
     // pnz already carries zeta when it came from k1
     const double zf = from_k1 ? 1.0 : a.zeta;
     double *part = g.part + ((size_t)r * g.tiles + blockIdx.x) * (d + 1);
-    {
+    if (!K1 || blockIdx.z == 0) {
         // d/dlog zeta: sum_i a_i k1_i
-        R zs = (R)0;
+        double zt = 0.0;
 #pragma unroll
-        for (int l = 0; l < KC_ITERS; ++l)
-            if (((valid >> l) & 1u) && nz[l] == 0) zs += av[l] * pnz[l];
-        const double w = wave_sum((double)zs * zf);
+        for (int l0 = 0; l0 < IT; l0 += KC_ITERS) {
+            R zs = (R)0;
+#pragma unroll
+            for (int l = l0; l < l0 + KC_ITERS; ++l)
+                if (((valid >> l) & 1u) && nz[l] == 0) zs += av[l] * pnz[l];
+            zt += (double)zs;
+        }
+        const double w = wave_sum(zt * zf);
         if (lane == 0) red[wave][0] = w;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -269,17 +311,20 @@ __global__ __launch_bounds__(KC_THREADS) void k_kernel_grad(KgradArgs g)
         }
         __syncthreads();
     }
-    // sweep 2: t_ij times the product of the other factors
-    double acc = 0.0;
-    auto emit = [&](int j, R ps) {
-        const double w = wave_sum((double)ps * zf);
-        if ((j & 63) == lane) acc = w;
-        if ((j & 63) == 63 || j == d - 1) {
+    // t_ij times the product of the other factors
+    double acc = 0.0, sum = 0.0;
+    auto emit = [&](int j, int l0, R ps) {
+        sum = l0 == 0 ? (double)ps : sum + (double)ps;
+        if (l0 + KC_ITERS < IT) return;
+        const double w = wave_sum(sum * zf);
+        const int at = (j - ja) & 63;
+        if (at == lane) acc = w;
+        if (at == 63 || j == jb - 1) {
             // block-uniform: every thread reaches these barriers
-            const int j0 = j & ~63;
+            const int j0 = j - at;
             red[wave][lane] = acc;
             __syncthreads();
-            if (threadIdx.x < 64 && j0 + (int)threadIdx.x <= j) {
+            if ((int)threadIdx.x <= at) {
                 double s = 0.0;
                 for (int q = 0; q < KG_WAVES; ++q) s += red[q][threadIdx.x];
                 part[j0 + threadIdx.x] = s;
@@ -287,102 +332,140 @@ __global__ __launch_bounds__(KC_THREADS) void k_kernel_grad(KgradArgs g)
             __syncthreads();
         }
     };
-    if (K1 && from_k1) {
+    if (from_k1) {
         // no zero factor at any valid point of the tile
-        sweep<R, ALPHA, SRC>(a, L, r, tile0, first,
-                             [&](int j, const R(&t)[KC_ITERS], const R(&f)[KC_ITERS]) {
+        sweep<R, ALPHA, SRC, IT>(a, L, r, ja, jb, tile0,
+                                 [&](int j, int l0, const R(&t)[KC_ITERS], const R(&f)[KC_ITERS]) {
             R ps = (R)0;
 #pragma unroll
             for (int l = 0; l < KC_ITERS; ++l) {
-                const R c = av[l] * (t[l] * quot(pnz[l], f[l]));
-                ps += ((valid >> l) & 1u) ? c : (R)0;
+                const R c = av[l0 + l] * (t[l] * quot(pnz[l0 + l], f[l]));
+                ps += ((valid >> (l0 + l)) & 1u) ? c : (R)0;
             }
-            emit(j, ps);
+            emit(j, l0, ps);
         });
     } else {
-        sweep<R, ALPHA, SRC>(a, L, r, tile0, first,
-                             [&](int j, const R(&t)[KC_ITERS], const R(&f)[KC_ITERS]) {
+        sweep<R, ALPHA, SRC, IT>(a, L, r, ja, jb, tile0,
+                                 [&](int j, int l0, const R(&t)[KC_ITERS], const R(&f)[KC_ITERS]) {
             R ps = (R)0;
 #pragma unroll
             for (int l = 0; l < KC_ITERS; ++l) {
-                const R q = quot(pnz[l], f[l]);
-                const R one_zero = (nz[l] == 1 && f[l] == (R)0) ? pnz[l] : (R)0;
-                const R other = nz[l] == 0 ? q : one_zero;
-                const R c = av[l] * (t[l] * other);
-                ps += ((valid >> l) & 1u) ? c : (R)0;
+                const int k = l0 + l;
+                const R q = quot(pnz[k], f[l]);
+                const R one_zero = (nz[k] == 1 && f[l] == (R)0) ? pnz[k] : (R)0;
+                const R other = nz[k] == 0 ? q : one_zero;
+                const R c = av[k] * (t[l] * other);
+                ps += ((valid >> k) & 1u) ? c : (R)0;
             }
-            emit(j, ps);
+            emit(j, l0, ps);
         });
     }
 }
 
-// grad[r][j] = sum over tiles of the partials, in a fixed order (four
-// interleaved accumulators, combined in a fixed order).
-__global__ __launch_bounds__(256) void k_grad_final(const double *__restrict__ part, int64_t tiles,
-                                                    int d, double *__restrict__ grad)
+// Points per thread and dimensions per block given the forward column.  The
+// dimensions are independent then, so a grid short of three blocks per
+// compute unit is split over them; a large one takes twice the points per
+// thread (the dimension's setup and reduction serve more factors; FP64 nets
+// lose their occupancy to it and do not).  Measured (us, D = 16 / 8 / 4 / 2
+// dimensions per block): FP64 net 2^16 points x d = 16: 21.0 / 13.8 / 10.2 /
+// 8.8; 2^18 x 32: 22.0 / 18.2 / 17.0 / 20.5; 2^20 x 32: 42.4 / 43.8 / 48.3 /
+// 63.6; 16 instead of 8 points per thread at 2^22 x 64: lattice FP64 194 ->
+// 185, FP32 133 -> 127, net FP32 132 -> 130, net FP64 268 -> 272.
+void grad_split(const PointsetArgs &p, int64_t cnt, int dtype, int *it, int *dims)
 {
-    const int r = blockIdx.y;
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j > d) return;
-    const size_t stride = (size_t)(d + 1);
-    const double *p = part + (size_t)r * tiles * stride + j;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int64_t q = 0;
-    for (; q + 4 <= tiles; q += 4) {
-        s0 += p[(size_t)q * stride];
-        s1 += p[(size_t)(q + 1) * stride];
-        s2 += p[(size_t)(q + 2) * stride];
-        s3 += p[(size_t)(q + 3) * stride];
+    auto blocks = [&](int n, int dd) {
+        return (cnt + KC_THREADS * n - 1) / (KC_THREADS * n) * p.R * ((p.d + dd - 1) / dd);
+    };
+    *it = KC_ITERS;
+    *dims = NT_DIMS;
+    if ((p.kind == LDK_LATTICE || dtype == LDK_F32) && blocks(2 * KC_ITERS, NT_DIMS) >= 1024)
+        *it = 2 * KC_ITERS;
+    while (*dims > 2 && blocks(*it, *dims) < 768) *dims /= 2;
+}
+
+// grad[r][j] = sum over tiles of the partials, in a fixed order: 64 sums per
+// block (one per lane), each wave taking every KG_FINAL_WAVES-th tile, then
+// the waves' sums in turn.  One thread per sum walking every tile was a chain
+// of memory latencies (60 us of the 75 us of a gradient of 512 tiles).
+constexpr int KG_FINAL_WAVES = 16;
+__global__ __launch_bounds__(64 * KG_FINAL_WAVES) void k_grad_final(const double *__restrict__ part,
+                                                                    int64_t tiles, int d,
+                                                                    double *__restrict__ grad)
+{
+    __shared__ double red[KG_FINAL_WAVES][64];
+    const int r = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = blockIdx.x * 64 + lane;
+    double s = 0.0;
+    if (j <= d) {
+        const double *p = part + (size_t)r * tiles * (d + 1) + j;
+#pragma unroll 4
+        for (int64_t q = wave; q < tiles; q += KG_FINAL_WAVES) s += p[(size_t)q * (d + 1)];
     }
-    for (; q < tiles; ++q) s0 += p[(size_t)q * stride];
-    grad[(size_t)r * (d + 1) + j] = (s0 + s1) + (s2 + s3);
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && j <= d) {
+        for (int w = 1; w < KG_FINAL_WAVES; ++w) s += red[w][lane];
+        grad[(size_t)r * (d + 1) + j] = s;
+    }
 }
 
 template <typename R, int ALPHA, int SRC>
-void launch_grad_k1(const KgradArgs &g, dim3 grid, hipStream_t s)
+void launch_grad_k1(const KgradArgs &g, int it, dim3 grid, hipStream_t s)
 {
-    if (g.k1) hipLaunchKernelGGL((k_kernel_grad<R, ALPHA, SRC, true>), grid, dim3(KC_THREADS), 0, s, g);
-    else hipLaunchKernelGGL((k_kernel_grad<R, ALPHA, SRC, false>), grid, dim3(KC_THREADS), 0, s, g);
+    constexpr int N = KC_ITERS;
+    if (!g.k1) {
+        hipLaunchKernelGGL((k_kernel_grad<R, ALPHA, SRC, false, N>), grid, dim3(KC_THREADS), 0, s, g);
+        return;
+    }
+    grid.z = (unsigned)((g.k.ps.d + g.dims_per_block - 1) / g.dims_per_block);
+    if constexpr (SRC < 2 || (SRC == 2 && sizeof(R) == 4)) {
+        if (it == 2 * N) {
+            hipLaunchKernelGGL((k_kernel_grad<R, ALPHA, SRC, true, 2 * N>), grid, dim3(KC_THREADS), 0, s, g);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_kernel_grad<R, ALPHA, SRC, true, N>), grid, dim3(KC_THREADS), 0, s, g);
 }
 
 template <typename R, int ALPHA>
-void launch_grad_src(int src, const KgradArgs &g, dim3 grid, hipStream_t s)
+void launch_grad_src(int src, const KgradArgs &g, int it, dim3 grid, hipStream_t s)
 {
     switch (src) {
-    case 0: launch_grad_k1<R, ALPHA, 0>(g, grid, s); break;
-    case 1: launch_grad_k1<R, ALPHA, 1>(g, grid, s); break;
-    default: launch_grad_k1<R, ALPHA, 2>(g, grid, s); break;
+    case 0: launch_grad_k1<R, ALPHA, 0>(g, it, grid, s); break;
+    case 1: launch_grad_k1<R, ALPHA, 1>(g, it, grid, s); break;
+    default: launch_grad_k1<R, ALPHA, 2>(g, it, grid, s); break;
     }
 }
 
 template <typename R>
-void launch_grad(int src, int uniform, const KgradArgs &g, dim3 grid, hipStream_t s)
+void launch_grad(int src, int uniform, const KgradArgs &g, int it, dim3 grid, hipStream_t s)
 {
     if (src >= 3) {  // points given: generic orders
-        if (src == 3) launch_grad_k1<R, 0, 3>(g, grid, s);
-        else launch_grad_k1<R, 0, 4>(g, grid, s);
+        if (src == 3) launch_grad_k1<R, 0, 3>(g, it, grid, s);
+        else launch_grad_k1<R, 0, 4>(g, it, grid, s);
         return;
     }
     switch (uniform) {
-    case 1: launch_grad_src<R, 1>(src, g, grid, s); break;
-    case 2: launch_grad_src<R, 2>(src, g, grid, s); break;
-    case 3: launch_grad_src<R, 3>(src, g, grid, s); break;
+    case 1: launch_grad_src<R, 1>(src, g, it, grid, s); break;
+    case 2: launch_grad_src<R, 2>(src, g, it, grid, s); break;
+    case 3: launch_grad_src<R, 3>(src, g, it, grid, s); break;
     case 4:
         if (src == 2) {
-            launch_grad_k1<R, 4, 2>(g, grid, s);
+            launch_grad_k1<R, 4, 2>(g, it, grid, s);
             break;
         }
         [[fallthrough]];
-    default: launch_grad_src<R, 0>(src, g, grid, s);
+    default: launch_grad_src<R, 0>(src, g, it, grid, s);
     }
 }
 
-// Tiles of KC_TILE points covering [n_min, n_max): aligned to absolute
-// multiples of KC_TILE when regenerating, from n_min when points are given.
-void grad_tiles(bool given, int64_t n_min, int64_t n_max, int64_t *base, int64_t *tiles)
+// Tiles of KC_THREADS it points covering [n_min, n_max): aligned to absolute
+// multiples of their size when regenerating, from n_min when points are given.
+void grad_tiles(bool given, int it, int64_t n_min, int64_t n_max, int64_t *base, int64_t *tiles)
 {
-    *base = given ? n_min : (n_min / KC_TILE) * KC_TILE;
-    *tiles = (n_max - *base + KC_TILE - 1) / KC_TILE;
+    const int64_t tile = (int64_t)KC_THREADS * it;
+    *base = given ? n_min : (n_min / tile) * tile;
+    *tiles = (n_max - *base + tile - 1) / tile;
 }
 
 }  // namespace
@@ -396,7 +479,8 @@ extern "C" size_t ldk_kernel_grad_workspace_bytes(int R, int d, int64_t n_min, i
 {
     if (R < 1 || d < 1 || d > LDK_MAX_D || n_min < 0 || n_max < n_min) return 0;
     int64_t base, tiles;
-    grad_tiles(points_given != 0, n_min, n_max, &base, &tiles);
+    // the smallest tile gives the most partial sums
+    grad_tiles(points_given != 0, KC_ITERS, n_min, n_max, &base, &tiles);
     return (size_t)R * (size_t)tiles * (size_t)(d + 1) * sizeof(double);
 }
 
@@ -414,14 +498,17 @@ extern "C" int ldk_kernel_grad(const ldk_kernel *k, const ldk_pointset *ps, cons
     hipStream_t s = as_stream(stream);
     if (n_max == n_min) {
         // empty window: every sum is zero
-        hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 255) / 256, p.R), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 63) / 64, p.R), dim3(64 * KG_FINAL_WAVES), 0, s,
                            (const double *)nullptr, (int64_t)0, p.d, grad);
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }
     if (!a || !ws) return LDK_EINVAL;
     const bool given = pts != nullptr;
-    grad_tiles(given, n_min, n_max, &g.tile_base, &g.tiles);
+    int it = KC_ITERS;
+    g.dims_per_block = p.d;
+    if (k1 && !given) grad_split(p, n_max - n_min, dtype, &it, &g.dims_per_block);
+    grad_tiles(given, it, n_min, n_max, &g.tile_base, &g.tiles);
     if (g.tiles > 0x7fffffff) return LDK_ENOTSUP;
     g.a = a;
     g.k1 = k1;
@@ -429,10 +516,10 @@ extern "C" int ldk_kernel_grad(const ldk_kernel *k, const ldk_pointset *ps, cons
     const int src = given ? (p.kind == LDK_DNET_B2 ? 4 : 3)
                           : (p.kind == LDK_DNET_B2 ? 2 : (p.order == LDK_LINEAR ? 1 : 0));
     const dim3 grid((unsigned)g.tiles, (unsigned)p.R);
-    if (dtype == LDK_F64) launch_grad<double>(src, uniform, g, grid, s);
-    else launch_grad<float>(src, uniform, g, grid, s);
+    if (dtype == LDK_F64) launch_grad<double>(src, uniform, g, it, grid, s);
+    else launch_grad<float>(src, uniform, g, it, grid, s);
     LDK_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 255) / 256, p.R), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 63) / 64, p.R), dim3(64 * KG_FINAL_WAVES), 0, s,
                        (const double *)g.part, g.tiles, p.d, grad);
     LDK_LAUNCH_CHECK();
     return LDK_OK;

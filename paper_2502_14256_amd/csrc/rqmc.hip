@@ -10,7 +10,7 @@
 // with the same point
 // recurrences as the regenerating kernel column (plus the randomization's
 // shift), applies the integrand and sums in FP64 in a fixed order.
-#include "kfactor.hpp"
+#include "nettile.hpp"
 
 namespace ldk {
 
@@ -112,36 +112,40 @@ __device__ __forceinline__ void lattice_dot(const PointsetArgs &ps, const double
 // starting word.  The high and low words of a point are summed apart (no
 // product of the two conversions per point).
 template <int IT>
-__device__ __forceinline__ void net_dot(const KcolArgs &a, NetLds &L, const double *__restrict__ coef,
-                                        int r, int64_t tile0, double (&s)[IT])
+struct RqmcNetLds {
+    NetTables<uint64_t, KC_LOG_THREADS + log2_of(IT) + 1> t;
+    double c[NT_DIMS];
+    uint64_t sh[NT_DIMS];
+};
+template <int IT>
+__device__ __forceinline__ void net_dot(const KcolArgs &a, RqmcNetLds<IT> &L,
+                                        const double *__restrict__ coef, int r, int64_t tile0,
+                                        double (&s)[IT])
 {
-    constexpr int sft = KC_LOG_THREADS;
+    constexpr int NW = KC_LOG_THREADS + log2_of(IT) + 1;
     const int d = a.ps.d, t = threadIdx.x;
-    const bool gray = a.ps.order == LDK_GRAY;
-    const uint64_t code_tile = gray ? gray_code((uint64_t)tile0) : (uint64_t)tile0;
-    const uint32_t code_t = gray ? (uint32_t)gray_code((uint64_t)t) : (uint32_t)t;
     // sums of c_j hi_j and c_j lo_j for x = hi 2^-32 + lo 2^-64, scaled by
     // the powers of two once at the end (exactly)
     double s_lo[IT];
 #pragma unroll
     for (int l = 0; l < IT; ++l) s_lo[l] = 0.0;
-    for (int jc = 0; jc < d; jc += KC_DIM_CHUNK) {
-        const int DB = min(KC_DIM_CHUNK, d - jc);
-        build_net_chunk(a, L, r, jc, DB, code_tile);
+    for (int jc = 0; jc < d; jc += NT_DIMS) {
+        const int DB = min(NT_DIMS, d - jc);
+        build_net_tables(a.ps, L.t, r, jc, DB, (uint64_t)tile0, [&] {
+            if (t < DB) {
+                L.c[t] = coef[jc + t];
+                L.sh[t] = a.ps.shift ? a.ps.shift[(size_t)r * d + jc + t] : 0;
+            }
+        });
         for (int jj = 0; jj < DB; ++jj) {
-            const int j = jc + jj;
-            const uint64_t sh = a.ps.shift ? a.ps.shift[(size_t)r * d + j] : 0;
-            const double c = coef[j];
-            // the shift enters once: XOR steps commute with it
-            uint64_t z = L.zb[jj] ^ L.nib[jj][0][code_t & 15] ^ L.nib[jj][1][(code_t >> 4) & 15] ^ sh;
+            const double c = L.c[jj];
+            // the shift enters once: the step words commute with it
+            uint64_t z[IT];
+            net_points<IT>(L.t, jj, L.t.w[jj][NW - 1] ^ L.sh[jj], z);
 #pragma unroll
             for (int l = 0; l < IT; ++l) {
-                s[l] = fma(c, cvt_u32((uint32_t)(z >> 32)), s[l]);
-                s_lo[l] = fma(c, cvt_u32((uint32_t)z), s_lo[l]);
-                // past the last index of the net the step columns are zero
-                // (such points are masked by the caller)
-                const uint64_t nb = ((uint64_t)tile0 >> sft) + (uint64_t)l + 1;
-                if (l + 1 < IT) z ^= L.step[jj][ctz64(nb)];
+                s[l] = fma(c, cvt_u32((uint32_t)(z[l] >> 32)), s[l]);
+                s_lo[l] = fma(c, cvt_u32((uint32_t)z[l]), s_lo[l]);
             }
         }
     }
@@ -187,7 +191,7 @@ __global__ __launch_bounds__(KC_THREADS) void k_rqmc_tiles(KcolArgs a, const dou
 #pragma unroll
     for (int l = 0; l < IT; ++l) s[l] = 0.0;
     if constexpr (KIND == LDK_DNET_B2) {
-        __shared__ NetLds L;
+        __shared__ RqmcNetLds<IT> L;
         net_dot<IT>(a, L, coef, r, tile0, s);
     } else {
         lattice_dot<ORDER, IT>(a.ps, coef, r, tile0, s);

@@ -1,0 +1,83 @@
+"""GPU tests of the tile shapes of the regenerating kernels: the first column
+with 1, 4, 8 and 16 points per thread (chosen by the number of points) and the
+gradient split over dimensions.  Every shape forms a factor with the same
+roundings, so a window's column equals, bit for bit, the columns of its
+pieces; the gradient given the forward column is held to the gradient formed
+without it (both gated elsewhere against the oracle)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_14256_amd as ldk
+import workloads as W
+from ldk_dev import kernel, kernel_scale, pointset
+
+pytestmark = pytest.mark.gpu
+
+
+def _inst(kind, m, d, R, alpha):
+    w = W.small_lattice(31, m, d, R) if kind == "lattice" else W.small_net(32, m, d, R)
+    al = np.array([1 + j % 3 for j in range(d)]) if alpha == 0 else np.full(d, alpha)
+    w.update(alpha=al.astype(np.int32), gamma=0.8 ** np.arange(1, d + 1), zeta=1.1, sigma2=1e-3)
+    return w
+
+
+# points R (hi - lo): one below, at and above each step of the rule, windows
+# that start and end inside a tile; d across the 16-dimension table chunk
+WINDOWS = [(18, 1, 0, 2**18 - 1), (18, 1, 1, 2**18), (19, 1, 0, 2**19), (19, 3, 77, 2**19 - 5),
+           (20, 1, 5, 2**20), (20, 1, 0, 2**20), (18, 17, 300, 2**18 - 300)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("kind,order,alpha", [("dnet", "natural", 2), ("dnet", "gray", 4),
+                                              ("dnet", "gray", 0), ("dnet", "natural", 1),
+                                              ("dnet", "natural", 3), ("lattice", "natural", 2),
+                                              ("lattice", "linear", 0)])
+@pytest.mark.parametrize("m,R,lo,hi", WINDOWS)
+def test_column_equals_its_pieces(kind, order, alpha, dtype, m, R, lo, hi):
+    d = 17 if R == 1 else 3
+    w = _inst(kind, m, d, R, alpha)
+    k, ps = kernel(w), pointset(w, order)
+    full = ldk.kernel_column(k, ps, lo, hi, dtype=dtype)
+    step = 50000 // R  # pieces of one point per thread
+    for a in list(range(lo, hi, step))[:: max(1, (hi - lo) // step // 5)]:
+        b = min(a + step, hi)
+        part = ldk.kernel_column(k, ps, a, b, dtype=dtype)
+        assert torch.equal(full[:, a - lo:b - lo], part), (a, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("kind,order,alpha", [("dnet", "natural", 2), ("dnet", "gray", 0),
+                                              ("dnet", "gray", 4), ("lattice", "natural", 2),
+                                              ("lattice", "linear", 3)])
+@pytest.mark.parametrize("m,d,R,lo", [(4, 1, 1, 0), (11, 5, 1, 0), (12, 33, 2, 9), (16, 17, 3, 0),
+                                      (17, 70, 5, 1000), (16, 100, 20, 0)])
+def test_gradient_given_the_column(kind, order, alpha, dtype, m, d, R, lo):
+    w = _inst(kind, m, d, R, alpha)
+    w["gamma"] = w["gamma"] * 0.3
+    k, ps, n = kernel(w), pointset(w, order), 2**m
+    k1 = ldk.kernel_column(k, ps, lo, n, dtype=dtype)
+    g = torch.Generator("cuda").manual_seed(m)
+    a = torch.randn((R, n - lo), dtype=torch.float64, device="cuda", generator=g)
+    one = ldk.kernel_grad(k, ps, lo, n, a, dtype=dtype, k1=k1)
+    two = ldk.kernel_grad(k, ps, lo, n, a, dtype=dtype)
+    # each side within tol |a|_1 scale of the exact sums
+    tol = 1e-14 if dtype == torch.float64 else 2e-6
+    bound = 2 * tol * a.abs().sum(1, keepdim=True) * kernel_scale(w)
+    assert (one.isfinite() & ((one - two).abs() <= bound)).all()
+
+
+def test_gradient_with_a_zero_factor():
+    """A tile holding a zero k1_i (a factor exactly zero) forms the products
+    itself, also where the dimensions are split over blocks."""
+    d, m = 9, 12
+    w = _inst("dnet", m, d, 1, 1)
+    w["gamma"] = np.full(d, 0.3)
+    w["gamma"][4] = 2.0  # 1 + 2 K = 0 where K = 1 - 3/2 (beta = 1)
+    k, ps, n = kernel(w), pointset(w), 2**m
+    k1 = ldk.kernel_column(k, ps, 0, n)
+    assert (k1 == 0).any()
+    a = torch.randn((1, n), dtype=torch.float64, device="cuda")
+    one = ldk.kernel_grad(k, ps, 0, n, a, k1=k1)
+    two = ldk.kernel_grad(k, ps, 0, n, a)
+    assert (one - two).abs().max() <= 2e-14 * a.abs().sum() * kernel_scale(w)
