@@ -355,40 +355,125 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z)
     return z ^ (z >> 31);
 }
 
-// NUS: a block takes 64 consecutive indices of one replication, one per
-// lane; its eight waves split the dimensions of each tile of up to 64 and
-// the block stores the tile's rows (contiguous when d <= 64).
-__global__ __launch_bounds__(BP_TT) void k_gen_nus(int d, int m, int64_t n_min, int64_t cnt,
-                                                   const uint64_t *__restrict__ gen,
-                                                   const uint64_t *__restrict__ seed, double *__restrict__ out)
+// The word whose top bit says whether digit t of a point is flipped: the high
+// half of mix64(key XOR seed) (its last step leaves the top bit alone).  With
+// key = 2^(t-1) + (z >> (65 - t)), z the unscrambled word, the first step
+// w ^ (w >> 30) is linear and commutes with the shift, so zz = z ^ (z >> 30)
+// is formed once per point and c = seed ^ (seed >> 30) once per dimension:
+// 13 to 15 instructions a digit (23 with the key put together each time).
+__device__ __forceinline__ uint64_t mix_first(uint64_t v) { return v ^ (v >> 30); }
+__device__ __forceinline__ uint32_t nus_flip_word(uint64_t zz, uint64_t c, int t)
 {
-    double *tile = reinterpret_cast<double *>(g_bp_lds);  // [64][min(d, 64)]
+    uint64_t w = (t > 1 ? zz >> (65 - t) : 0) ^ (c ^ mix_first(1ull << (t - 1)));
+    w *= 0xbf58476d1ce4e5b9ull;
+    w = (w ^ (w >> 27)) * 0x94d049bb133111ebull;
+    return (uint32_t)(w >> 32);
+}
+// f with the top bit of w shifted in.
+__device__ __forceinline__ uint32_t shift_in(uint32_t f, uint32_t w) { return __builtin_amdgcn_alignbit(f, w, 31); }
+
+// NUS.  Bound by the 64 mixing functions a coordinate (VALU): the first
+// NUS_B digits have at most 2^NUS_B prefixes, so a block forms their flips
+// once per dimension, as a table over the top NUS_B digits, and a point mixes
+// the remaining 64 - NUS_B.  Block: NUS_D dimensions (one wave each), one
+// replication, `span` consecutive indices (a multiple of 64), 64 at a time,
+// one per lane; the word of an index is a lane word (its low 6 bits) XOR a
+// wave-uniform one.  The tile of 64 points x NUS_D coordinates goes out in
+// runs of 8 NUS_D bytes per point (less than a tenth of the store
+// bandwidth is in use).  R = 16, d = 52, n = 2^16: 2.10 -> 1.14 ms.
+constexpr int NUS_B = 12;  // table digits: 8 KiB per dimension, 2^12 mixing functions per block
+constexpr int NUS_D = 4;
+constexpr int NUS_T = 64 * NUS_D;
+// Orders a wave's own LDS accesses (they complete in order in the hardware).
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+__global__ __launch_bounds__(NUS_T) void k_gen_nus(int d, int m, int B, int span, int64_t n_min, int64_t cnt,
+                                                   const uint64_t *__restrict__ gen,
+                                                   const uint64_t *__restrict__ seed,
+                                                   double *__restrict__ out)
+{
+    __shared__ uint16_t table[NUS_D][1 << NUS_B];  // [top B digits] -> their flips
+    __shared__ double tile[64][NUS_D + 1];
     const int tid = threadIdx.x, lane = tid & 63, r = blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t i0 = (int64_t)blockIdx.x * BP_P;
-    const int64_t ii = i0 + lane;
-    const uint64_t i = (uint64_t)(n_min + (ii < cnt ? ii : 0));
-    for (int j0 = 0; j0 < d; j0 += BP_DCH) {
-        const int dch = d - j0 < BP_DCH ? d - j0 : BP_DCH;
-        for (int jj = wave; jj < dch; jj += BP_WAVES) {
-            const int j = j0 + jj;
-            uint64_t z = 0;
-            for (int k = 0; k < m; ++k)
-                if ((i >> k) & 1u) z ^= gen[(size_t)j * m + k];
-            const uint64_t s = seed[(size_t)r * d + j];
-            // the flip of digit t keyed by the digits above it; the bit
-            // position of digit t is 64 - t
-            uint64_t flips = mix64(1ull ^ s) & 0x8000000000000000ull;
-            for (int t = 2; t <= 64; ++t) {
-                const uint64_t key = (1ull << (t - 1)) | (z >> (65 - t));
-                flips |= (mix64(key ^ s) >> 63) << (64 - t);
+    // blocks of the same points are neighbours: their runs share cache lines
+    const int groups = (d + NUS_D - 1) / NUS_D;
+    const int j0 = (int)(blockIdx.x % groups) * NUS_D, dims = d - j0 < NUS_D ? d - j0 : NUS_D;
+    const int j = j0 + (wave < dims ? wave : 0);  // idle waves repeat dimension j0
+    const uint64_t s = seed[(size_t)r * d + j];
+    const uint64_t *__restrict__ col = gen + (size_t)j * m;
+    uint16_t *const tab = table[wave];
+    const uint64_t cs = mix_first(s);
+    // flips of the top b digits from those of the top b - 1: entry q becomes
+    // 2 q and 2 q + 1.  The wave goes from the last entries down, so that an
+    // entry is read before it is overwritten: a step reads entries q0 .. q0 +
+    // 63 and then writes 2 q0 .. 2 q0 + 127.
+    if (lane == 0) tab[0] = 0;
+    for (int b = 1; b <= B; ++b) {
+        const int half = 1 << (b - 1);
+        for (int q0 = (half - 1) & ~63; q0 >= 0; q0 -= 64) {
+            const int q = q0 + lane;
+            wave_lds_fence();
+            const uint32_t up = q < half ? tab[q] : 0;
+            wave_lds_fence();
+            if (q < half) {
+                const uint64_t zq = b > 1 ? (uint64_t)q << (65 - b) : 0;
+                const uint16_t v = (uint16_t)shift_in(up, nus_flip_word(mix_first(zq), cs, b));
+                tab[2 * q] = v;
+                tab[2 * q + 1] = v;
             }
-            tile[lane * dch + jj] = unit_f64(z ^ flips);
         }
-        __syncthreads();
-        flush_tile(out, tile, cnt, d, r, i0, j0, dch, tid);
-        __syncthreads();  // the tile is free for the next dimensions
     }
+    wave_lds_fence();
+    // word of the low 6 index bits, and of the tile's
+    const int64_t first = n_min + (int64_t)(blockIdx.x / groups) * span;
+    const int64_t lo = first & ~(int64_t)63;  // tiles at multiples of 64
+    uint64_t zl = 0, zu = 0;
+    for (int k = 0; k < 6 && k < m; ++k)
+        if ((lane >> k) & 1) zl ^= col[k];
+    for (int k = 6; k < m; ++k) zu ^= col[k] & -(uint64_t)((lo >> k) & 1);
+    const int64_t end = first + span < n_min + cnt ? first + span : n_min + cnt;
+    for (int64_t i0 = lo; i0 < end; i0 += 64) {
+        const uint64_t z = zl ^ zu, zz = mix_first(z);
+        // c's XORs with the 52 constants stay in the loop, on the scalar unit
+        // (hoisted, they spill the scalar registers)
+        uint64_t c = cs;
+        asm volatile("" : "+s"(c));
+        uint32_t fh = B ? tab[z >> (64 - B)] : 0, fl = 0;
+        for (int t = B + 1; t <= NUS_B; ++t) fh = shift_in(fh, nus_flip_word(zz, c, t));
+#pragma unroll
+        for (int t = NUS_B + 1; t <= 32; ++t) fh = shift_in(fh, nus_flip_word(zz, c, t));
+#pragma unroll
+        for (int t = 33; t <= 64; ++t) fl = shift_in(fl, nus_flip_word(zz, c, t));
+        __syncthreads();  // the previous tile is out
+        tile[lane][wave] = unit_f64(z ^ (((uint64_t)fh << 32) | fl));
+        __syncthreads();
+        const int p = tid / NUS_D, q = tid % NUS_D;
+        const int64_t i = i0 + p;
+        if (q < dims && i >= first && i < end)
+            out[((size_t)r * cnt + (i - n_min)) * d + j0 + q] = tile[p][q];
+        // the next tile flips the index bits from 6 up to its lowest zero one
+        for (int k = 6; k < m; ++k) {
+            zu ^= col[k];
+            if (!((i0 >> k) & 1)) break;
+        }
+    }
+}
+
+// Indices per NUS block and table digits: the longest span that leaves about
+// ten blocks per compute unit (the tail of the last round of blocks is a
+// tenth of the launch), 64 at least, and a table of at most a sixteenth of
+// the span's points, so that forming it costs a thousandth of using it per
+// digit saved.
+struct NusSplit {
+    int span, B;
+};
+NusSplit nus_split(int64_t cnt, int64_t columns)
+{
+    int span = 64;
+    while (span < 8192 && (cnt + 2 * span - 1) / (2 * span) * columns >= 2560) span *= 2;
+    NusSplit s{span, 0};
+    while (s.B < NUS_B && (2 << s.B) <= span / 2) ++s.B;
+    return s;
 }
 
 bool is_prime(int v)
@@ -473,11 +558,12 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
     if (st) return st;
     hipStream_t s = as_stream(stream);
     if (ps->kind == LDK_DNET_NUS) {
-        const int64_t blocks = (cnt + BP_P - 1) / BP_P;
-        if (blocks > 0x7fffffff) return LDK_ENOTSUP;
-        const size_t lds = (size_t)BP_P * (ps->d < BP_DCH ? ps->d : BP_DCH) * sizeof(double);
-        hipLaunchKernelGGL(k_gen_nus, dim3((unsigned)blocks, (unsigned)ps->R), dim3(BP_TT), lds, s, ps->d,
-                           ps->m, n_min, cnt, ps->gen, ps->seed, out);
+        const int64_t groups = (ps->d + NUS_D - 1) / NUS_D;
+        const NusSplit sp = nus_split(cnt, groups * ps->R);
+        const int64_t blocks = (cnt + sp.span - 1) / sp.span * groups;
+        if ((uint64_t)blocks * NUS_T > 0xffffffffull) return LDK_ENOTSUP;
+        hipLaunchKernelGGL(k_gen_nus, dim3((unsigned)blocks, (unsigned)ps->R), dim3(NUS_T),
+                           0, s, ps->d, ps->m, sp.B, sp.span, n_min, cnt, ps->gen, ps->seed, out);
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }

@@ -1,6 +1,6 @@
 """GPU tests of the tile shapes of the regenerating kernels: the first column
 with 1, 4, 8 and 16 points per thread (chosen by the number of points) and the
-gradient split over dimensions.  Every shape forms a factor with the same
+gradient split over dimensions, and of the nested scrambling's blocks.  Every column shape forms a factor with the same
 roundings, so a window's column equals, bit for bit, the columns of its
 pieces; the gradient given the forward column is held to the gradient formed
 without it (both gated elsewhere against the oracle)."""
@@ -10,7 +10,7 @@ import torch
 
 import paper_2502_14256_amd as ldk
 import workloads as W
-from ldk_dev import kernel, kernel_scale, pointset
+from ldk_dev import dev_u64, kernel, kernel_scale, pointset
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +81,20 @@ def test_gradient_with_a_zero_factor():
     one = ldk.kernel_grad(k, ps, 0, n, a, k1=k1)
     two = ldk.kernel_grad(k, ps, 0, n, a)
     assert (one - two).abs().max() <= 2e-14 * a.abs().sum() * kernel_scale(w)
+
+
+@pytest.mark.parametrize("R,d,m,lo,hi", [(1, 1, 7, 3, 128), (3, 5, 17, 37, 2**17 - 11),
+                                         (16, 9, 16, 1, 2**16), (32, 61, 14, 0, 2**14),
+                                         (2, 52, 20, 2**19 + 5, 2**20)])
+def test_nus_block_shapes(orc, R, d, m, lo, hi):
+    """Short and long blocks, flip tables of 0 to 12 digits, windows that
+    start inside a tile of 64, dimensions that do not fill a block: bit-exact
+    at both ends and in the middle."""
+    t = W.small_net(m, m, d)
+    seed = W.nus_seeds(m, R, d)
+    ps = ldk.BPointSet("nus", R, d, gen=dev_u64(t["gen"]), seed=dev_u64(seed), m=m)
+    x = ldk.gen_bpoints(ps, lo, hi).cpu().numpy()
+    mid = (lo + hi) // 2
+    for a, b in ((lo, min(lo + 70, hi)), (mid, min(mid + 70, hi)), (max(lo, hi - 70), hi)):
+        ref = orc.unit_points(orc.nus_points(t["gen"], seed, m, a, b))
+        assert np.array_equal(x[:, a - lo:b - lo], ref), (a, b)
