@@ -253,12 +253,37 @@ constexpr int RQ_PTS_GROUPS = KC_THREADS / RQ_PTS_W;  // point groups of a block
 constexpr int RQ_PTS_TILE = RQ_PTS_GROUPS * RQ_PTS_W; // points per block: each group takes 16
 constexpr int RQ_PTS_MAX_D = 128;               // coefficients per lane: d / 16 <= 8
 
+// Sum over the 16 lanes of a row, in every lane, by lane moves within the
+// vector unit: neighbours, pairs, then the mirror of 8 and of 16 lanes, whose
+// lanes hold one sum per 4 and per 8 lanes (the order of a butterfly).
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+__device__ __forceinline__ double row_sum(double v)
+{
+    v += row_move<0xb1>(v);   // quad_perm [1,0,3,2]
+    v += row_move<0x4e>(v);   // quad_perm [2,3,0,1]
+    v += row_move<0x141>(v);  // row_half_mirror
+    v += row_move<0x140>(v);  // row_mirror
+    return v;
+}
+
 // Group g of 16 lanes reads the rows of points first + g + 16 it (it < 16):
 // lane q takes coordinates q, q + 16, ..., so a wave's four groups read four
 // consecutive rows, whole cache lines per load.  The 16-lane sum of each
 // dot product lands in every lane of the group; lane q keeps the one of
-// it == q, and every lane then evaluates one integrand.
-template <int F>
+// it == q, and every lane then evaluates one integrand.  Bound by the one
+// read of the coordinates, so the rows of RQ_PTS_BATCH points are loaded
+// before any is summed: K = ceil(d / 16) loads a point with no branch between
+// them (past the last dimension, and past the last point, a lane repeats one
+// it may read and drops the value).
+constexpr int RQ_PTS_BATCH = 4;
+template <int F, int K>
 __global__ __launch_bounds__(KC_THREADS) void k_rqmc_pts(const double *__restrict__ x, int d,
                                                          int64_t n, const double *__restrict__ coef,
                                                          double phase, double *__restrict__ part)
@@ -266,36 +291,52 @@ __global__ __launch_bounds__(KC_THREADS) void k_rqmc_pts(const double *__restric
     __shared__ double red[KC_THREADS / 64];
     const int r = blockIdx.y, t = threadIdx.x;
     const int q = t & (RQ_PTS_W - 1), g = t / RQ_PTS_W;
-    double c[RQ_PTS_MAX_D / RQ_PTS_W];
+    const int jl = q + RQ_PTS_W * (K - 1);  // the one coordinate that may lie past d
+    const bool has = jl < d;
+    double c[K];
 #pragma unroll
-    for (int k = 0; k < RQ_PTS_MAX_D / RQ_PTS_W; ++k) {
-        const int j = q + RQ_PTS_W * k;
-        c[k] = j < d ? coef[j] : 0.0;
-    }
+    for (int k = 0; k < K; ++k) c[k] = k < K - 1 || has ? coef[q + RQ_PTS_W * k] : 0.0;
     const int64_t first = (int64_t)blockIdx.x * RQ_PTS_TILE + g;
     double mine = 0.0;
-#pragma unroll 2
-    for (int it = 0; it < RQ_PTS_W; ++it) {
-        const int64_t p = first + (int64_t)RQ_PTS_W * it;
-        double s = 0.0;
-        if (p < n) {
-            const double *row = x + ((size_t)r * n + p) * d;
+    for (int it0 = 0; it0 < RQ_PTS_W; it0 += RQ_PTS_BATCH) {
+        double v[RQ_PTS_BATCH][K];
 #pragma unroll
-            for (int k = 0; k < RQ_PTS_MAX_D / RQ_PTS_W; ++k) {
-                const int j = q + RQ_PTS_W * k;
-                if (j < d) s = fma(c[k], row[j], s);
-            }
+        for (int b = 0; b < RQ_PTS_BATCH; ++b) {
+            const int64_t p = first + (int64_t)RQ_PTS_W * (it0 + b);
+            const double *row = x + ((size_t)r * n + (p < n ? p : n - 1)) * d;
+#pragma unroll
+            for (int k = 0; k < K - 1; ++k) v[b][k] = row[q + RQ_PTS_W * k];
+            v[b][K - 1] = row[has ? jl : d - 1];
         }
-        s += __shfl_xor(s, 1, 64);
-        s += __shfl_xor(s, 2, 64);
-        s += __shfl_xor(s, 4, 64);
-        s += __shfl_xor(s, 8, 64);
-        if (it == q) mine = s;
+#pragma unroll
+        for (int b = 0; b < RQ_PTS_BATCH; ++b) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < K - 1; ++k) s = fma(c[k], v[b][k], s);
+            s = fma(c[K - 1], has ? v[b][K - 1] : 0.0, s);
+            s = row_sum(s);
+            if (it0 + b == q) mine = s;
+        }
     }
     const int64_t pm = first + (int64_t)RQ_PTS_W * q;
     const double acc = pm < n ? integrand<F>(mine, d, phase) : 0.0;
     const double tot = block_sum<KC_THREADS>(acc, red);
     if (threadIdx.x == 0) part[(size_t)r * gridDim.x + blockIdx.x] = tot;
+}
+
+template <int F>
+void launch_pts(dim3 grid, hipStream_t s, const double *x, int d, int64_t n, const double *coef,
+                double phase, double *part)
+{
+#define RQ_PTS_K(K)                                                                                \
+    case K:                                                                                        \
+        hipLaunchKernelGGL((k_rqmc_pts<F, K>), grid, dim3(KC_THREADS), 0, s, x, d, n, coef, phase, \
+                           part);                                                                  \
+        break;
+    switch ((d + RQ_PTS_W - 1) / RQ_PTS_W) {
+        RQ_PTS_K(1) RQ_PTS_K(2) RQ_PTS_K(3) RQ_PTS_K(4) RQ_PTS_K(5) RQ_PTS_K(6) RQ_PTS_K(7) RQ_PTS_K(8)
+    }
+#undef RQ_PTS_K
 }
 
 constexpr int RQ_IT_FULL = 8, RQ_IT_SMALL = 2;
@@ -430,12 +471,8 @@ extern "C" int ldk_rqmc_points(int R, int64_t n, int d, const double *x, int int
     double *part = static_cast<double *>(ws);
     const dim3 grid((unsigned)tiles, (unsigned)R);
     const double phase = 6.283185307179586476925286766559 * u;
-    if (integrand == LDK_GENZ_CORNER_PEAK)
-        hipLaunchKernelGGL(k_rqmc_pts<LDK_GENZ_CORNER_PEAK>, grid, dim3(KC_THREADS), 0, s, x, d, n,
-                           coef, phase, part);
-    else
-        hipLaunchKernelGGL(k_rqmc_pts<LDK_GENZ_OSCILLATORY>, grid, dim3(KC_THREADS), 0, s, x, d, n,
-                           coef, phase, part);
+    if (integrand == LDK_GENZ_CORNER_PEAK) launch_pts<LDK_GENZ_CORNER_PEAK>(grid, s, x, d, n, coef, phase, part);
+    else launch_pts<LDK_GENZ_OSCILLATORY>(grid, s, x, d, n, coef, phase, part);
     LDK_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_rqmc_final, dim3(1), dim3(RQ_FINAL_THREADS), 0, s, (const double *)part,
                        (int)tiles, R, (double)n, t, mu_r, stats);
