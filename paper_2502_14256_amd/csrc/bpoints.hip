@@ -14,14 +14,14 @@
 // b.  T digits are kept, the largest T with b^T <= 2^53, so the coordinate is
 // the integer v = sum_t z_t b^(T-1-t) < 2^53 divided by b^T, rounded once.
 //
-// A block takes 512 consecutive indices of one replication (two per thread)
-// and walks the dimensions.  The digits of an index live in registers, four
-// to a 32-bit word, so a row of S (or of Faure's C) times the digit vector is
-// one v_dot4_u32_u8 per word; the sum stays below 2^21 and is reduced mod b
-// with an exact 24-bit reciprocal product.  Per dimension the block stages
-// S's rows, packed the same way, and the T x b table of the digit
-// permutation and shift combined, in LDS; the Faure matrices come packed
-// from a small kernel, formed once per call into the workspace.
+// A block takes 64 consecutive indices of one replication, one per lane; its
+// eight waves split the dimensions.  The digits of an index live in registers,
+// four to a 32-bit word, so a row of S (or of Faure's C) times the digit
+// vector is one v_dot4_u32_u8 per word; the sum stays below 2^21 and is
+// reduced mod b by a 32-bit reciprocal (32-bit products run at full rate
+// here).  Four output digits make one 32-bit integer before they join the
+// FP64 Horner sum.  The Faure matrices come packed from a small kernel, formed
+// once per call into the workspace.
 //
 // Nested uniform scrambling of a base-2 net (Sec. 4.3, NUS): the point word
 // z = C i (64 digits), then digit t = 1..64 is flipped when the top bit of
@@ -54,10 +54,12 @@ struct BpArgs {
     uint32_t lms_off;  // byte offset of lms within its first word
     // per dimension (Halton; Faure uses entry 0 for every dimension), 32-bit
     // words so that a uniform index reads them with scalar loads
-    uint32_t base[BP_MAX_D], T[BP_MAX_D], M[BP_MAX_D], L[BP_MAX_D];
-    uint32_t mg[BP_MAX_D];  // ceil(2^L / b)
-    double rb[BP_MAX_D];    // 1 / b, rounded
-    double bT[BP_MAX_D];    // b^T, exact
+    uint32_t base[BP_MAX_D], T[BP_MAX_D], M[BP_MAX_D];
+    uint32_t inv[BP_MAX_D];  // ceil(2^32 / b)
+    double rb[BP_MAX_D];     // 1 / b, rounded
+    double bT[BP_MAX_D], ibT[BP_MAX_D];  // b^T, exact; 1 / b^T, rounded
+    double bTM[BP_MAX_D];    // b^(T - min(M, T)), exact
+    uint32_t small;          // every index below 2^24: digits by one reciprocal product each
     // Halton: wave w computes dimensions ord[q] for wbeg[w] <= q < wbeg[w + 1]
     uint32_t ord[BP_MAX_D], wbeg[BP_WAVES + 1];
 };
@@ -99,14 +101,11 @@ __global__ __launch_bounds__(64) void k_faure_cmat(int b, int T, int mj, uint32_
         }
 }
 
-// s mod b for s < 2^21 and b <= 251.  With L = 21 + ceil(log2 b) and
-// mg = ceil(2^L / b) < 2^22, e = mg b - 2^L < b gives s e < 2^L, so
-// floor(s mg / 2^L) = floor(s / b) exactly; both factors fit 24 bits.
-__device__ __forceinline__ uint32_t mod_b(uint32_t s, uint32_t b, uint32_t mg, uint32_t L)
+// s mod b for s < 2^24 and b <= 251: with inv = ceil(2^32 / b), e = inv b -
+// 2^32 < b gives s e < 2^32, so floor(s inv / 2^32) = floor(s / b) exactly.
+__device__ __forceinline__ uint32_t mod_b(uint32_t s, uint32_t b, uint32_t inv)
 {
-    const uint64_t p = (uint64_t)(s & 0xffffffu) * (uint64_t)(mg & 0xffffffu);
-    const uint32_t q = __builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, L);
-    return s - __umul24(q, b);
+    return s - __umul24(__umulhi(s, inv), b);
 }
 
 // floor(x / b) and the remainder for x < 2^32: x RN(1/b) in FP64 lies within
@@ -128,16 +127,24 @@ __device__ __forceinline__ uint32_t div_b(uint32_t x, uint32_t b, double rb, uin
 // Base-b digits of an index, least significant first, four to a word
 // (digit k in byte k % 4 of word k / 4); M digits, the rest zero.
 template <int MJ>
-__device__ __forceinline__ void index_digits_packed(uint32_t x, uint32_t b, double rb, int M,
-                                                    uint32_t (&z)[MJ])
+__device__ __forceinline__ void index_digits_packed(const BpArgs &a, int j, uint32_t x, uint32_t (&z)[MJ])
 {
+    const uint32_t b = a.base[j], inv = a.inv[j];
+    const int M = a.M[j];
+    const double rb = a.rb[j];
 #pragma unroll
     for (int q = 0; q < MJ; ++q) z[q] = 0;
 #pragma unroll
     for (int k = 0; k < 4 * MJ; ++k)
         if (k < M) {
             uint32_t dg;
-            x = div_b(x, b, rb, dg);
+            if (a.small) {
+                const uint32_t q = __umulhi(x, inv);
+                dg = x - __umul24(q, b);
+                x = q;
+            } else {
+                x = div_b(x, b, rb, dg);
+            }
             z[k >> 2] |= dg << (8 * (k & 3));
         }
 }
@@ -168,71 +175,116 @@ __device__ __forceinline__ void lane_row(const uint32_t *__restrict__ W, uint64_
     }
 }
 
-// K consecutive output digits t0 .. t0+K-1 (all below T) of one coordinate:
-// w_t = (S z)_t mod b from row t of S (lane t's, by v_readlane), then
-// pi_t(w_t) (K gathers in flight together), then + delta_t mod b, each
-// joining the Horner sum.
-template <int K, int MJ, int F>
-__device__ __forceinline__ void digit_group(const uint32_t (&srows)[MJ], uint32_t dlane, const uint8_t *prow,
-                                            const uint32_t (&z)[MJ], int t0, uint32_t b, uint32_t mg,
-                                            uint32_t L, double bd, double &v)
+// K <= 4 consecutive output digits of one coordinate: their values g before
+// the permutation go through pi_t (K gathers in flight together) and + delta_t
+// mod b, and join the Horner sum as one integer below b^K < 2^32.
+template <int K, int F>
+__device__ __forceinline__ void digits_join(uint32_t (&g)[K], uint32_t dlane, const uint8_t *prow, int t0, uint32_t b,
+                                            double bK, double &v)
 {
-    constexpr bool LMS = F & LDK_BR_LMS, DP = F & LDK_BR_DP, DS = F & LDK_BR_DS;
+    if constexpr (F & LDK_BR_DP) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) g[k] = prow[(t0 + k) * 256 + g[k]];
+    }
+    if constexpr (F & LDK_BR_DS) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            g[k] += __builtin_amdgcn_readlane(dlane, t0 + k);
+            g[k] = min(g[k], g[k] - b);  // the difference wraps where it is negative
+        }
+    }
+    uint32_t acc = g[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k) acc = __umul24(acc, b) + g[k];  // acc below b^3 < 2^24
+    v = fma(v, bK, (double)acc);
+}
+// Digits t0 .. t0 + K - 1 (all below T) of S z mod b: row t of S is lane t's,
+// read by v_readlane.
+template <int K, int MJ, int F>
+__device__ __forceinline__ void digits_lms(const uint32_t (&srows)[MJ], uint32_t dlane, const uint8_t *prow,
+                                           const uint32_t (&z)[MJ], int t0, uint32_t b, uint32_t inv, double bK,
+                                           double &v)
+{
     uint32_t g[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int t = t0 + k;
         uint32_t s = 0;
 #pragma unroll
-        for (int q = 0; q < MJ; ++q) {
-            uint32_t sr;
-            if constexpr (LMS) sr = __builtin_amdgcn_readlane(srows[q], t);
-            else sr = (t >> 2) == q ? 1u << (8 * (t & 3)) : 0u;
-            s = __builtin_amdgcn_udot4(sr, z[q], s, false);
-        }
-        const uint32_t w = mod_b(s, b, mg, L);
-        if constexpr (DP) g[k] = prow[t * 256 + w];
-        else g[k] = w;
+        for (int q = 0; q < MJ; ++q)
+            s = __builtin_amdgcn_udot4(__builtin_amdgcn_readlane(srows[q], t0 + k), z[q], s, false);
+        g[k] = mod_b(s, b, inv);
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        uint32_t u = g[k];
-        if constexpr (DS) {
-            u += __builtin_amdgcn_readlane(dlane, t0 + k);
-            if (u >= b) u -= b;
-        }
-        v = fma(v, bd, (double)u);
-    }
+    digits_join<K, F>(g, dlane, prow, t0, b, bK, v);
 }
 
-// Coordinate of one point in dimension j of replication r (rj = r d + j):
-// digit t of the output is w_t = (S z)_t mod b, then pi_t(w_t), then
-// + delta_t mod b (each step as the flags F ask); Horner's rule in FP64 is
-// exact (every partial sum is an integer below 2^53) and the one division
-// rounds.  The wave's lanes first fetch one row of S and one delta each.
-// With permutations the digits go four at a time (four gathers in flight),
-// the last T mod 4 one at a time.
+// Coordinate of one point in dimension j of replication r (rj = r d + j,
+// parameters at index p): digit t of the output is w_t = (S z)_t mod b, then
+// pi_t(w_t), then + delta_t mod b (each step as the flags F ask); Horner's
+// rule in FP64 is exact (every partial sum is an integer below 2^53) and the
+// one division rounds.  The wave's lanes first fetch one row of S and one
+// delta each.  Digits go four at a time, as one 32-bit integer each four.
+// Without S the digits past the index's own M are zero before the
+// permutation, the same for every lane (skipped where nothing maps them).
+// v / b^T from the rounded reciprocal: two corrections by the exact remainder
+// (the first leaves less than an ulp, the second then rounds correctly).
 template <int MJ, int F>
-__device__ __forceinline__ double coordinate(const BpArgs &a, const uint32_t *__restrict__ lmsw,
+__device__ __forceinline__ double coordinate(const BpArgs &a, int p, const uint32_t *__restrict__ lmsw,
                                              const uint8_t *__restrict__ shift,
                                              const uint8_t *__restrict__ perm, const uint32_t (&z)[MJ],
-                                             size_t rj, int T, uint32_t b, uint32_t mg, uint32_t L,
-                                             double bT, int lane)
+                                             size_t rj, int lane)
 {
     constexpr bool LMS = F & LDK_BR_LMS, DP = F & LDK_BR_DP, DS = F & LDK_BR_DS;
     const uint8_t *prow = DP ? perm + rj * BP_T * 256 : nullptr;
-    const double bd = (double)b;
-    uint32_t srows[MJ] = {};
-    if constexpr (LMS)
-        lane_row<MJ>(lmsw, a.lms_off + ((uint64_t)rj * BP_T + lane) * BP_T, lane, T, srows);
+    const uint32_t b = a.base[p], inv = a.inv[p];
+    const int T = a.T[p];
+    const double bd = (double)b, b2 = bd * bd, b4 = b2 * b2;
     uint32_t dlane = 0;
     if constexpr (DS) dlane = lane < T ? shift[rj * BP_T + lane] : 0u;
     double v = 0.0;
-    int t0 = 0;
-    if constexpr (DP)
-        for (; t0 + 4 <= T; t0 += 4) digit_group<4, MJ, F>(srows, dlane, prow, z, t0, b, mg, L, bd, v);
-    for (; t0 < T; ++t0) digit_group<1, MJ, F>(srows, dlane, prow, z, t0, b, mg, L, bd, v);
-    return v / bT;
+    if constexpr (LMS) {
+        uint32_t srows[MJ];
+        lane_row<MJ>(lmsw, a.lms_off + ((uint64_t)rj * BP_T + lane) * BP_T, lane, T, srows);
+        int t0 = 0;
+        for (; t0 + 4 <= T; t0 += 4) digits_lms<4, MJ, F>(srows, dlane, prow, z, t0, b, inv, b4, v);
+        if (t0 + 2 <= T) {
+            digits_lms<2, MJ, F>(srows, dlane, prow, z, t0, b, inv, b2, v);
+            t0 += 2;
+        }
+        if (t0 < T) digits_lms<1, MJ, F>(srows, dlane, prow, z, t0, b, inv, bd, v);
+    } else {
+        // with a map every digit takes part; those past M start from zero
+        const int rows = DP || DS ? T : min(T, (int)a.M[p]);
+#pragma unroll
+        for (int q = 0; q < MJ; ++q) {
+            uint32_t g[4] = {z[q] & 255u, (z[q] >> 8) & 255u, (z[q] >> 16) & 255u, z[q] >> 24};
+            if (4 * q + 4 <= rows) {
+                digits_join<4, F>(g, dlane, prow, 4 * q, b, b4, v);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    uint32_t one[1] = {g[k]};
+                    if (4 * q + k < rows) digits_join<1, F>(one, dlane, prow, 4 * q + k, b, bd, v);
+                }
+            }
+        }
+        if constexpr (DP || DS) {
+            int t0 = 4 * MJ;
+            for (; t0 + 4 <= T; t0 += 4) {
+                uint32_t g[4] = {0, 0, 0, 0};
+                digits_join<4, F>(g, dlane, prow, t0, b, b4, v);
+            }
+            for (; t0 < T; ++t0) {
+                uint32_t g[1] = {0};
+                digits_join<1, F>(g, dlane, prow, t0, b, bd, v);
+            }
+        } else {
+            v *= a.bTM[p];  // exact: below b^T
+        }
+    }
+    const double bT = a.bT[p], ib = a.ibT[p];
+    double q = v * ib;
+    q = fma(fma(-bT, q, v), ib, q);
+    return fma(fma(-bT, q, v), ib, q);
 }
 
 // Write a finished tile: rows p < valid of dimensions j0 .. j0+dch-1 of the
@@ -260,17 +312,20 @@ __device__ __forceinline__ double halton_coordinate(const BpArgs &a, const uint3
                                                     const uint8_t *__restrict__ perm, uint32_t i, int r,
                                                     int j, int lane)
 {
-    const uint32_t b = a.base[j];
     uint32_t z[MJ];
-    index_digits_packed<MJ>(i, b, a.rb[j], a.M[j], z);
-    return coordinate<MJ, F>(a, lmsw, shift, perm, z, (size_t)r * a.d + j, a.T[j], b, a.mg[j], a.L[j],
-                             a.bT[j], lane);
+    index_digits_packed<MJ>(a, j, i, z);
+    return coordinate<MJ, F>(a, j, lmsw, shift, perm, z, (size_t)r * a.d + j, lane);
 }
 
 // Halton: a block takes 64 consecutive indices of one replication, one per
 // lane; its eight waves split the dimensions (a balanced order from the
 // host) and write into an LDS tile of whole rows, which the block then
-// stores as one contiguous run (d <= 54 fits one tile).
+// stores as one contiguous run (d <= 54 fits one tile).  Bound by VALU issue
+// and, with permutations, by the gathers of their bytes.  R = 16, n = 2^15,
+// d = 52 (us): no scrambles 106 -> 64, LMS + DP 196 -> 174 (194 -> 150 VALU
+// instructions a coordinate), LMS + DS 175 -> 151.  Staging S and the
+// permutations in LDS for longer spans of points measured no better (175 to
+// 185) and loses on small sets.
 template <int F>
 __global__ __launch_bounds__(BP_TT) void k_gen_halton(BpArgs a, const uint32_t *__restrict__ lmsw,
                                                       const uint8_t *__restrict__ shift,
@@ -319,10 +374,9 @@ __global__ __launch_bounds__(BP_TT) void k_gen_faure(BpArgs a, const uint32_t *_
     const int64_t i0 = (int64_t)blockIdx.x * BP_P;
     const int64_t ii = i0 + lane;
     const uint32_t i = (uint32_t)(a.n_min + (ii < a.cnt ? ii : 0));
-    const uint32_t b = a.base[0], mg = a.mg[0], L = a.L[0];
-    const int M = a.M[0], T = a.T[0];
+    const uint32_t b = a.base[0], inv = a.inv[0];
     uint32_t ad[MJ];
-    index_digits_packed<MJ>(i, b, a.rb[0], M, ad);
+    index_digits_packed<MJ>(a, 0, i, ad);
     for (int j0 = 0; j0 < a.d; j0 += BP_DCH) {
         const int dch = a.d - j0 < BP_DCH ? a.d - j0 : BP_DCH;
         for (int jj = wave; jj < dch; jj += BP_WAVES) {
@@ -337,10 +391,9 @@ __global__ __launch_bounds__(BP_TT) void k_gen_faure(BpArgs a, const uint32_t *_
                 uint32_t s = 0;
 #pragma unroll
                 for (int q = 0; q < MJ; ++q) s = __builtin_amdgcn_udot4(cj[t * MJ + q], ad[q], s, false);
-                z[t >> 2] |= mod_b(s, b, mg, L) << (8 * (t & 3));
+                z[t >> 2] |= mod_b(s, b, inv) << (8 * (t & 3));
             }
-            tile[lane * dch + jj] = coordinate<MJ, F>(a, lmsw, shift, perm, z, (size_t)r * a.d + j, T, b, mg,
-                                                      L, a.bT[0], lane);
+            tile[lane * dch + jj] = coordinate<MJ, F>(a, 0, lmsw, shift, perm, z, (size_t)r * a.d + j, lane);
         }
         __syncthreads();
         flush_tile(out, tile, a.cnt, a.d, r, i0, j0, dch, tid);
@@ -575,6 +628,7 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
     a.flags = ps->flags;
     a.n_min = n_min;
     a.cnt = cnt;
+    a.small = n_max <= (1 << 24);
     // lms is read as 32-bit words from the word boundary at or below its
     // first byte (the same word, so within the allocation's page)
     const uintptr_t lp = reinterpret_cast<uintptr_t>(ps->lms);
@@ -591,18 +645,18 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
             b = prime;
         }
         const int T = digits_kept(b), M = index_digits(b, n_max);
-        int lg = 0;
-        while ((1 << lg) < b) ++lg;
         if (M > BP_KMAX) return LDK_EINVAL;  // not reached for i < 2^32
         a.base[j] = (uint32_t)b;
         a.T[j] = (uint32_t)T;
         a.M[j] = (uint32_t)M;
-        a.L[j] = (uint32_t)(21 + lg);
-        a.mg[j] = (uint32_t)((((uint64_t)1 << (21 + lg)) + (uint64_t)b - 1) / (uint64_t)b);
+        a.inv[j] = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)b - 1) / (uint64_t)b);
         a.rb[j] = 1.0 / (double)b;
         double p = 1.0;
         for (int t = 0; t < T; ++t) p *= (double)b;
         a.bT[j] = p;
+        a.ibT[j] = 1.0 / p;
+        a.bTM[j] = 1.0;
+        for (int t = M; t < T; ++t) a.bTM[j] *= (double)b;
         m_max = M > m_max ? M : m_max;
         cost[j] = (double)T * (((M + 3) / 4) + 12) + 10.0 * M;  // VALU work per coordinate, roughly
     }
