@@ -395,6 +395,44 @@ int real_apply(int dtype, int mode, int m, int64_t rows, int nrhs, const double 
     return LDK_OK;
 }
 
+// The n -> 2n update's top pass on real rows of n (PM_UPDATE, PM_UPDATE_EIG;
+// rows and scale set in a): the new half y as packed rows of n/2 complex
+// entries (work, stride work_row), meeting `old` in the store into `full`
+// rows of 2n.
+int real_update(int dtype, int mode, int m, PassArgs a, const void *y, bool y_f32, const void *old, void *full,
+                void *work, int64_t work_row, hipStream_t s)
+{
+    const int mp = m - 1;
+    const int64_t N = (int64_t)1 << mp;
+    const Plan pl = make_plan(mp, log_tile_for(LDK_LATTICE, dtype));
+    const double scale = a.scale;
+    a.m = mp;
+    a.nrhs = 1;
+    a.half = N;
+    for (int p = 0; p < pl.P - 1; ++p) {
+        a.src = p == 0 ? y : work;
+        a.src_row = p == 0 ? 2 * N : work_row;
+        a.dst = work;
+        a.dst_row = work_row;
+        a.g = pl.pass[p];
+        a.global_tw = p > 0;
+        a.scale = 1.0;
+        const int st = launch_pass(LDK_LATTICE, dtype, PM_FWD, p == 0 ? PIO_PACKED : PIO_SAME, PIO_SAME, a, s,
+                                   p == 0 && y_f32);
+        if (st) return st;
+    }
+    const bool single = pl.P == 1;
+    a.src = single ? y : work;
+    a.src_row = single ? 2 * N : work_row;
+    a.dst = full;
+    a.dst_row = 4 * N;
+    a.old = old;
+    a.g = pl.pass[pl.P - 1];
+    a.global_tw = !single;
+    a.scale = scale;
+    return launch_real_top(dtype, mode, a, nullptr, s, single && y_f32);
+}
+
 // The fused fit (lattice, FP64, n >= 4): eigenvalues, every solve and the
 // log-det share the tile passes of the half-length packed transforms.
 bool fit_fused(int kind, int m, int dtype) { return kind == LDK_LATTICE && m >= 2 && dtype == LDK_F64; }
@@ -858,6 +896,16 @@ int ldk_update_double(int kind, int B, int m, int dtype, const void *yt_old, con
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }
+    if (real_path(kind, m)) {
+        // the new half is real: packed rows of n/2 (in the second halves of
+        // the output rows), and the top pass meets the old half's transform.
+        // A tile of the top pass reads the elements n + k, k < n/2, that it
+        // alone writes, so the update runs in place.
+        PassArgs a{};
+        a.rows = B;
+        a.scale = 1.0 / std::sqrt((double)n);
+        return real_update(dtype, PM_UPDATE, m, a, y_new, false, yt_old, yt_full, u, 2 * n, s);
+    }
     // the transform of the new half; intermediates of a multi-pass plan live
     // in the output rows' second halves (stride 2n), and the last pass meets
     // the old half's transform in its store (PIO_COMBINE) and writes both
@@ -909,6 +957,11 @@ int ldk_eig_update_double(int kind, int R, int m, int dtype, const double *lam_o
                                lam_full, k1_new, (int64_t)1, (int64_t)R, 0);
         LDK_LAUNCH_CHECK();
         return LDK_OK;
+    }
+    if (real_path(kind, m)) {
+        PassArgs a{};
+        a.rows = R;
+        return real_update(LDK_F64, PM_UPDATE_EIG, m, a, k1_new, dtype == LDK_F32, lam_old, lam_full, ws, n / 2, s);
     }
     // FP64 transform of the new half (k1 widened when FP32); intermediates of
     // a multi-pass plan in the workspace (lattice, complex) or in the output

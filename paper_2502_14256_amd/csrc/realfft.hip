@@ -37,6 +37,12 @@
 // the cubature: it weights |Y_k|^2 by lambda_k or 1 / (lambda_k + sigma2)
 // and sums the tile (into ld_part[row][cb]) instead of storing the spectrum,
 // and the tile holding k = 0 stores Y_0 = sum_j y_j (into lam_out[row]).
+//
+// PM_UPDATE and PM_UPDATE_EIG serve the n -> 2n update: the real new half's
+// spectrum meets the old half's transform a.old in the store, w_k = W_{2n}^k:
+//   PM_UPDATE      dst[k], dst[n+k] = (old_k +- scale w_k Y_k) / sqrt 2 (complex),
+//   PM_UPDATE_EIG  dst[k], dst[n+k] = old_k +- Re(w_k Y_k)              (FP64),
+// with dst rows of 2n and w_{k+N} = -i w_k.
 #include "passkit.hpp"
 
 namespace ldk {
@@ -148,6 +154,7 @@ __device__ __forceinline__ void real_top_body(const PassArgs &a, double *lam_out
     // across the transform (with the eigenvalue loads in flight) they took
     // every register and spilled.
     constexpr bool LATE = MODE == PM_SOLVE || MODE == PM_MATVEC;
+    constexpr bool UPDATE = MODE == PM_UPDATE || MODE == PM_UPDATE_EIG;
     T wkv[E];
     double f1[E], f2[E];
     // precomputed filter coefficients (p, q), when given: one pair per
@@ -272,6 +279,29 @@ __device__ __forceinline__ void real_top_body(const PassArgs &a, double *lam_out
             lam_out[row * n + k] = (double)yk.re * (double)yk.re + (double)yk.im * (double)yk.im;
             lam_out[row * n + k + N] =
                 (double)ykn.re * (double)ykn.re + (double)ykn.im * (double)ykn.im;
+        } else if constexpr (UPDATE) {
+            // the old half's values were not needed before: read here
+            const T w2 = tw_any<R>((uint64_t)k, mp + 2);  // W_{2n}^k
+            const T o1 = cmul(yk, w2), o2 = cmul(ykn, T{w2.im, -w2.re});
+            if constexpr (MODE == PM_UPDATE_EIG) {
+                const double *od = static_cast<const double *>(a.old) + row * n;
+                double *full = static_cast<double *>(a.dst) + row * a.dst_row;
+                const double d1 = od[k], d2 = od[k + N];
+                full[k] = d1 + (double)o1.re;
+                full[n + k] = d1 - (double)o1.re;
+                full[k + N] = d2 + (double)o2.re;
+                full[n + k + N] = d2 - (double)o2.re;
+            } else {
+                const R h = (R)0.70710678118654752440, sc = (R)a.scale;
+                const T *od = static_cast<const T *>(a.old) + row * n;
+                T *full = static_cast<T *>(a.dst) + row * a.dst_row;
+                const T d1 = od[k], d2 = od[k + N];
+                const T p1 = scl(o1, sc), p2 = scl(o2, sc);
+                full[k] = scl(add(d1, p1), h);
+                full[n + k] = scl(sub(d1, p1), h);
+                full[k + N] = scl(add(d2, p2), h);
+                full[n + k + N] = scl(sub(d2, p2), h);
+            }
         } else if constexpr (MODE == PM_QFORM) {
             const double p1 = (double)yk.re * (double)yk.re + (double)yk.im * (double)yk.im;
             const double p2 = (double)ykn.re * (double)ykn.re + (double)ykn.im * (double)ykn.im;
@@ -297,7 +327,7 @@ __device__ __forceinline__ void real_top_body(const PassArgs &a, double *lam_out
         }
         return;
     }
-    if constexpr (MODE == PM_POWER) return;
+    if constexpr (MODE == PM_POWER || UPDATE) return;
     if constexpr (MODE == PM_QFORM) {
         // block sum in a fixed order: lanes, then waves (a block of fewer
         // than 64 threads sums its threads through LDS)
@@ -578,10 +608,14 @@ int launch_ft(const PassArgs &aK, const PassArgs &aY, double *lam_out, double *l
     if (aK.g.b0 > 0 && aK.g.logW < 1) return LDK_ENOTSUP;
     const size_t lds = 2 * (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(cplx<double>);
     if constexpr (LOGE == 3 && LD == IO_SAME && ST == IO_SAME) {
-        // the fit's top pass at n = 2^19 .. 2^20 (8 axis bits, 8-column tiles)
-        if (aK.g.a == 8 && aK.g.logW == 3) {
-            hipLaunchKernelGGL((k_fit_top<LOGE, LD, ST, 8, 3>), dim3((unsigned)blocks), dim3(2 * Tn),
+        int st = LDK_OK;
+        const bool fixed = with_top_geometry<11>(aK.g, [&](auto ca) {
+            constexpr int A = ca();
+            hipLaunchKernelGGL((k_fit_top<LOGE, LD, ST, A, 11 - A>), dim3((unsigned)blocks), dim3(2 * Tn),
                                lds, s, aK, aY, lam_out, ld_part);
+            return LDK_OK;
+        }, st);
+        if (fixed) {
             LDK_LAUNCH_CHECK();
             return LDK_OK;
         }
@@ -623,26 +657,24 @@ int launch_rt(const PassArgs &a, double *lam_out, hipStream_t s, double *ld_part
     if (a.g.b0 + a.g.a != a.m) return LDK_EINVAL;  // must be the top pass
     if (a.g.b0 > 0 && a.g.logW < 1) return LDK_ENOTSUP;  // mirror runs need W >= 2
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(T);
-    if constexpr ((MODE == PM_SOLVE || (MODE == PM_FWD && !CF)) && LD == IO_SAME && ST == IO_SAME &&
-                  !SRC_F32 && LOGE == 3) {
-        // the solve's and the eigenvalues' top pass of the plans at n = 2^20
-        // (FP64: 8 axis bits, 8-column tiles; FP32: 7 axis bits, 32-column
-        // tiles): geometry fixed at compile time
-        constexpr bool F64 = std::is_same<T, cplx<double>>::value;
-        constexpr int TA = F64 ? 8 : 7, TLW = F64 ? 3 : 5;
-        if (a.g.a == TA && a.g.logW == TLW) {
-            bool pair = false;
-            if constexpr (CF) pair = a.nrhs % 2 == 0;
+    constexpr int TILE = std::is_same<T, cplx<double>>::value ? 11 : 12;
+    if constexpr (MODE != PM_MATVEC && LD == IO_SAME && ST == IO_SAME && !SRC_F32 && LOGE == 3) {
+        int st = LDK_OK;
+        const bool fixed = with_top_geometry<TILE>(a.g, [&](auto ca) {
+            constexpr int A = ca();
             if constexpr (CF) {
-                if (pair)
-                    hipLaunchKernelGGL((k_real_top<T, LOGE, MODE, LD, ST, SRC_F32, CF, TA, TLW, 2>),
+                if (a.nrhs % 2 == 0) {
+                    hipLaunchKernelGGL((k_real_top<T, LOGE, MODE, LD, ST, SRC_F32, CF, A, TILE - A, 2>),
                                        dim3((unsigned)(blocks / 2)), dim3(threads), lds, s, a,
                                        lam_out, ld_part);
+                    return LDK_OK;
+                }
             }
-            if (!pair)
-                hipLaunchKernelGGL((k_real_top<T, LOGE, MODE, LD, ST, SRC_F32, CF, TA, TLW>),
-                                   dim3((unsigned)blocks), dim3(threads), lds, s, a, lam_out,
-                                   ld_part);
+            hipLaunchKernelGGL((k_real_top<T, LOGE, MODE, LD, ST, SRC_F32, CF, A, TILE - A>),
+                               dim3((unsigned)blocks), dim3(threads), lds, s, a, lam_out, ld_part);
+            return LDK_OK;
+        }, st);
+        if (fixed) {
             LDK_LAUNCH_CHECK();
             return LDK_OK;
         }
@@ -758,7 +790,22 @@ int launch_real_top(int dtype, int mode, const PassArgs &a, double *lam_out, hip
         return launch_rt_e<cplx<float>, PM_QFORM, IO_SAME, IO_SAME, false>(a, lam_out, s, ld_part);
     }
     if (ld_part) return LDK_EINVAL;  // log-det partials come with the eigenvalues only
+    if (mode == PM_UPDATE_EIG) {
+        if (dtype != LDK_F64 || !a.old || (src_f32 && !single)) return LDK_EINVAL;
+        if (src_f32) return launch_rt_e<cplx<double>, PM_UPDATE_EIG, IO_PACKED, IO_SAME, true>(a, nullptr, s);
+        if (single) return launch_rt_e<cplx<double>, PM_UPDATE_EIG, IO_PACKED, IO_SAME, false>(a, nullptr, s);
+        return launch_rt_e<cplx<double>, PM_UPDATE_EIG, IO_SAME, IO_SAME, false>(a, nullptr, s);
+    }
     if (src_f32) return LDK_EINVAL;
+    if (mode == PM_UPDATE) {
+        if (!a.old) return LDK_EINVAL;
+        if (dtype == LDK_F64) {
+            if (single) return launch_rt_e<cplx<double>, PM_UPDATE, IO_PACKED, IO_SAME, false>(a, nullptr, s);
+            return launch_rt_e<cplx<double>, PM_UPDATE, IO_SAME, IO_SAME, false>(a, nullptr, s);
+        }
+        if (single) return launch_rt_e<cplx<float>, PM_UPDATE, IO_PACKED, IO_SAME, false>(a, nullptr, s);
+        return launch_rt_e<cplx<float>, PM_UPDATE, IO_SAME, IO_SAME, false>(a, nullptr, s);
+    }
     if (mode == PM_POWER) {
         if (!lam_out) return LDK_EINVAL;
         if (dtype == LDK_F64) {

@@ -200,14 +200,12 @@ __global__ __launch_bounds__(CA >= 0 ? (1 << (CA + CLW - LOGE)) : 512) void k_pa
     else pass_body<T, LOGE, MODE, LD, ST, SRC_F32, CA, CLW>(a1, b - nb0);
 }
 
-// The passes of the plans at n = 2^20 get kernels with their geometry
-// fixed at compile time: the lattice row passes (the packed half-length row
-// in one contiguous tile: 11 axis bits in FP64, also the row pass of every
-// FP64 lattice plan from n = 2^13; 12 in FP32), and the digital-net passes
-// (FP64 and FP32: 12 row bits, and the top pass with the filter over 8 bits
-// in 16-column tiles).
+// The passes of the default two-pass plans get kernels with their geometry
+// fixed at compile time: the lattice row passes (the packed half-length row in
+// contiguous tiles of up to 2^11 elements in FP64, 2^12 in FP32), and the
+// digital-net row passes (up to 2^12) and top passes (4 to 8 axis bits).
 template <typename T>
-constexpr int row_a()
+constexpr int tile_log()
 {
     return std::is_same<T, cplx<double>>::value ? 11 : 12;
 }
@@ -218,11 +216,10 @@ constexpr bool row_specialised()
     return !std::is_floating_point<T>::value && LOGE == 3 &&
            (!SRC_F32 || std::is_same<T, cplx<double>>::value);
 }
-constexpr int NET_ROW_A = 12, NET_TOP_A = 8, NET_TOP_LOGW = 4;
-template <typename T, int LOGE, bool SRC_F32>
+template <typename T, int LOGE>
 constexpr bool net_specialised()
 {
-    return std::is_floating_point<T>::value && LOGE == 3 && !SRC_F32;
+    return std::is_floating_point<T>::value && LOGE == 3;
 }
 
 // The fit of a net whose transform is one pass (the whole row in one tile),
@@ -275,35 +272,48 @@ int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
     if ((a.g.a + LOGE - 1) / LOGE > MAX_GROUPS) return LDK_ENOTSUP;  // group twiddle bases
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(T);
     const dim3 grid((unsigned)blocks), block(threads);
-    if constexpr (net_specialised<T, LOGE, SRC_F32>() && (MODE == PM_FWD || MODE == PM_INV)) {
-        if (ld == IO_SAME && st == IO_SAME && a.g.a == NET_ROW_A && a.g.logW == 0) {
-            hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_SAME, SRC_F32, NET_ROW_A, 0>), grid,
-                               block, lds, s, a);
-            LDK_LAUNCH_CHECK();
-            return LDK_OK;
-        }
+    constexpr int TILE = tile_log<T>();
+    int st_fixed = LDK_OK;
+    bool fixed = false;
+    if constexpr (net_specialised<T, LOGE>() && (MODE == PM_FWD || MODE == PM_INV)) {
+        if (ld == IO_SAME && st == IO_SAME && a.m > a.g.a)
+            fixed = with_row_geometry<TILE>(a.g, [&](auto ca) {
+                hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_SAME, SRC_F32, ca(), 0>), grid, block, lds,
+                                   s, a);
+                return LDK_OK;
+            }, st_fixed);
     }
-    if constexpr (net_specialised<T, LOGE, SRC_F32>() && MODE == PM_SOLVE) {
-        if (ld == IO_SAME && st == IO_SAME && a.g.a == NET_TOP_A && a.g.logW == NET_TOP_LOGW) {
-            hipLaunchKernelGGL(
-                (k_pass<T, LOGE, MODE, IO_SAME, IO_SAME, SRC_F32, NET_TOP_A, NET_TOP_LOGW>), grid,
-                block, lds, s, a);
-            LDK_LAUNCH_CHECK();
-            return LDK_OK;
-        }
+    if constexpr (net_specialised<T, LOGE>() && !SRC_F32 && (MODE == PM_FWD || MODE == PM_SOLVE)) {
+        if (!fixed && a.g.b0 > 0 && ld == IO_SAME)
+            fixed = with_top_geometry<TILE>(a.g, [&](auto ca) {
+                constexpr int A = ca(), W = TILE - A;
+                if constexpr (MODE == PM_FWD) {
+                    if (st == IO_POWER) {
+                        hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_POWER, false, A, W>), grid, block, lds, s, a);
+                        return LDK_OK;
+                    }
+                    if (st == IO_COMBINE) {
+                        hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_COMBINE, false, A, W>), grid, block, lds, s, a);
+                        return LDK_OK;
+                    }
+                }
+                hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_SAME, false, A, W>), grid, block, lds, s, a);
+                return LDK_OK;
+            }, st_fixed);
     }
     if constexpr (row_specialised<T, LOGE, SRC_F32>() && (MODE == PM_FWD || MODE == PM_INV)) {
-        constexpr int RA = row_a<T>();
-        if (a.g.a == RA && a.g.logW == 0) {
-            constexpr int LDs = MODE == PM_FWD ? IO_PACKED : IO_SAME;
-            constexpr int STs = MODE == PM_FWD ? IO_SAME : IO_PACKED;
-            if (ld == LDs && st == STs) {
-                hipLaunchKernelGGL((k_pass<T, LOGE, MODE, LDs, STs, SRC_F32, RA, 0>), grid, block,
-                                   lds, s, a);
-                LDK_LAUNCH_CHECK();
+        constexpr int LDs = MODE == PM_FWD ? IO_PACKED : IO_SAME;
+        constexpr int STs = MODE == PM_FWD ? IO_SAME : IO_PACKED;
+        if (ld == LDs && st == STs)
+            fixed = with_row_geometry<TILE>(a.g, [&](auto ca) {
+                hipLaunchKernelGGL((k_pass<T, LOGE, MODE, LDs, STs, SRC_F32, ca(), 0>), grid, block, lds, s, a);
                 return LDK_OK;
-            }
-        }
+            }, st_fixed);
+    }
+    if (fixed) {
+        if (st_fixed) return st_fixed;
+        LDK_LAUNCH_CHECK();
+        return LDK_OK;
     }
 #define LDK_PASS(LD_, ST_) hipLaunchKernelGGL((k_pass<T, LOGE, MODE, LD_, ST_, SRC_F32>), grid, block, lds, s, a)
     if constexpr (std::is_floating_point<T>::value) {
@@ -580,12 +590,14 @@ int launch_fwd2(const PassArgs &a0, const PassArgs &a1, hipStream_t s)
     if ((a0.g.a + LOGE - 1) / LOGE > MAX_GROUPS) return LDK_ENOTSUP;
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(T);
     if constexpr (row_specialised<T, LOGE, false>() && LD == IO_PACKED) {
-        constexpr int RA = row_a<T>();
-        if (a0.g.a == RA && a0.g.logW == 0) {
-            hipLaunchKernelGGL((k_pass2<T, LOGE, PM_FWD, LD, IO_SAME, false, RA, 0>),
-                               dim3((unsigned)(nb0 + nb1)), dim3(threads), lds, s, a0, a1, nb0);
+        int st = LDK_OK;
+        if (with_row_geometry<tile_log<T>()>(a0.g, [&](auto ca) {
+                hipLaunchKernelGGL((k_pass2<T, LOGE, PM_FWD, LD, IO_SAME, false, ca(), 0>),
+                                   dim3((unsigned)(nb0 + nb1)), dim3(threads), lds, s, a0, a1, nb0);
+                return LDK_OK;
+            }, st)) {
             LDK_LAUNCH_CHECK();
-            return LDK_OK;
+            return st;
         }
     }
     hipLaunchKernelGGL((k_pass2<T, LOGE, PM_FWD, LD, IO_SAME, false>), dim3((unsigned)(nb0 + nb1)),

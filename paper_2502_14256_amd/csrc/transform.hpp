@@ -17,11 +17,13 @@
 // caller folds n^-1/2 or 1/n into one multiply.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace ldk {
 
-// PM_POWER, PM_ADJ and PM_QFORM exist only in the real-input lattice top pass.
+// PM_POWER and the modes after it exist only in the real-input lattice top pass.
 enum PassMode {
     PM_FWD = 0,
     PM_INV = 1,
@@ -29,7 +31,9 @@ enum PassMode {
     PM_MATVEC = 3,
     PM_POWER = 4,
     PM_ADJ = 5,
-    PM_QFORM = 6
+    PM_QFORM = 6,
+    PM_UPDATE = 7,
+    PM_UPDATE_EIG = 8
 };
 
 struct PassGeom {
@@ -102,7 +106,7 @@ struct PassArgs {
     // pairs [rows / nrhs][N] (launch_filter_coef); NULL forms them from lam
     // in the pass itself.
     const void *coef;
-    // PIO_COMBINE only: the old half's transform [rows][2^m]; the store
+    // PIO_COMBINE and PM_UPDATE(_EIG): the old half's transform [rows][2^m]; the store
     // writes (old + w) / sqrt 2 at k and (old - w) / sqrt 2 at 2^m + k of
     // dst rows of 2^(m+1), w the pass output (times W_{2^(m+1)}^k, lattice).
     // With combine_real: FP64 rows old +- Re w, unnormalised (eigenvalues).
@@ -125,6 +129,39 @@ enum PassIo {
 // src_f32: src holds floats widened to the FP64 working type (PM_FWD only).
 int launch_pass(int kind, int dtype, int mode, int ld, int st, const PassArgs &a, hipStream_t s,
                 bool src_f32 = false);
+
+// Calls f(integral_constant<A>) for a top (or column) pass over g.a = A = 4 ..
+// 8 axis bits in full tiles of 2^TILE elements, radix 8: the geometries the
+// default plans give every transform of two passes.  Kernels instantiated on
+// A fold their index maps, group loops and twiddle choices to constants
+// (about half the instructions of the run-time geometry).  False: not one of
+// them, f was not called.
+template <int TILE, typename F>
+inline bool with_top_geometry(const PassGeom &g, F &&f, int &st)
+{
+    if (g.logE != 3 || g.a + g.logW != TILE) return false;
+    switch (g.a) {
+    case 4: st = f(std::integral_constant<int, 4>()); return true;
+    case 5: st = f(std::integral_constant<int, 5>()); return true;
+    case 6: st = f(std::integral_constant<int, 6>()); return true;
+    case 7: st = f(std::integral_constant<int, 7>()); return true;
+    case 8: st = f(std::integral_constant<int, 8>()); return true;
+    default: return false;
+    }
+}
+// The same for a row pass (contiguous tiles) over g.a = TILE - 3 .. TILE bits.
+template <int TILE, typename F>
+inline bool with_row_geometry(const PassGeom &g, F &&f, int &st)
+{
+    if (g.logE != 3 || g.logW != 0 || g.b0 != 0) return false;
+    switch (TILE - g.a) {
+    case 0: st = f(std::integral_constant<int, TILE>()); return true;
+    case 1: st = f(std::integral_constant<int, TILE - 1>()); return true;
+    case 2: st = f(std::integral_constant<int, TILE - 2>()); return true;
+    case 3: st = f(std::integral_constant<int, TILE - 3>()); return true;
+    default: return false;
+    }
+}
 
 // Real-input lattice top pass (see realfft.hip): forward transform of the
 // packed half-length row's top bit group, untangling of the real spectrum,
