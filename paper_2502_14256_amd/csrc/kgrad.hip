@@ -365,12 +365,13 @@ __global__ __launch_bounds__(KC_THREADS) void k_kernel_grad(KgradArgs g)
 // Points per thread and dimensions per block given the forward column.  The
 // dimensions are independent then, so a grid short of three blocks per
 // compute unit is split over them; a large one takes twice the points per
-// thread (the dimension's setup and reduction serve more factors; FP64 nets
-// lose their occupancy to it and do not).  Measured (us, D = 16 / 8 / 4 / 2
+// thread in FP32 (the dimension's setup and reduction serve more factors; in
+// FP64, where it would change the order of the sums, nets lose their
+// occupancy to it and lattices gain 5 %).  Measured (us, D = 16 / 8 / 4 / 2
 // dimensions per block): FP64 net 2^16 points x d = 16: 21.0 / 13.8 / 10.2 /
 // 8.8; 2^18 x 32: 22.0 / 18.2 / 17.0 / 20.5; 2^20 x 32: 42.4 / 43.8 / 48.3 /
-// 63.6; 16 instead of 8 points per thread at 2^22 x 64: lattice FP64 194 ->
-// 185, FP32 133 -> 127, net FP32 132 -> 130, net FP64 268 -> 272.
+// 63.6; 16 instead of 8 points per thread at 2^22 x 64: lattice FP32 133 ->
+// 127, net FP32 132 -> 130, net FP64 268 -> 272.
 void grad_split(const PointsetArgs &p, int64_t cnt, int dtype, int *it, int *dims)
 {
     auto blocks = [&](int n, int dd) {
@@ -378,35 +379,49 @@ void grad_split(const PointsetArgs &p, int64_t cnt, int dtype, int *it, int *dim
     };
     *it = KC_ITERS;
     *dims = NT_DIMS;
-    if ((p.kind == LDK_LATTICE || dtype == LDK_F32) && blocks(2 * KC_ITERS, NT_DIMS) >= 1024)
+    if (dtype == LDK_F32 && blocks(2 * KC_ITERS, NT_DIMS) >= 1024)
         *it = 2 * KC_ITERS;
     while (*dims > 2 && blocks(*it, *dims) < 768) *dims /= 2;
 }
 
-// grad[r][j] = sum over tiles of the partials, in a fixed order: 64 sums per
-// block (one per lane), each wave taking every KG_FINAL_WAVES-th tile, then
-// the waves' sums in turn.  One thread per sum walking every tile was a chain
-// of memory latencies (60 us of the 75 us of a gradient of 512 tiles).
-constexpr int KG_FINAL_WAVES = 16;
-__global__ __launch_bounds__(64 * KG_FINAL_WAVES) void k_grad_final(const double *__restrict__ part,
-                                                                    int64_t tiles, int d,
-                                                                    double *__restrict__ grad)
+// grad[r][j] = sum over tiles of the partials in a fixed order: four
+// interleaved sums, tile by tile, then (s0 + s1) + (s2 + s3).  A block takes 64
+// components: its threads bring KG_FINAL_TILES tiles' partials into LDS
+// together, then four threads per component add them in turn.  (One thread
+// per component walking the tiles in memory was a chain of latencies: 60 us
+// of the 75 us of a gradient of 512 tiles.)
+constexpr int KG_FINAL_TILES = 64;
+constexpr int KG_FINAL_THREADS = 1024;
+__global__ __launch_bounds__(KG_FINAL_THREADS) void k_grad_final(const double *__restrict__ part, int64_t tiles,
+                                                                 int d, double *__restrict__ grad)
 {
-    __shared__ double red[KG_FINAL_WAVES][64];
-    const int r = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ double v[KG_FINAL_TILES][65];
+    const int r = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int j = blockIdx.x * 64 + lane;
-    double s = 0.0;
-    if (j <= d) {
-        const double *p = part + (size_t)r * tiles * (d + 1) + j;
-#pragma unroll 4
-        for (int64_t q = wave; q < tiles; q += KG_FINAL_WAVES) s += p[(size_t)q * (d + 1)];
+    const double *p = part + (size_t)r * tiles * (d + 1) + (j <= d ? j : d);
+    double s = 0.0;  // threads 0 .. 255: sum `wave` of component j
+    for (int64_t q0 = 0; q0 < tiles; q0 += KG_FINAL_TILES) {
+        const int n = (int)(tiles - q0 < KG_FINAL_TILES ? tiles - q0 : KG_FINAL_TILES);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KG_FINAL_TILES / (KG_FINAL_THREADS / 64); ++k) {
+            const int q = wave + k * (KG_FINAL_THREADS / 64);
+            if (q < n) v[q][lane] = p[(size_t)(q0 + q) * (d + 1)];
+        }
+        __syncthreads();
+        if (wave < 4) {
+            // the tiles past the last multiple of four belong to sum 0
+            const int whole = q0 + n == tiles ? n & ~3 : n;
+            for (int q = wave; q < whole; q += 4) s += v[q][lane];
+            if (wave == 0)
+                for (int q = whole; q < n; ++q) s += v[q][lane];
+        }
     }
-    red[wave][lane] = s;
     __syncthreads();
-    if (wave == 0 && j <= d) {
-        for (int w = 1; w < KG_FINAL_WAVES; ++w) s += red[w][lane];
-        grad[(size_t)r * (d + 1) + j] = s;
-    }
+    if (wave < 4) v[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && j <= d)
+        grad[(size_t)r * (d + 1) + j] = (v[0][lane] + v[1][lane]) + (v[2][lane] + v[3][lane]);
 }
 
 template <typename R, int ALPHA, int SRC>
@@ -418,7 +433,7 @@ void launch_grad_k1(const KgradArgs &g, int it, dim3 grid, hipStream_t s)
         return;
     }
     grid.z = (unsigned)((g.k.ps.d + g.dims_per_block - 1) / g.dims_per_block);
-    if constexpr (SRC < 2 || (SRC == 2 && sizeof(R) == 4)) {
+    if constexpr (SRC < 3 && sizeof(R) == 4) {
         if (it == 2 * N) {
             hipLaunchKernelGGL((k_kernel_grad<R, ALPHA, SRC, true, 2 * N>), grid, dim3(KC_THREADS), 0, s, g);
             return;
@@ -498,7 +513,7 @@ extern "C" int ldk_kernel_grad(const ldk_kernel *k, const ldk_pointset *ps, cons
     hipStream_t s = as_stream(stream);
     if (n_max == n_min) {
         // empty window: every sum is zero
-        hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 63) / 64, p.R), dim3(64 * KG_FINAL_WAVES), 0, s,
+        hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 63) / 64, p.R), dim3(KG_FINAL_THREADS), 0, s,
                            (const double *)nullptr, (int64_t)0, p.d, grad);
         LDK_LAUNCH_CHECK();
         return LDK_OK;
@@ -519,7 +534,7 @@ extern "C" int ldk_kernel_grad(const ldk_kernel *k, const ldk_pointset *ps, cons
     if (dtype == LDK_F64) launch_grad<double>(src, uniform, g, it, grid, s);
     else launch_grad<float>(src, uniform, g, it, grid, s);
     LDK_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 63) / 64, p.R), dim3(64 * KG_FINAL_WAVES), 0, s,
+    hipLaunchKernelGGL(k_grad_final, dim3((p.d + 1 + 63) / 64, p.R), dim3(KG_FINAL_THREADS), 0, s,
                        (const double *)g.part, g.tiles, p.d, grad);
     LDK_LAUNCH_CHECK();
     return LDK_OK;

@@ -658,9 +658,12 @@ int launch_rt(const PassArgs &a, double *lam_out, hipStream_t s, double *ld_part
     if (a.g.b0 > 0 && a.g.logW < 1) return LDK_ENOTSUP;  // mirror runs need W >= 2
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(T);
     constexpr int TILE = std::is_same<T, cplx<double>>::value ? 11 : 12;
-    if constexpr (MODE != PM_MATVEC && LD == IO_SAME && ST == IO_SAME && !SRC_F32 && LOGE == 3) {
+    if constexpr (MODE != PM_MATVEC && MODE != PM_POWER && MODE != PM_ADJ && LD == IO_SAME &&
+                  ST == IO_SAME && !SRC_F32 && LOGE == 3) {
         int st = LDK_OK;
-        const bool fixed = with_top_geometry<TILE>(a.g, [&](auto ca) {
+        // without any_fixed: the n = 2^20 eigenvalues and solves only
+        const bool may = a.any_fixed || ((MODE == PM_SOLVE || MODE == PM_FWD) && a.g.a == (TILE == 11 ? 8 : 7));
+        const bool fixed = may && with_top_geometry<TILE>(a.g, [&](auto ca) {
             constexpr int A = ca();
             if constexpr (CF) {
                 if (a.nrhs % 2 == 0) {

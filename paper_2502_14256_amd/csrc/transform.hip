@@ -202,8 +202,8 @@ __global__ __launch_bounds__(CA >= 0 ? (1 << (CA + CLW - LOGE)) : 512) void k_pa
 
 // The passes of the default two-pass plans get kernels with their geometry
 // fixed at compile time: the lattice row passes (the packed half-length row in
-// contiguous tiles of up to 2^11 elements in FP64, 2^12 in FP32), and the
-// digital-net row passes (up to 2^12) and top passes (4 to 8 axis bits).
+// contiguous tiles of 2^8 to 2^11 elements in FP64, 2^9 to 2^12 in FP32), and the
+// digital-net row passes (2^9 to 2^12) and top passes (4 to 8 axis bits).
 template <typename T>
 constexpr int tile_log()
 {
@@ -304,7 +304,7 @@ int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
     if constexpr (row_specialised<T, LOGE, SRC_F32>() && (MODE == PM_FWD || MODE == PM_INV)) {
         constexpr int LDs = MODE == PM_FWD ? IO_PACKED : IO_SAME;
         constexpr int STs = MODE == PM_FWD ? IO_SAME : IO_PACKED;
-        if (ld == LDs && st == STs)
+        if (ld == LDs && st == STs && (a.any_fixed || a.g.a == TILE))
             fixed = with_row_geometry<TILE>(a.g, [&](auto ca) {
                 hipLaunchKernelGGL((k_pass<T, LOGE, MODE, LDs, STs, SRC_F32, ca(), 0>), grid, block, lds, s, a);
                 return LDK_OK;
