@@ -130,20 +130,27 @@ def _check(rc: int, what: str):
         raise LdkError(f"{what}: {msg} (status {rc}, hip error {lib().ldk_last_hip_error()})")
 
 
+# The calls below run in microseconds, so the path from a call to its launch
+# is kept short: no stream object is built (torch.cuda.current_stream() costs
+# as much as the launch itself), pointers go as plain integers, and checks
+# look at each tensor once.
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle on the current device."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_DTYPE_CODE = {torch.float64: F64, torch.complex128: F64, torch.float32: F32, torch.complex64: F32}
 
 
 def _dtype_code(dt: torch.dtype) -> int:
-    if dt in (torch.float64, torch.complex128):
-        return F64
-    if dt in (torch.float32, torch.complex64):
-        return F32
-    raise LdkError(f"unsupported dtype {dt}")
+    code = _DTYPE_CODE.get(dt)
+    if code is None:
+        raise LdkError(f"unsupported dtype {dt}")
+    return code
 
 
 def _real(dtype_code: int):
@@ -157,7 +164,7 @@ def _cplx(dtype_code: int):
 def _need(t: torch.Tensor, name: str, device=None):
     if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
         raise LdkError(f"{name} must be a contiguous device tensor")
-    if device is not None and t.device != torch.device(device):
+    if device is not None and t.device != device and t.device != torch.device(device):
         raise LdkError(f"{name} is on {t.device}, expected {device}")
 
 
@@ -167,11 +174,20 @@ def _need_out(t: torch.Tensor, name: str, dtype: torch.dtype, shape, device):
     _need(t, name, device)
     if t.dtype != dtype:
         raise LdkError(f"{name} must be {dtype}, got {t.dtype}")
-    want = 1
-    for s_ in shape:
-        want *= int(s_)
-    if t.numel() != want:
-        raise LdkError(f"{name} holds {t.numel()} elements, expected {want} ({tuple(shape)})")
+    if t.shape != shape:
+        want = 1
+        for s_ in shape:
+            want *= int(s_)
+        if t.numel() != want:
+            raise LdkError(f"{name} holds {t.numel()} elements, expected {want} ({tuple(shape)})")
+
+
+def _out(t, name: str, dtype: torch.dtype, shape, device):
+    """`t` checked as an output (_need_out), or a new tensor when None."""
+    if t is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    _need_out(t, name, dtype, shape, device)
+    return t
 
 
 def _need_ws(ws, nbytes: int, device):
@@ -186,13 +202,17 @@ def _need_ws(ws, nbytes: int, device):
     return ws
 
 
+_KINDS = {"lattice": LATTICE, "dnet": DNET_B2, LATTICE: LATTICE, DNET_B2: DNET_B2}
+_ORDERS = {"natural": NATURAL, "linear": LINEAR, "gray": GRAY,
+           NATURAL: NATURAL, LINEAR: LINEAR, GRAY: GRAY}
+
+
 def _kind(kind) -> int:
-    return {"lattice": LATTICE, "dnet": DNET_B2, LATTICE: LATTICE, DNET_B2: DNET_B2}[kind]
+    return _KINDS[kind]
 
 
 def _order(order) -> int:
-    return {"natural": NATURAL, "linear": LINEAR, "gray": GRAY,
-            NATURAL: NATURAL, LINEAR: LINEAR, GRAY: GRAY}[order]
+    return _ORDERS[order]
 
 
 def _workspace(op: int, kind: int, rows: int, m: int, dt: int, device, ws=None):
@@ -240,11 +260,12 @@ class PointSet:
     order: str = "natural"
     per_replication: bool = False
 
-    def _c(self) -> _Pointset:
-        for name in ("gen", "lms", "shift"):
-            t = getattr(self, name)
-            if t is not None:
-                _need(t, name)
+    def _c(self, checked: bool = False) -> _Pointset:
+        if not checked:
+            for name in ("gen", "lms", "shift"):
+                t = getattr(self, name)
+                if t is not None:
+                    _need(t, name)
         return _Pointset(_kind(self.kind), _order(self.order), self.R, self.d, self.m_max,
                          GEN_PER_REPLICATION if self.per_replication else 0,
                          _ptr(self.gen), _ptr(self.lms), _ptr(self.shift))
@@ -268,10 +289,11 @@ class Kernel:
         a = self.alpha.cpu().numpy() if isinstance(self.alpha, torch.Tensor) else self.alpha
         self._alpha_host = np.ascontiguousarray(np.asarray(a, dtype=np.int32).ravel())
 
-    def _c(self) -> _Kernel:
-        _need(self.gamma, "gamma")
-        return _Kernel(_kind(self.kind), int(self._alpha_host.size),
-                       C.c_void_p(self._alpha_host.ctypes.data), _ptr(self.gamma),
+    def _c(self, checked: bool = False) -> _Kernel:
+        if not checked:
+            _need(self.gamma, "gamma")
+        return _Kernel(_KINDS[self.kind], self._alpha_host.size,
+                       self._alpha_host.__array_interface__["data"][0], self.gamma.data_ptr(),
                        float(self.zeta))
 
 
@@ -298,22 +320,20 @@ def _ps_checked(ps: PointSet):
         _need(ps.shift, "shift", dev)
         if ps.shift.numel() < ps.R * ps.d:
             raise LdkError("shift must hold [R][d] words")
-    return ps._c()
+    return ps._c(checked=True)
 
 
 def _k_checked(k: Kernel, d: int, dev):
     _need(k.gamma, "gamma", dev)
     if k.gamma.dtype != torch.float64 or k.gamma.numel() != d or k._alpha_host.size != d:
         raise LdkError("kernel gamma must be float64[d] and alpha hold d orders")
-    return k._c()
+    return k._c(checked=True)
 
 
 def gen_points(ps: PointSet, n_min: int, n_max: int, out: torch.Tensor | None = None):
     dev = _dev_of(ps)
     shape = (ps.R, n_max - n_min, ps.d)
-    if out is None:
-        out = torch.empty(shape, dtype=torch.int64, device=dev)
-    _need_out(out, "out", torch.int64, shape, dev)
+    out = _out(out, "out", torch.int64, shape, dev)
     _check(lib().ldk_gen_points(C.byref(_ps_checked(ps)), n_min, n_max, _ptr(out), _stream()),
            "ldk_gen_points")
     return out
@@ -324,9 +344,7 @@ def kernel_column(k: Kernel, ps: PointSet, n_min: int, n_max: int, pts=None, x0=
     dt = _dtype_code(dtype)
     dev = _dev_of(ps)
     shape = (ps.R, n_max - n_min)
-    if out is None:
-        out = torch.empty(shape, dtype=_real(dt), device=dev)
-    _need_out(out, "out", _real(dt), shape, dev)
+    out = _out(out, "out", _real(dt), shape, dev)
     if pts is not None:
         _need_out(pts, "pts", torch.int64, (ps.R, n_max - n_min, ps.d), dev)
     if x0 is not None:
@@ -349,9 +367,7 @@ def interlace(src: PointSet, alpha: int, shift: torch.Tensor | None = None, orde
     d = src.d // alpha
     dev = _dev_of(src)
     shape = (src.R, d, src.m_max)
-    if out is None:
-        out = torch.empty(shape, dtype=torch.int64, device=dev)
-    _need_out(out, "out", torch.int64, shape, dev)
+    out = _out(out, "out", torch.int64, shape, dev)
     _check(lib().ldk_interlace(C.byref(_ps_checked(src)), alpha, _ptr(out), _stream()),
            "ldk_interlace")
     return PointSet("dnet", src.R, d, src.m_max, out, None, shift, order or src.order,
@@ -364,12 +380,8 @@ def points_column(k: Kernel, ps: PointSet, n_min: int, n_max: int, dtype=torch.f
     regenerated) in one call, bit for bit the same outputs."""
     dt = _dtype_code(dtype)
     dev = _dev_of(ps)
-    if pts is None:
-        pts = torch.empty((ps.R, n_max - n_min, ps.d), dtype=torch.int64, device=dev)
-    if k1 is None:
-        k1 = torch.empty((ps.R, n_max - n_min), dtype=_real(dt), device=dev)
-    _need_out(pts, "pts", torch.int64, (ps.R, n_max - n_min, ps.d), dev)
-    _need_out(k1, "k1", _real(dt), (ps.R, n_max - n_min), dev)
+    pts = _out(pts, "pts", torch.int64, (ps.R, n_max - n_min, ps.d), dev)
+    k1 = _out(k1, "k1", _real(dt), (ps.R, n_max - n_min), dev)
     _check(lib().ldk_points_column(C.byref(_k_checked(k, ps.d, dev)), C.byref(_ps_checked(ps)),
                                    n_min, n_max, _ptr(pts), dt, _ptr(k1), _stream()),
            "ldk_points_column")
@@ -417,8 +429,7 @@ def eig(kind, k1: torch.Tensor, out=None, ws=None):
     R, n = k1.shape
     m = _m_of(n)
     dev = k1.device
-    out = torch.empty((R, n), dtype=torch.float64, device=dev) if out is None else out
-    _need_out(out, "out", torch.float64, (R, n), dev)
+    out = _out(out, "out", torch.float64, (R, n), dev)
     ws = _workspace(OP_EIG, kd, R, m, dt, dev, ws)
     _check(lib().ldk_eig(kd, R, m, dt, _ptr(k1), _ptr(out), _ptr(ws), _stream()), "ldk_eig")
     return out
@@ -434,8 +445,7 @@ def _apply_args(kind, lam, y, out, ws, op):
     R, nrhs, n = y.shape
     m = _m_of(n)
     _need_f64(lam, "lam", (R, n), dev)
-    out = torch.empty_like(y) if out is None else out
-    _need_out(out, "out", y.dtype, y.shape, dev)
+    out = _out(out, "out", y.dtype, y.shape, dev)
     ws = _workspace(op, kd, R * nrhs, m, dt, dev, ws)
     return kd, dt, R, nrhs, m, out, ws
 
@@ -491,8 +501,7 @@ def logdet(lam: torch.Tensor, sigma2: float, out=None, ws=None, checked: bool = 
     R, n = lam.shape
     m = _m_of(n)
     dev = lam.device
-    out = torch.empty(R, dtype=torch.float64, device=dev) if out is None else out
-    _need_out(out, "out", torch.float64, (R,), dev)
+    out = _out(out, "out", torch.float64, (R,), dev)
     ws = _workspace(OP_LOGDET, DNET_B2, R, m, F64, dev, ws)
     fn = lib().ldk_logdet_checked if checked else lib().ldk_logdet
     _check(fn(R, m, _ptr(lam), float(sigma2), _ptr(out), _ptr(ws), _stream()),
@@ -516,10 +525,8 @@ def fit(kind, k1: torch.Tensor, sigma2: float, y: torch.Tensor, lam=None, c=None
         raise LdkError("y must be [R][nrhs][n]")
     nrhs = y.shape[1]
     m = _m_of(n)
-    lam = torch.empty((R, n), dtype=torch.float64, device=dev) if lam is None else lam
-    _need_out(lam, "lam", torch.float64, (R, n), dev)
-    c = torch.empty_like(y) if c is None else c
-    _need_out(c, "c", y.dtype, y.shape, dev)
+    lam = _out(lam, "lam", torch.float64, (R, n), dev)
+    c = _out(c, "c", y.dtype, y.shape, dev)
     ld = None
     if logdet is True:
         ld = torch.empty(R, dtype=torch.float64, device=dev)
@@ -542,9 +549,7 @@ def update_double(kind, yt_old: torch.Tensor, y_new: torch.Tensor, out=None):
     m = _m_of(n)
     want = _cplx(dt) if kd == LATTICE else _real(dt)
     _need_out(yt_old, "yt_old", want, (B, n), dev)
-    if out is None:
-        out = torch.empty((B, 2 * n), dtype=want, device=dev)
-    _need_out(out, "out", want, (B, 2 * n), dev)
+    out = _out(out, "out", want, (B, 2 * n), dev)
     ws = _workspace(OP_UPDATE_DOUBLE, kd, B, m, dt, dev)
     _check(lib().ldk_update_double(kd, B, m, dt, _ptr(yt_old), _ptr(y_new), _ptr(out), _ptr(ws),
                                    _stream()), "ldk_update_double")
@@ -561,9 +566,7 @@ def eig_update_double(kind, lam_old: torch.Tensor, k1_new: torch.Tensor, out=Non
     if tuple(k1_new.shape) != (R, n):
         raise LdkError("k1_new must be [R][n] like lam_old")
     m = _m_of(n)
-    if out is None:
-        out = torch.empty((R, 2 * n), dtype=torch.float64, device=dev)
-    _need_out(out, "out", torch.float64, (R, 2 * n), dev)
+    out = _out(out, "out", torch.float64, (R, 2 * n), dev)
     ws = _workspace(OP_EIG_UPDATE_DOUBLE, kd, R, m, dt, dev)
     _check(lib().ldk_eig_update_double(kd, R, m, dt, _ptr(lam_old), _ptr(k1_new), _ptr(out),
                                        _ptr(ws), _stream()), "ldk_eig_update_double")
@@ -585,8 +588,7 @@ def mll(kind, lam: torch.Tensor, sigma2: float, y: torch.Tensor, out_g=None, ws=
     m = _m_of(n)
     L = torch.empty(R, dtype=torch.float64, device=dev)
     ds = torch.empty(R, dtype=torch.float64, device=dev)
-    g = torch.empty((R, n), dtype=torch.float64, device=dev) if out_g is None else out_g
-    _need_out(g, "g", torch.float64, (R, n), dev)
+    g = _out(out_g, "g", torch.float64, (R, n), dev)
     ws = _workspace(OP_MLL, kd, R, m, dt, dev, ws)
     _check(lib().ldk_mll(kd, R, m, dt, _ptr(lam), float(sigma2), _ptr(y), _ptr(L), _ptr(g),
                          _ptr(ds), _ptr(ws), _stream()), "ldk_mll")
@@ -603,8 +605,7 @@ def wce(kind, lam: torch.Tensor, w: torch.Tensor, zeta: float, out=None, ws=None
     R, nw, n = w.shape
     _need_f64(lam, "lam", (R, n), dev)
     m = _m_of(n)
-    out = torch.empty((R, nw), dtype=torch.float64, device=dev) if out is None else out
-    _need_out(out, "out", torch.float64, (R, nw), dev)
+    out = _out(out, "out", torch.float64, (R, nw), dev)
     ws = _workspace(OP_WCE, kd, R * nw, m, dt, dev, ws)
     _check(lib().ldk_wce(kd, R, nw, m, dt, _ptr(lam), float(zeta), _ptr(w), _ptr(out), _ptr(ws),
                          _stream()), "ldk_wce")
@@ -645,9 +646,7 @@ def bayes_cubature(kind, lam: torch.Tensor, sigma2: float, zeta: float, y: torch
         raise LdkError("level must lie in (0, 1)")
     m = _m_of(n)
     z = normal_quantile(0.5 + 0.5 * level)
-    out = torch.empty((R, len(BC_FIELDS)), dtype=torch.float64, device=dev) \
-        if out is None else out
-    _need_out(out, "out", torch.float64, (R, len(BC_FIELDS)), dev)
+    out = _out(out, "out", torch.float64, (R, len(BC_FIELDS)), dev)
     ws = _workspace(OP_BAYES_CUBATURE, kd, R, m, dt, dev, ws)
     _check(lib().ldk_bayes_cubature(kd, R, m, dt, _ptr(lam), float(sigma2), float(zeta), _ptr(y),
                                     float(z), _ptr(out), _ptr(ws), _stream()),
@@ -667,11 +666,8 @@ def rqmc(ps: PointSet, n: int, integrand, coef: torch.Tensor, u: float = 0.0, ta
     if not 0.0 < tau < 1.0:
         raise LdkError("tau must lie in (0, 1)")
     t = student_t_quantile(1.0 - tau / 2.0, ps.R - 1) if ps.R > 1 else 0.0
-    mu_r = torch.empty(ps.R, dtype=torch.float64, device=dev) if mu_r is None else mu_r
-    stats = torch.empty(len(RQMC_FIELDS), dtype=torch.float64, device=dev) if stats is None \
-        else stats
-    _need_out(mu_r, "mu_r", torch.float64, (ps.R,), dev)
-    _need_out(stats, "stats", torch.float64, (len(RQMC_FIELDS),), dev)
+    mu_r = _out(mu_r, "mu_r", torch.float64, (ps.R,), dev)
+    stats = _out(stats, "stats", torch.float64, (len(RQMC_FIELDS),), dev)
     cps = _ps_checked(ps)
     ws = _need_ws(ws, lib().ldk_rqmc_workspace_bytes(C.byref(cps), int(n)), dev)
     _check(lib().ldk_rqmc(C.byref(cps), int(n), f, _ptr(coef), float(u), t, _ptr(mu_r),
@@ -747,11 +743,8 @@ def rqmc_points(x: torch.Tensor, integrand, coef: torch.Tensor, u: float = 0.0, 
     if not 0.0 < tau < 1.0:
         raise LdkError("tau must lie in (0, 1)")
     t = student_t_quantile(1.0 - tau / 2.0, R - 1) if R > 1 else 0.0
-    mu_r = torch.empty(R, dtype=torch.float64, device=dev) if mu_r is None else mu_r
-    stats = torch.empty(len(RQMC_FIELDS), dtype=torch.float64, device=dev) if stats is None \
-        else stats
-    _need_out(mu_r, "mu_r", torch.float64, (R,), dev)
-    _need_out(stats, "stats", torch.float64, (len(RQMC_FIELDS),), dev)
+    mu_r = _out(mu_r, "mu_r", torch.float64, (R,), dev)
+    stats = _out(stats, "stats", torch.float64, (len(RQMC_FIELDS),), dev)
     ws = _need_ws(ws, lib().ldk_rqmc_points_workspace_bytes(R, n), dev)
     _check(lib().ldk_rqmc_points(R, n, d, _ptr(x), f, _ptr(coef), float(u), t, _ptr(mu_r),
                                  _ptr(stats), _ptr(ws), _stream()), "ldk_rqmc_points")
@@ -765,8 +758,7 @@ def mll_adjoint(kind, g: torch.Tensor, out=None, ws=None):
     R, n = g.shape
     m = _m_of(n)
     dev = g.device
-    out = torch.empty_like(g) if out is None else out
-    _need_out(out, "out", torch.float64, (R, n), dev)
+    out = _out(out, "out", torch.float64, (R, n), dev)
     ws = _workspace(OP_MLL_ADJOINT, kd, R, m, F64, dev, ws)
     _check(lib().ldk_mll_adjoint(kd, R, m, _ptr(g), _ptr(out), _ptr(ws), _stream()),
            "ldk_mll_adjoint")
@@ -781,9 +773,7 @@ def kernel_grad(k: Kernel, ps: PointSet, n_min: int, n_max: int, a: torch.Tensor
     dt = _dtype_code(dtype)
     dev = _dev_of(ps)
     _need_f64(a, "a", (ps.R, n_max - n_min), dev)
-    if out is None:
-        out = torch.empty((ps.R, ps.d + 1), dtype=torch.float64, device=dev)
-    _need_out(out, "out", torch.float64, (ps.R, ps.d + 1), dev)
+    out = _out(out, "out", torch.float64, (ps.R, ps.d + 1), dev)
     if pts is not None:
         _need_out(pts, "pts", torch.int64, (ps.R, n_max - n_min, ps.d), dev)
     if x0 is not None:

@@ -30,19 +30,21 @@ from . import (Kernel, LdkError, PointSet, _kind, eig, kernel_column, kernel_gra
                mll_adjoint)
 
 
-def _kernel(kind: str, alpha, log_gamma: torch.Tensor, log_zeta: torch.Tensor) -> Kernel:
-    gamma = torch.exp(log_gamma.detach()).to(torch.float64).contiguous()
-    return Kernel(kind, alpha, gamma, float(torch.exp(log_zeta.detach()).item()))
+def _parameters(log_gamma, log_zeta, log_sigma2):
+    """(gamma [d] on the device, zeta, sigma2): the two numbers the library
+    takes from the host come over in one copy, the call's one wait for the
+    device."""
+    theta = torch.exp(torch.cat([log_gamma.detach().reshape(-1), log_zeta.detach().reshape(1),
+                                 log_sigma2.detach().reshape(1)]))
+    zeta, sigma2 = theta[-2:].tolist()
+    return theta[:-2].contiguous(), zeta, sigma2
 
 
-def _forward_parts(ps: PointSet, kind: str, alpha, log_gamma, log_zeta, log_sigma2, y, dtype):
-    n = y.shape[-1]
-    k = _kernel(kind, alpha, log_gamma, log_zeta)
-    k1 = kernel_column(k, ps, 0, n, dtype=dtype)
-    lam = eig(kind, k1)
-    s2 = float(torch.exp(log_sigma2.detach()).item())
-    L, g, ds = mll(kind, lam, s2, y.to(dtype).contiguous())
-    return k, k1, L, g, ds
+def _forward_parts(k: Kernel, ps: PointSet, sigma2: float, y, dtype):
+    k1 = kernel_column(k, ps, 0, y.shape[-1], dtype=dtype)
+    lam = eig(k.kind, k1)
+    L, g, ds = mll(k.kind, lam, sigma2, y.to(dtype).contiguous())
+    return k1, L, g, ds
 
 
 class MarginalLogLikelihood(torch.autograd.Function):
@@ -53,10 +55,13 @@ class MarginalLogLikelihood(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, log_gamma, log_zeta, log_sigma2, ps, kind, alpha, y, dtype, recompute):
-        k, k1, L, g, ds = _forward_parts(ps, kind, alpha, log_gamma, log_zeta, log_sigma2, y,
-                                         dtype)
+        gamma, zeta, sigma2 = _parameters(log_gamma, log_zeta, log_sigma2)
+        k1, L, g, ds = _forward_parts(Kernel(kind, alpha, gamma, zeta), ps, sigma2, y, dtype)
         ctx.ps, ctx.kind, ctx.alpha, ctx.dtype, ctx.recompute = ps, kind, alpha, dtype, recompute
         ctx.n = y.shape[-1]
+        # the two host numbers of this forward pass: backward does not wait
+        # for the device again
+        ctx.zeta, ctx.sigma2 = zeta, sigma2
         if recompute:
             ctx.save_for_backward(log_gamma.detach(), log_zeta.detach(), log_sigma2.detach(), y)
         else:
@@ -68,12 +73,12 @@ class MarginalLogLikelihood(torch.autograd.Function):
     def backward(ctx, grad_L):
         saved = ctx.saved_tensors
         log_gamma, log_zeta, log_sigma2, y = saved[:4]
+        gamma = torch.exp(log_gamma.reshape(-1)).to(torch.float64).contiguous()
+        k = Kernel(ctx.kind, ctx.alpha, gamma, ctx.zeta)
         if ctx.recompute:
-            k, k1, _, g, ds = _forward_parts(ctx.ps, ctx.kind, ctx.alpha, log_gamma, log_zeta,
-                                             log_sigma2, y, ctx.dtype)
+            k1, _, g, ds = _forward_parts(k, ctx.ps, ctx.sigma2, y, ctx.dtype)
         else:
             k1, g, ds = saved[4:]
-            k = _kernel(ctx.kind, ctx.alpha, log_gamma, log_zeta)
         a = mll_adjoint(ctx.kind, g)
         kg = kernel_grad(k, ctx.ps, 0, ctx.n, a, dtype=ctx.dtype, k1=k1)  # [R][d + 1]
         w = grad_L.to(torch.float64).reshape(-1, 1)
