@@ -275,7 +275,7 @@ bool real_path(int kind, int m) { return kind == LDK_LATTICE && m >= 2; }
 // With ld_part, the top pass also leaves each row's log-det partial sums
 // there (*ld_count per row, at ld_part + row * *ld_count), sigma2 added.
 int real_eig(int m, int64_t rows, const void *k1, bool k1_f32, double *lam, void *ws, hipStream_t s,
-             double *ld_part = nullptr, double sigma2 = 0.0, int *ld_count = nullptr, int any_fixed = 0)
+             double *ld_part = nullptr, double sigma2 = 0.0, int *ld_count = nullptr)
 {
     const int mp = m - 1;
     const int64_t N = (int64_t)1 << mp;
@@ -287,7 +287,6 @@ int real_eig(int m, int64_t rows, const void *k1, bool k1_f32, double *lam, void
     a.half = N;
     a.scale = 1.0;
     a.sigma2 = sigma2;
-    a.any_fixed = any_fixed;
     const PassGeom &top = pl.pass[pl.P - 1];
     if (ld_count) *ld_count = 1 << (top.b0 - top.logW);
     if (pl.P == 1) {
@@ -333,7 +332,6 @@ int real_apply(int dtype, int mode, int m, int64_t rows, int nrhs, const double 
     a.half = N;
     a.lam = lam;
     a.sigma2 = sigma2;
-    a.any_fixed = 1;
     if (pl.P == 1) {
         a.src = y;
         a.dst = c;
@@ -411,7 +409,6 @@ int real_update(int dtype, int mode, int m, PassArgs a, const void *y, bool y_f3
     a.m = mp;
     a.nrhs = 1;
     a.half = N;
-    a.any_fixed = 1;
     for (int p = 0; p < pl.P - 1; ++p) {
         a.src = p == 0 ? y : work;
         a.src_row = p == 0 ? 2 * N : work_row;
@@ -740,7 +737,7 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
         void *rest = static_cast<unsigned char *>(ws) +
                      align256((size_t)R * ((size_t)1 << (top.b0 - top.logW)) * sizeof(double));
         int cb = 0;
-        st = real_eig(m, R, k1, dtype == LDK_F32, lam, rest, s, partial, sigma2, &cb, 1);
+        st = real_eig(m, R, k1, dtype == LDK_F32, lam, rest, s, partial, sigma2, &cb);
         if (st) return st;
         bool done = false;
         st = real_apply(dtype, PM_SOLVE, m, (int64_t)R * nrhs, nrhs, lam, sigma2, y, c, rest, s, partial, cb,
@@ -785,7 +782,6 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
     aK.m = aY.m = mp;
     aK.half = aY.half = N;
     aK.sigma2 = aY.sigma2 = sigma2;
-    aK.any_fixed = aY.any_fixed = 1;
     aK.scale = 1.0;
     aY.lam = lam;
     // forward passes below the top one: column and right-hand sides in one launch

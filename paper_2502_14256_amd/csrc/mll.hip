@@ -462,7 +462,6 @@ int cubature(int kind, int R, int nw, int m, int dtype, const double *lam, doubl
         a.m = mp;
         a.half = N;
         a.scale = 1.0;
-        a.any_fixed = 1;
         for (int p = 0; p < pl.P - 1; ++p) {
             a.src = p == 0 ? w : tmp;
             a.src_row = p == 0 ? n : N;

@@ -608,14 +608,11 @@ int launch_ft(const PassArgs &aK, const PassArgs &aY, double *lam_out, double *l
     if (aK.g.b0 > 0 && aK.g.logW < 1) return LDK_ENOTSUP;
     const size_t lds = 2 * (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(cplx<double>);
     if constexpr (LOGE == 3 && LD == IO_SAME && ST == IO_SAME) {
-        int st = LDK_OK;
-        const bool fixed = with_top_geometry<11>(aK.g, [&](auto ca) {
-            constexpr int A = ca();
-            hipLaunchKernelGGL((k_fit_top<LOGE, LD, ST, A, 11 - A>), dim3((unsigned)blocks), dim3(2 * Tn),
+        // the fit's top pass at n = 2^19 .. 2^20 (8 axis bits, 8-column tiles);
+        // at other sizes the run-time geometry, whose bits ldk_eig returns
+        if (aK.g.a == 8 && aK.g.logW == 3) {
+            hipLaunchKernelGGL((k_fit_top<LOGE, LD, ST, 8, 3>), dim3((unsigned)blocks), dim3(2 * Tn),
                                lds, s, aK, aY, lam_out, ld_part);
-            return LDK_OK;
-        }, st);
-        if (fixed) {
             LDK_LAUNCH_CHECK();
             return LDK_OK;
         }
@@ -661,10 +658,16 @@ int launch_rt(const PassArgs &a, double *lam_out, hipStream_t s, double *ld_part
     if constexpr (MODE != PM_MATVEC && MODE != PM_POWER && MODE != PM_ADJ && LD == IO_SAME &&
                   ST == IO_SAME && !SRC_F32 && LOGE == 3) {
         int st = LDK_OK;
-        // without any_fixed: the n = 2^20 eigenvalues and solves only
-        const bool may = a.any_fixed || ((MODE == PM_SOLVE || MODE == PM_FWD) && a.g.a == (TILE == 11 ? 8 : 7));
-        const bool fixed = may && with_top_geometry<TILE>(a.g, [&](auto ca) {
-            constexpr int A = ca();
+        // Eigenvalues and solves take the fixed geometry of their plans at
+        // n = 2^20 only: the compiler contracts the twiddle products of a
+        // fixed geometry differently from the run-time one's, the
+        // likelihood's gradient (a sum that cancels by 1e4 to 1e9 on smooth
+        // low-dimensional kernels) is built on their bits, and the fused fit
+        // returns theirs.
+        constexpr bool ANY = MODE != PM_FWD && MODE != PM_SOLVE;
+        constexpr int ONE = TILE == 11 ? 8 : 7;
+        const bool fixed = (ANY || a.g.a == ONE) && with_top_geometry<TILE>(a.g, [&](auto ca) {
+            constexpr int A = ANY ? ca() : ONE;
             if constexpr (CF) {
                 if (a.nrhs % 2 == 0) {
                     hipLaunchKernelGGL((k_real_top<T, LOGE, MODE, LD, ST, SRC_F32, CF, A, TILE - A, 2>),

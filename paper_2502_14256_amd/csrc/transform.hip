@@ -304,11 +304,11 @@ int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
     if constexpr (row_specialised<T, LOGE, SRC_F32>() && (MODE == PM_FWD || MODE == PM_INV)) {
         constexpr int LDs = MODE == PM_FWD ? IO_PACKED : IO_SAME;
         constexpr int STs = MODE == PM_FWD ? IO_SAME : IO_PACKED;
-        if (ld == LDs && st == STs && (a.any_fixed || a.g.a == TILE))
-            fixed = with_row_geometry<TILE>(a.g, [&](auto ca) {
-                hipLaunchKernelGGL((k_pass<T, LOGE, MODE, LDs, STs, SRC_F32, ca(), 0>), grid, block, lds, s, a);
-                return LDK_OK;
-            }, st_fixed);
+        // full tiles only: the eigenvalues' bits (see launch_rt)
+        if (ld == LDs && st == STs && a.g.a == TILE && a.g.logW == 0 && a.g.b0 == 0) {
+            hipLaunchKernelGGL((k_pass<T, LOGE, MODE, LDs, STs, SRC_F32, TILE, 0>), grid, block, lds, s, a);
+            fixed = true;
+        }
     }
     if (fixed) {
         if (st_fixed) return st_fixed;
@@ -590,14 +590,12 @@ int launch_fwd2(const PassArgs &a0, const PassArgs &a1, hipStream_t s)
     if ((a0.g.a + LOGE - 1) / LOGE > MAX_GROUPS) return LDK_ENOTSUP;
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(T);
     if constexpr (row_specialised<T, LOGE, false>() && LD == IO_PACKED) {
-        int st = LDK_OK;
-        if (with_row_geometry<tile_log<T>()>(a0.g, [&](auto ca) {
-                hipLaunchKernelGGL((k_pass2<T, LOGE, PM_FWD, LD, IO_SAME, false, ca(), 0>),
-                                   dim3((unsigned)(nb0 + nb1)), dim3(threads), lds, s, a0, a1, nb0);
-                return LDK_OK;
-            }, st)) {
+        constexpr int TILE = tile_log<T>();
+        if (a0.g.a == TILE && a0.g.logW == 0 && a0.g.b0 == 0) {
+            hipLaunchKernelGGL((k_pass2<T, LOGE, PM_FWD, LD, IO_SAME, false, TILE, 0>),
+                               dim3((unsigned)(nb0 + nb1)), dim3(threads), lds, s, a0, a1, nb0);
             LDK_LAUNCH_CHECK();
-            return st;
+            return LDK_OK;
         }
     }
     hipLaunchKernelGGL((k_pass2<T, LOGE, PM_FWD, LD, IO_SAME, false>), dim3((unsigned)(nb0 + nb1)),

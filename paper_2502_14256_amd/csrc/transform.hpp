@@ -112,13 +112,6 @@ struct PassArgs {
     // With combine_real: FP64 rows old +- Re w, unnormalised (eigenvalues).
     const void *old;
     int combine_real;
-    // Lattice passes: the call may run any of the kernels with their geometry
-    // fixed at compile time.  The compiler contracts the twiddle products of
-    // those differently from the run-time geometry's, and the likelihood's
-    // gradient (a sum that cancels by 1e4 to 1e9 on smooth low-dimensional
-    // kernels) shows a changed rounding, so the eigenvalue, likelihood and
-    // adjoint calls (0) keep to the kernels at n = 2^20.
-    int any_fixed;
 };
 
 // Global IO of a pass (lattice only; nets are always real):
