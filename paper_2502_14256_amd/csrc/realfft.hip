@@ -658,13 +658,15 @@ int launch_rt(const PassArgs &a, double *lam_out, hipStream_t s, double *ld_part
     if constexpr (MODE != PM_MATVEC && MODE != PM_POWER && MODE != PM_ADJ && LD == IO_SAME &&
                   ST == IO_SAME && !SRC_F32 && LOGE == 3) {
         int st = LDK_OK;
-        // Eigenvalues and solves take the fixed geometry of their plans at
-        // n = 2^20 only: the compiler contracts the twiddle products of a
-        // fixed geometry differently from the run-time one's, the
-        // likelihood's gradient (a sum that cancels by 1e4 to 1e9 on smooth
-        // low-dimensional kernels) is built on their bits, and the fused fit
-        // returns theirs.
-        constexpr bool ANY = MODE != PM_FWD && MODE != PM_SOLVE;
+        // Eigenvalues and solves of one right-hand side take the fixed
+        // geometry of their plans at n = 2^20 only: the compiler contracts the
+        // twiddle products of a fixed geometry differently from the run-time
+        // one's, the likelihood's gradient (a sum that cancels by 1e4 to 1e9
+        // on smooth low-dimensional kernels) is built on their bits, and
+        // k_fit_top returns theirs.  Solves by precomputed coefficients (two
+        // or more right-hand sides; the fit runs this kernel then) take it at
+        // every size: n = 2^18, 4 x 8 right-hand sides, 44.4 -> 33.4 us.
+        constexpr bool ANY = (MODE != PM_FWD && MODE != PM_SOLVE) || (MODE == PM_SOLVE && CF);
         constexpr int ONE = TILE == 11 ? 8 : 7;
         const bool fixed = (ANY || a.g.a == ONE) && with_top_geometry<TILE>(a.g, [&](auto ca) {
             constexpr int A = ANY ? ca() : ONE;

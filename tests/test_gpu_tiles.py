@@ -98,3 +98,49 @@ def test_nus_block_shapes(orc, R, d, m, lo, hi):
     for a, b in ((lo, min(lo + 70, hi)), (mid, min(mid + 70, hi)), (max(lo, hi - 70), hi)):
         ref = orc.unit_points(orc.nus_points(t["gen"], seed, m, a, b))
         assert np.array_equal(x[:, a - lo:b - lo], ref), (a, b)
+
+
+@pytest.mark.parametrize("m", [0, 1, 5, 9, 12])
+@pytest.mark.parametrize("R,nrhs", [(1, 2), (2, 8), (3, 100), (129, 2), (300, 3)])
+def test_one_launch_net_fit_split_over_right_hand_sides(m, R, nrhs):
+    """The right-hand sides of a one-pass net shared out over workgroups: the
+    eigenvalues and solutions of the separate calls bit for bit, also with the
+    eigenvalues written over the column (one workgroup a row then)."""
+    n, s2 = 2**m, 1e-2
+    g = torch.Generator("cuda").manual_seed(m)
+    k1 = torch.rand((R, n), dtype=torch.float64, device="cuda", generator=g)
+    k1[:, 0] += n
+    y = torch.randn((R, nrhs, n), dtype=torch.float64, device="cuda", generator=g)
+    lam_ref = ldk.eig("dnet", k1)
+    c_ref, ld_ref = ldk.solve("dnet", lam_ref, s2, y), ldk.logdet(lam_ref, s2)
+    over = k1.clone()
+    for col, out in ((k1, None), (over, over)):
+        lam, c, ld = ldk.fit("dnet", col, s2, y, lam=out)
+        assert torch.equal(lam, lam_ref) and torch.equal(c, c_ref)
+        assert torch.allclose(ld, ld_ref, rtol=1e-13, atol=1e-13 * n)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("m", range(13, 21))
+@pytest.mark.parametrize("nrhs", [2, 3])
+def test_lattice_solve_by_coefficients_equals_single_solves(m, nrhs, dtype):
+    """Every default top pass of a solve with its filter formed once (4 to 8
+    axis bits, geometry fixed at compile time) against the solves of the single
+    rows: both within the solve's first-order rounding bound; the fused fit
+    runs the same kernel."""
+    n, s2 = 2**m, 1e-2
+    g = torch.Generator("cuda").manual_seed(m)
+    k1 = torch.rand((1, n), dtype=torch.float64, device="cuda", generator=g)
+    k1 = k1 + k1.roll(-1, 1).flip(1)
+    k1[:, 0] += 2 * n
+    k1 = k1.to(dtype)
+    y = torch.randn((1, nrhs, n), dtype=torch.float64, device="cuda", generator=g).to(dtype)
+    lam, c, _ = ldk.fit("lattice", k1, s2, y)
+    many = ldk.solve("lattice", lam, s2, y)
+    assert torch.equal(c, many)
+    eps = float(torch.finfo(dtype).eps)
+    inv = 1 / (lam + s2).abs().min()
+    for q in range(nrhs):
+        one = ldk.solve("lattice", lam, s2, y[:, q:q + 1].contiguous())
+        tol = 2 * 4 * (2 * m + 2) * eps * inv * y[0, q].double().norm()
+        assert (one[0, 0] - many[0, q]).double().norm() <= tol
