@@ -19,9 +19,10 @@ namespace {
 // CA, CLW >= 0: a and logW fixed at compile time (they must equal a.g.a and
 // a.g.logW); the index maps, group loops and twiddle choices then fold to
 // constants.  REGLAM (real rows only): the E values a thread stores at tile
-// positions t + Tn i go to regl[i] too (PM_FWD), or the filter takes its
-// eigenvalues from regl[i] instead of a.lam (PM_SOLVE / PM_MATVEC) -- the
-// same elements, when both passes have the same geometry.
+// positions t + Tn i go to regl[i] too (PM_FWD; a null a.dst stores them
+// there only), or the filter takes its eigenvalues from regl[i] instead of
+// a.lam (PM_SOLVE / PM_MATVEC) -- the same elements, when both passes have the
+// same geometry.
 template <typename T, int LOGE, int MODE, int LD, int ST, bool SRC_F32, int CA = -1, int CLW = -1,
           bool REGLAM = false>
 __device__ __forceinline__ void pass_body(const PassArgs &a, int64_t bid, double *regl = nullptr)
@@ -142,7 +143,10 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int64_t bid, double
     for (int i = 0; i < E; ++i) {
         T o = v[i];
         if (MODE == PM_FWD || MODE == PM_INV) o = scl(o, sc);
-        if constexpr (REGLAM && MODE == PM_FWD) regl[i] = (double)o;
+        if constexpr (REGLAM && MODE == PM_FWD) {
+            regl[i] = (double)o;
+            if (!a.dst) continue;
+        }
         if constexpr (ST == IO_COMBINE) {
             // the doubling update: the new half's transform o meets the old
             // half's at k (Sec. 5.4, eq. ft_next_parts)
@@ -223,17 +227,22 @@ constexpr bool net_specialised()
 }
 
 // The fit of a net whose transform is one pass (the whole row in one tile),
-// FP64: workgroup r runs replication r's eigenvalue tile, then its
-// right-hand sides' solve tiles, with the pass bodies and arguments of
+// FP64: a workgroup runs replication r's eigenvalue tile, then its part of
+// r's right-hand sides' solve tiles, with the pass bodies and arguments of
 // ldk_eig and ldk_solve (so lambda and c are theirs bit for bit; the solve
 // takes the eigenvalues this workgroup has just computed from registers),
 // then the log-det of the row: per-thread products of the values (LogProd,
 // each thread's values in the order of ldk_logdet's partial loop) and a
-// fixed-order tree.
+// fixed-order tree.  Bound by its chain of barriers, a tile after the other,
+// so the right-hand sides are shared out over `parts` workgroups that each
+// repeat the eigenvalue tile (from L2); the first stores the eigenvalues and
+// the log-det.
 template <int LOGE>
-__global__ __launch_bounds__(512) void k_fit_net_one(PassArgs aE, PassArgs aS, double *logdet)
+__global__ __launch_bounds__(512) void k_fit_net_one(PassArgs aE, PassArgs aS, double *logdet, int parts)
 {
-    const int64_t r = blockIdx.x;
+    const int64_t r = blockIdx.x / parts;
+    const int part = blockIdx.x % parts;
+    if (part) aE.dst = nullptr;
     // thread t keeps the eigenvalues at positions t + T i of the row (the
     // tile is the whole row, and the solve tiles have the same geometry):
     // the solves and the log-det take them from registers, not back from
@@ -242,12 +251,12 @@ __global__ __launch_bounds__(512) void k_fit_net_one(PassArgs aE, PassArgs aS, d
     double lam_t[E];
     pass_body<double, LOGE, PM_FWD, IO_SAME, IO_SAME, false, -1, -1, true>(aE, r, lam_t);
     __syncthreads();  // the LDS is free for the solve tiles
-    for (int q = 0; q < aS.nrhs; ++q) {
+    for (int q = part; q < aS.nrhs; q += parts) {
         pass_body<double, LOGE, PM_SOLVE, IO_SAME, IO_SAME, false, -1, -1, true>(
             aS, r * aS.nrhs + q, lam_t);
         __syncthreads();  // the LDS is free for the next tile
     }
-    if (!logdet) return;
+    if (!logdet || part) return;
     const int t = threadIdx.x, T = blockDim.x;
     LogProd acc;
 #pragma unroll
@@ -558,19 +567,30 @@ int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, h
     if (threads > 512 || threads < 1 || (threads & (threads - 1)) || aE.rows > 0x7fffffff)
         return LDK_ENOTSUP;
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(double);
-    const dim3 grid((unsigned)aE.rows), block(threads);
+    // One workgroup per CU at most (256): R = 2, n = 4096, 8 right-hand sides
+    // 48.9 us in 2 workgroups.  A column that the eigenvalues or the solutions
+    // overwrite is read by one workgroup only.
+    auto meets = [&](const void *p, size_t bytes) {
+        const char *a = static_cast<const char *>(aE.src), *b = static_cast<const char *>(p);
+        return a < b + bytes && b < a + (size_t)aE.rows * S * sizeof(double);
+    };
+    int parts = 1;
+    if (!meets(aE.dst, (size_t)aE.rows * S * sizeof(double)) &&
+        !meets(aS.dst, (size_t)aS.rows * S * sizeof(double)))
+        while (parts < aS.nrhs && aE.rows * (parts + 1) <= 256) ++parts;
+    const dim3 grid((unsigned)(aE.rows * parts)), block(threads);
     switch (g.logE) {
     case 1:
         if ((g.a + 1 - 1) / 1 > MAX_GROUPS) return LDK_ENOTSUP;
-        hipLaunchKernelGGL(k_fit_net_one<1>, grid, block, lds, s, aE, aS, logdet);
+        hipLaunchKernelGGL(k_fit_net_one<1>, grid, block, lds, s, aE, aS, logdet, parts);
         break;
     case 2:
         if ((g.a + 2 - 1) / 2 > MAX_GROUPS) return LDK_ENOTSUP;
-        hipLaunchKernelGGL(k_fit_net_one<2>, grid, block, lds, s, aE, aS, logdet);
+        hipLaunchKernelGGL(k_fit_net_one<2>, grid, block, lds, s, aE, aS, logdet, parts);
         break;
     case 3:
         if ((g.a + 3 - 1) / 3 > MAX_GROUPS) return LDK_ENOTSUP;
-        hipLaunchKernelGGL(k_fit_net_one<3>, grid, block, lds, s, aE, aS, logdet);
+        hipLaunchKernelGGL(k_fit_net_one<3>, grid, block, lds, s, aE, aS, logdet, parts);
         break;
     default: return LDK_ENOTSUP;
     }
