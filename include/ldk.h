@@ -291,7 +291,8 @@ int ldk_logdet_checked(int R, int m, const double *lam, double sigma2, double *o
  * column's and the right-hand sides' forward passes run as one launch, and
  * the pass that forms the eigenvalues also sums their logarithms per tile,
  * so the log-det costs one small reduction instead of a pass over lambda.
- * Other cases run the three entry points in turn.  lam and c equal the
+ * Digital nets of up to 2^20 points with nrhs >= 1 share launches in the same
+ * way (one launch up to 2^12 points in FP64).  Other cases run the three entry points in turn.  lam and c equal the
  * separate calls bit for bit; the log-det to rounding (another fixed
  * summation order).
  * k1 = dtype[R][n]; y, c = dtype[R][nrhs][n]; lam = double[R][n];

@@ -724,6 +724,59 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
             if (st != LDK_ENOTSUP) return st;
         }
     }
+    if (kind == LDK_DNET_B2 && nrhs > 0 && m > 12 &&
+        !(dtype == LDK_F32 && plan_params(kind, dtype, m, (int64_t)R * nrhs).engine == ENGINE_SPLIT16)) {
+        // A net of two passes: three launches (and the log-det's sum in the
+        // last) instead of seven.  From seven to three: FP64, R = 1, n = 2^13,
+        // one right-hand side 28.9 -> 15.9 us (host bound), 2^20 48.7 -> 34.8;
+        // R = 16, n = 2^18, 4 right-hand sides 185 -> 151; R = 1000, n = 2^13, 4
+        // right-hand sides 347 -> 309; FP32 a little more.
+        const Plan pe = tuned_plan(LDK_DNET_B2, LDK_F64, m, m, R);
+        const Plan pq = tuned_plan(LDK_DNET_B2, dtype, m, m, (int64_t)R * nrhs);
+        auto same = [](const PassGeom &a, const PassGeom &b) {
+            return a.b0 == b.b0 && a.a == b.a && a.logW == b.logW && a.logE == b.logE;
+        };
+        const int64_t n = (int64_t)1 << m, tiles = n >> 12;
+        // solutions written over the column: one call after the other
+        if (pe.P == 2 && pq.P == 2 && same(pe.pass[0], pq.pass[0]) && same(pe.pass[1], pq.pass[1]) &&
+            !ranges_meet(k1, (size_t)R * n * esize(dtype), c, (size_t)R * nrhs * n * esize(dtype))) {
+            st = ensure_init();
+            if (st) return st;
+            hipStream_t s = as_stream(stream);
+            // R tiles of partial sums and counters: within the log-det's share
+            // of the workspace (a partial sum per 2^11 eigenvalues, B rows)
+            double *partial = static_cast<double *>(ws);
+            unsigned *count = reinterpret_cast<unsigned *>(partial + R * tiles);
+            PassArgs aK{}, aY{};
+            aK.src = k1;
+            aK.dst = lam;
+            aK.rows = R;
+            aK.nrhs = 1;
+            aY.src = y;
+            aY.dst = c;
+            aY.rows = (int64_t)R * nrhs;
+            aY.nrhs = nrhs;
+            aK.src_row = aK.dst_row = aY.src_row = aY.dst_row = n;
+            aK.m = aY.m = m;
+            aY.sigma2 = sigma2;
+            aY.scale = 1.0 / (double)n;
+            st = launch_net_fit(dtype, pq, aK, aY, lam, logdet ? partial : nullptr, count, s);
+            if (st == LDK_OK) {
+                PassArgs b = aY;
+                b.src = c;
+                b.g = pq.pass[0];
+                b.scale = 1.0;
+                if (logdet) {  // 2^9 elements a tile and more: a full wave
+                    b.ld_part = partial;
+                    b.ld_out = logdet;
+                    b.ld_rows = R;
+                    b.ld_count = tiles;
+                }
+                return launch_pass(kind, dtype, PM_INV, PIO_SAME, PIO_SAME, b, s);
+            }
+            if (st != LDK_ENOTSUP) return st;
+        }
+    }
     if (real_path(kind, m) && !fit_fused(kind, m, dtype) && nrhs > 0 && logdet) {
         // FP32 lattice: the eigenvalue pass leaves the log-det partials, the
         // solve's first inverse pass sums them (no separate log-det read of

@@ -271,6 +271,78 @@ __global__ __launch_bounds__(512) void k_fit_net_one(PassArgs aE, PassArgs aS, d
     if (t == 0) logdet[r] = red[0];
 }
 
+// The fit of a net whose transform is two passes, three launches: the row
+// passes of the column (FP64, job 0) and the right-hand sides (job 1) here,
+// the top passes of both in k_net_fit_top, then the right-hand sides' inverse
+// row pass.  Clears the top pass's `count` counters (one per column tile).
+template <typename T, int CA>
+__global__ __launch_bounds__(1 << (CA - 3)) void k_net_fit_rows(PassArgs aK, PassArgs aY, int64_t nbK,
+                                                                unsigned *count, int64_t counts)
+{
+    constexpr bool F32 = std::is_same<T, float>::value;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < counts) count[i] = 0;
+    const int64_t b = xcd_tile(blockIdx.x, gridDim.x);
+    if (b < nbK) pass_body<double, 3, PM_FWD, IO_SAME, IO_SAME, F32, CA, 0>(aK, b);
+    else pass_body<T, 3, PM_FWD, IO_SAME, IO_SAME, false, CA, 0>(aY, b - nbK);
+}
+
+// Top passes: a workgroup runs a column tile's eigenvalues and then its part
+// of that tile's right-hand sides, the eigenvalues staying in registers (the
+// solve does not read them back), with the pass bodies of ldk_eig and
+// ldk_solve.  Few tiles are shared out over `parts` workgroups each, which
+// repeat the column tile.  lam holds the column's intermediate values and
+// then the eigenvalues, so the workgroup that has read the tile last stores
+// them (nobody waits: every part has them in registers), and the tile's sum of
+// log(lambda + sigma2) at ld_part (may be NULL).
+template <typename T, int CA>
+__global__ __launch_bounds__(512) void k_net_fit_top(PassArgs aK, PassArgs aY, double *lam, double *ld_part,
+                                                     unsigned *count, int parts)
+{
+    constexpr int CLW = 12 - CA, E = 8, Tn = 512;
+    __shared__ double red[8];
+    __shared__ int store;
+    const int t = threadIdx.x;
+    const int64_t b = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t tile = b / parts;
+    const int part = (int)(b % parts);
+    const int64_t tiles = (int64_t)1 << (aK.g.b0 - CLW);
+    const int64_t r = tile / tiles, cb = tile % tiles;
+    double lam_t[E];
+    pass_body<double, 3, PM_FWD, IO_SAME, IO_SAME, false, CA, CLW, true>(aK, tile, lam_t);
+    __syncthreads();  // every thread holds its values: the tile has been read
+    if (t == 0) store = parts == 1 || atomicAdd(count + tile, 1u) == (unsigned)(parts - 1);
+    __syncthreads();
+    if (store) {
+        double *row = lam + (r << aK.m) + (cb << CLW);
+        LogProd acc;
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const int q = t + Tn * i;
+            row[((int64_t)(q >> CLW) << aK.g.b0) + (q & ((1 << CLW) - 1))] = lam_t[i];
+            acc.add(lam_t[i] + aY.sigma2);
+        }
+        if (ld_part) {
+            double ls = acc.value();
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) ls += __shfl_xor(ls, o, 64);
+            if ((t & 63) == 0) red[t >> 6] = ls;
+            __syncthreads();
+            if (t == 0) {
+                double sum = 0.0;
+#pragma unroll
+                for (int w = 0; w < 8; ++w) sum += red[w];
+                ld_part[tile] = sum;
+            }
+        }
+    }
+    for (int q = part; q < aY.nrhs; q += parts) {
+        pass_body<T, 3, PM_SOLVE, IO_SAME, IO_SAME, false, CA, CLW, true>(
+            aY, (r * aY.nrhs + q) * tiles + cb, lam_t);
+        __syncthreads();  // the LDS is free for the next tile
+    }
+}
+
 template <typename T, int LOGE, int MODE, bool SRC_F32>
 int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
 {
@@ -556,6 +628,64 @@ int launch_pass(int kind, int dtype, int mode, int ld, int st, const PassArgs &a
 
 namespace ldk {
 
+namespace {
+template <typename T>
+int launch_nf(const Plan &pl, PassArgs aK, PassArgs aY, double *lam, double *ld_part, unsigned *count,
+              hipStream_t s)
+{
+    constexpr int TILE = 12;
+    const int64_t n = (int64_t)1 << aK.m;
+    const PassGeom &g0 = pl.pass[0], &g1 = pl.pass[1];
+    const int64_t nbK = aK.rows << (aK.m - g0.a), nbY = aY.rows << (aK.m - g0.a);
+    const int64_t tiles = aK.rows << (aK.m - TILE);
+    // Four workgroups of 512 threads a CU (1024 in all): where the tiles give
+    // fewer, the right-hand sides are shared out.
+    int parts = 1;
+    while (parts < aY.nrhs && tiles * (parts + 1) <= 1024) ++parts;
+    if (nbK + nbY > 0x7fffffff || tiles * parts > 0x7fffffff) return LDK_ENOTSUP;
+    if (g1.b0 < TILE - g1.a) return LDK_ENOTSUP;
+    int st = LDK_OK;
+    // both geometries are looked at before anything is launched
+    if (!with_top_geometry<TILE>(g1, [&](auto) { return LDK_OK; }, st)) return LDK_ENOTSUP;
+    aK.g = aY.g = g0;
+    aK.global_tw = aY.global_tw = 0;
+    const double scale = aY.scale;
+    aK.scale = aY.scale = 1.0;
+    if (!with_row_geometry<TILE>(g0, [&](auto ca) {
+            constexpr int A = ca();
+            const size_t lds = (size_t)((1 << A) + (1 << (A - LDS_PAD_SHIFT))) * sizeof(double);
+            hipLaunchKernelGGL((k_net_fit_rows<T, A>), dim3((unsigned)(nbK + nbY)), dim3(1 << (A - 3)), lds, s,
+                               aK, aY, nbK, count, parts > 1 ? tiles : (int64_t)0);
+            return LDK_OK;
+        }, st))
+        return LDK_ENOTSUP;
+    LDK_LAUNCH_CHECK();
+    aK.src = lam;
+    aK.dst = nullptr;
+    aK.src_row = aY.src_row = n;
+    aY.src = aY.dst;
+    aY.scale = scale;
+    aK.g = aY.g = g1;
+    aK.global_tw = aY.global_tw = 1;
+    with_top_geometry<TILE>(g1, [&](auto ca) {
+        const size_t lds = (size_t)((1 << TILE) + (1 << (TILE - LDS_PAD_SHIFT))) * sizeof(double);
+        hipLaunchKernelGGL((k_net_fit_top<T, ca()>), dim3((unsigned)(tiles * parts)), dim3(512), lds, s, aK, aY,
+                           lam, ld_part, count, parts);
+        return LDK_OK;
+    }, st);
+    LDK_LAUNCH_CHECK();
+    return LDK_OK;
+}
+}  // namespace
+
+int launch_net_fit(int dtype, const Plan &pl, const PassArgs &aK, const PassArgs &aY, double *lam,
+                   double *ld_part, unsigned *count, hipStream_t s)
+{
+    if (pl.P != 2 || aK.m < 12) return LDK_ENOTSUP;
+    return dtype == LDK_F64 ? launch_nf<double>(pl, aK, aY, lam, ld_part, count, s)
+                            : launch_nf<float>(pl, aK, aY, lam, ld_part, count, s);
+}
+
 int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, hipStream_t s)
 {
     const PassGeom &g = aE.g;
@@ -570,13 +700,10 @@ int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, h
     // One workgroup per CU at most (256): R = 2, n = 4096, 8 right-hand sides
     // 48.9 us in 2 workgroups.  A column that the eigenvalues or the solutions
     // overwrite is read by one workgroup only.
-    auto meets = [&](const void *p, size_t bytes) {
-        const char *a = static_cast<const char *>(aE.src), *b = static_cast<const char *>(p);
-        return a < b + bytes && b < a + (size_t)aE.rows * S * sizeof(double);
-    };
+    const size_t row = (size_t)S * sizeof(double);
     int parts = 1;
-    if (!meets(aE.dst, (size_t)aE.rows * S * sizeof(double)) &&
-        !meets(aS.dst, (size_t)aS.rows * S * sizeof(double)))
+    if (!ranges_meet(aE.src, aE.rows * row, aE.dst, aE.rows * row) &&
+        !ranges_meet(aE.src, aE.rows * row, aS.dst, aS.rows * row))
         while (parts < aS.nrhs && aE.rows * (parts + 1) <= 256) ++parts;
     const dim3 grid((unsigned)(aE.rows * parts)), block(threads);
     switch (g.logE) {

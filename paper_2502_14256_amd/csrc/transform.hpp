@@ -78,6 +78,13 @@ int plan_candidates(int kind, int dtype, int m, PlanParams *out, int cap);
 // Loads (path) or clears (nullptr) the tuned-parameter table.
 int load_tune_table(const char *path);
 
+// Whether [p, p + bp) and [q, q + bq) share a byte.
+inline bool ranges_meet(const void *p, size_t bp, const void *q, size_t bq)
+{
+    const char *a = static_cast<const char *>(p), *b = static_cast<const char *>(q);
+    return a < b + bq && b < a + bp;
+}
+
 struct PassArgs {
     const void *src;
     void *dst;
@@ -193,6 +200,16 @@ int launch_filter_coef(int dtype, int mode, int mp, int64_t lam_rows, const doub
 // eigenvalue pass aE, then the solve passes aS (nrhs >= 1), then the
 // log-det.  LDK_ENOTSUP when the geometry is not one pass shared by both.
 int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, hipStream_t s);
+// The forward row passes and the top passes of the fit of a net whose plan pl
+// (the same for the FP64 column and the right-hand sides of dtype) is two
+// passes, nrhs >= 1: aK (src = the column of dtype, dst = lam), aY (src = y,
+// dst = c, scale and sigma2 of the solve).  lam receives the eigenvalues, c the
+// rows that the inverse row pass takes, ld_part (may be NULL) the log-det's
+// partial sum of every column tile of 2^12; count: one unsigned per column
+// tile, need not be cleared.  LDK_ENOTSUP, with nothing launched, for other
+// geometries.
+int launch_net_fit(int dtype, const Plan &pl, const PassArgs &aK, const PassArgs &aY, double *lam,
+                   double *ld_part, unsigned *count, hipStream_t s);
 int launch_fit_top(const PassArgs &aK, const PassArgs &aY, double *lam_out, double *ld_part,
                    hipStream_t s);
 // Whether launch_fit_top takes geometry g.

@@ -144,3 +144,36 @@ def test_lattice_solve_by_coefficients_equals_single_solves(m, nrhs, dtype):
         one = ldk.solve("lattice", lam, s2, y[:, q:q + 1].contiguous())
         tol = 2 * 4 * (2 * m + 2) * eps * inv * y[0, q].double().norm()
         assert (one[0, 0] - many[0, q]).double().norm() <= tol
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("m,R,nrhs", [(13, 1, 1), (13, 300, 3), (13, 3, 17), (14, 2, 8), (15, 5, 2),
+                                      (16, 5, 3), (16, 40, 2), (17, 1, 1), (17, 33, 1), (18, 1, 9),
+                                      (19, 2, 2), (20, 1, 1), (20, 3, 2), (21, 1, 1)])
+def test_two_pass_net_fit_equals_separate_calls(m, R, nrhs, dtype):
+    """A two-pass net's fit in three launches, a column tile's right-hand sides
+    in one workgroup or shared out over several: the separate calls bit for
+    bit, with the eigenvalues written over the column (FP64) and the solutions
+    written over it too."""
+    n, s2 = 2**m, 1e-2
+    g = torch.Generator("cuda").manual_seed(m)
+    k1 = torch.rand((R, n), dtype=torch.float64, device="cuda", generator=g)
+    k1[:, 0] += n
+    k1 = k1.to(dtype)
+    y = torch.randn((R, nrhs, n), dtype=torch.float64, device="cuda", generator=g).to(dtype)
+    lam_ref = ldk.eig("dnet", k1)
+    c_ref, ld_ref = ldk.solve("dnet", lam_ref, s2, y), ldk.logdet(lam_ref, s2)
+    runs = [(k1, None, None), (k1, None, y.clone())]
+    if dtype == torch.float64:
+        over = k1.clone()
+        runs.append((over, over, None))
+    if nrhs == 1:
+        over = k1.clone()
+        runs.append((over, None, over[:, None]))
+    for col, lam_out, c_out in runs:
+        rhs = c_out if c_out is not None and c_out.data_ptr() != col.data_ptr() else y
+        lam, c, ld = ldk.fit("dnet", col, s2, rhs, lam=lam_out, c=c_out)
+        assert torch.equal(lam, lam_ref) and torch.equal(c, c_ref)
+        assert torch.allclose(ld, ld_ref, rtol=1e-13, atol=1e-13 * n)
+    lam, c, ld = ldk.fit("dnet", k1, s2, y, logdet=False)
+    assert ld is None and torch.equal(lam, lam_ref) and torch.equal(c, c_ref)
