@@ -139,8 +139,11 @@ size_t power_tmp_bytes(int kind, int64_t R, int m, int dtype)
 int chunks_of(int m) { return (int)((((int64_t)1 << m) + MLL_CHUNK - 1) / MLL_CHUNK); }
 
 // p[r][k] = |FT(y_r)_k|^2 (unnormalised transform), FP64, into `pw`.
+// With part, a net's last pass may take the likelihood's terms with it (pw
+// then receives g and *done is set).
 int power_spectrum(int kind, int R, int m, int dtype, const void *y, double *pw, void *tmp,
-                   hipStream_t s)
+                   hipStream_t s, const double *lam = nullptr, double sigma2 = 0.0,
+                   double *part = nullptr, bool *done = nullptr)
 {
     const int64_t n = (int64_t)1 << m;
     if (m == 0) {
@@ -194,6 +197,14 @@ int power_spectrum(int kind, int R, int m, int dtype, const void *y, double *pw,
         a.dst = last ? (void *)pw : tmp;
         a.dst_row = n;
         a.g = pl.pass[p];
+        if (last && part) {
+            PassArgs b = a;
+            b.dst = nullptr;
+            b.sigma2 = sigma2;
+            const int st = launch_net_mll_top(dtype, b, lam, pw, part, s);
+            *done = st == LDK_OK;
+            if (st != LDK_ENOTSUP) return st;
+        }
         const int st = launch_pass(LDK_DNET_B2, dtype, PM_FWD, PIO_SAME, last ? PIO_POWER : PIO_SAME,
                                    a, s);
         if (st) return st;
@@ -346,14 +357,22 @@ extern "C" int ldk_mll(int kind, int R, int m, int dtype, const double *lam, dou
     if (st) return st;
     hipStream_t s = as_stream(stream);
     const int64_t n = (int64_t)1 << m;
-    const int chunks = chunks_of(m);
+    int chunks = chunks_of(m);
     double *part = static_cast<double *>(ws);
     void *tmp = static_cast<unsigned char *>(ws) + align256((size_t)R * chunks * 3 * sizeof(double));
-    st = power_spectrum(kind, R, m, dtype, y, g, tmp, s);
+    // Nets of more than one pass: the terms in the response's top pass (one sum
+    // per 2^12 values, so within the chunks' share).  The lattice keeps the
+    // separate pass.
+    bool done = false;
+    st = power_spectrum(kind, R, m, dtype, y, g, tmp, s, lam, sigma2, part, &done);
     if (st) return st;
-    hipLaunchKernelGGL(k_mll_terms, dim3(chunks, R), dim3(MLL_THREADS), 0, s, lam, g, n, sigma2,
-                       1.0 / (double)n, chunks, part);
-    LDK_LAUNCH_CHECK();
+    if (done) {
+        chunks = (int)(n >> 12);
+    } else {
+        hipLaunchKernelGGL(k_mll_terms, dim3(chunks, R), dim3(MLL_THREADS), 0, s, lam, g, n, sigma2,
+                           1.0 / (double)n, chunks, part);
+        LDK_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL(k_mll_final, dim3(R), dim3(MLL_THREADS), 0, s, (const double *)part, chunks,
                        n, sigma2, L, dlogs2);
     LDK_LAUNCH_CHECK();

@@ -343,6 +343,60 @@ __global__ __launch_bounds__(512) void k_net_fit_top(PassArgs aK, PassArgs aY, d
     }
 }
 
+// The top pass of a net likelihood's response: |yt|^2 (squared in FP64, as the
+// power-spectrum store) stays in registers and meets the eigenvalues there, so
+// it is neither written nor read back.  Leaves g and the tile's sums of
+// p / n / (lambda + s2), log(lambda + s2) and g.  Bound by memory (lambda and
+// the row read, g written: 84 MB at FP32, R = 64, n = 2^16, in 16.6 us, 5.1
+// TB/s; the power-spectrum store and the pass over it were 9.7 + 18.0).
+template <typename T, int CA>
+__global__ __launch_bounds__(512) void k_net_mll_top(PassArgs a, const double *__restrict__ lam, double inv_n,
+                                                     double *__restrict__ g, double *__restrict__ part)
+{
+    constexpr int CLW = 12 - CA, E = 8, Tn = 512;
+    __shared__ double red[8][3];
+    const int t = threadIdx.x;
+    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t tiles = (int64_t)1 << (a.g.b0 - CLW);
+    const int64_t first = ((tile / tiles) << a.m) + ((tile % tiles) << CLW);
+    auto at = [&](int i) -> int64_t {
+        const int q = t + Tn * i;
+        return first + ((int64_t)(q >> CLW) << a.g.b0) + (q & ((1 << CLW) - 1));
+    };
+    double yt[E], l[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) l[i] = lam[at(i)];  // in flight through the transform
+    pass_body<T, 3, PM_FWD, IO_SAME, IO_SAME, false, CA, CLW, true>(a, tile, yt);
+    double acc[3] = {0.0, 0.0, 0.0};
+    LogProd lsum;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const double s = l[i] + a.sigma2;
+        const double p = yt[i] * yt[i] * inv_n;
+        const double is = 1.0 / s;
+        const double q = p * is;
+        acc[0] += q;
+        lsum.add(s);
+        const double gk = 0.5 * (q - 1.0) * is;  // 1/2 p/s^2 - 1/2 /s
+        acc[2] += gk;
+        g[at(i)] = gk;
+    }
+    acc[1] = lsum.value();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) acc[c] += __shfl_xor(acc[c], o, 64);
+        if ((t & 63) == 0) red[t >> 6][c] = acc[c];
+    }
+    __syncthreads();
+    if (t < 3) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) s += red[w][t];
+        part[tile * 3 + t] = s;
+    }
+}
+
 template <typename T, int LOGE, int MODE, bool SRC_F32>
 int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
 {
@@ -677,6 +731,29 @@ int launch_nf(const Plan &pl, PassArgs aK, PassArgs aY, double *lam, double *ld_
     return LDK_OK;
 }
 }  // namespace
+
+int launch_net_mll_top(int dtype, const PassArgs &a, const double *lam, double *g, double *part,
+                       hipStream_t s)
+{
+    constexpr int TILE = 12;
+    const int64_t blocks = a.rows << (a.m - TILE);
+    if (a.m <= TILE || a.g.b0 + a.g.a != a.m || blocks > 0x7fffffff) return LDK_ENOTSUP;
+    const double inv_n = 1.0 / (double)((int64_t)1 << a.m);
+    int st = LDK_OK;
+    if (!with_top_geometry<TILE>(a.g, [&](auto ca) {
+            constexpr size_t E = (1 << TILE) + (1 << (TILE - LDS_PAD_SHIFT));
+            if (dtype == LDK_F64)
+                hipLaunchKernelGGL((k_net_mll_top<double, ca()>), dim3((unsigned)blocks), dim3(512),
+                                   E * sizeof(double), s, a, lam, inv_n, g, part);
+            else
+                hipLaunchKernelGGL((k_net_mll_top<float, ca()>), dim3((unsigned)blocks), dim3(512),
+                                   E * sizeof(float), s, a, lam, inv_n, g, part);
+            return LDK_OK;
+        }, st))
+        return LDK_ENOTSUP;
+    LDK_LAUNCH_CHECK();
+    return LDK_OK;
+}
 
 int launch_net_fit(int dtype, const Plan &pl, const PassArgs &aK, const PassArgs &aY, double *lam,
                    double *ld_part, unsigned *count, hipStream_t s)

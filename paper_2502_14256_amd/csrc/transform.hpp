@@ -210,6 +210,12 @@ int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, h
 // geometries.
 int launch_net_fit(int dtype, const Plan &pl, const PassArgs &aK, const PassArgs &aY, double *lam,
                    double *ld_part, unsigned *count, hipStream_t s);
+// The top pass of ldk_mll's response rows for nets of more than 2^12 points,
+// with the likelihood's terms: a as for launch_pass (dst NULL, sigma2 set),
+// lam and g [rows][n], part [rows][n / 2^12][3].  LDK_ENOTSUP, with nothing
+// launched, for other geometries.
+int launch_net_mll_top(int dtype, const PassArgs &a, const double *lam, double *g, double *part,
+                       hipStream_t s);
 int launch_fit_top(const PassArgs &aK, const PassArgs &aY, double *lam_out, double *ld_part,
                    hipStream_t s);
 // Whether launch_fit_top takes geometry g.

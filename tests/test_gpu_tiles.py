@@ -177,3 +177,26 @@ def test_two_pass_net_fit_equals_separate_calls(m, R, nrhs, dtype):
         assert torch.allclose(ld, ld_ref, rtol=1e-13, atol=1e-13 * n)
     lam, c, ld = ldk.fit("dnet", k1, s2, y, logdet=False)
     assert ld is None and torch.equal(lam, lam_ref) and torch.equal(c, c_ref)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("m,R", [(12, 3), (13, 5), (14, 1), (15, 2), (16, 9), (17, 1), (18, 2),
+                                 (19, 1), (20, 1), (21, 1)])
+def test_net_likelihood_terms(m, R, dtype):
+    """The terms formed in the response's top pass (2^13 .. 2^20 points) and in
+    the pass of their own, against the same formulas on the transform's output
+    (orthonormal: a rounding of the working type more a side)."""
+    n, s2 = 2**m, 1e-2
+    g = torch.Generator("cuda").manual_seed(m)
+    lam = torch.rand((R, n), dtype=torch.float64, device="cuda", generator=g) * 3
+    y = torch.randn((R, n), dtype=torch.float64, device="cuda", generator=g).to(dtype)
+    L, gr, ds = ldk.mll("dnet", lam, s2, y)
+    q = ldk.transform("dnet", y).double().square() / (lam + s2)
+    ref = 0.5 * (q - 1) / (lam + s2)
+    eps, u = float(torch.finfo(dtype).eps), 2.0**-52
+    # the transforms' values agree but for the scale's rounding; then a few FP64 ones
+    bound = (2 * eps * q + 8 * u * (q + 1)) / (lam + s2)
+    assert ((gr - ref).abs() <= bound).all()
+    Lref = -0.5 * q.sum(1) - 0.5 * (lam + s2).log().sum(1) - 0.5 * n * np.log(2 * np.pi)
+    assert ((L - Lref).abs() <= (2 * eps + m * u) * q.sum(1) + m * u * n * 8).all()
+    assert ((ds - s2 * gr.sum(1)).abs() <= 2 * m * u * s2 * gr.abs().sum(1)).all()
