@@ -14,8 +14,8 @@
 // b.  T digits are kept, the largest T with b^T <= 2^53, so the coordinate is
 // the integer v = sum_t z_t b^(T-1-t) < 2^53 divided by b^T, rounded once.
 //
-// A block takes 64 consecutive indices of one replication, one per lane; its
-// eight waves split the dimensions.  The digits of an index live in registers,
+// A block takes 64 or 128 consecutive indices of one replication, one or two
+// per lane; its eight waves split the dimensions.  The digits of an index live in registers,
 // four to a 32-bit word, so a row of S (or of Faure's C) times the digit
 // vector is one v_dot4_u32_u8 per word; the sum stays below 2^21 and is
 // reduced mod b by a 32-bit reciprocal (32-bit products run at full rate
@@ -45,8 +45,9 @@ constexpr int BP_KMAX = 32;     // index digits (i < 2^32)
 constexpr int BP_QW = BP_KMAX / 4;  // words of a packed digit row
 constexpr int BP_TT = 512;      // threads of a tile block (Halton, Faure)
 constexpr int BP_WAVES = BP_TT / 64;
-constexpr int BP_P = 64;        // points per tile block, one per lane
+constexpr int BP_P = 64;        // points per tile block and point of a lane
 constexpr int BP_DCH = 64;      // dimensions per output tile
+constexpr size_t LDS_PER_CU = 163840;
 
 struct BpArgs {
     int d, flags;
@@ -175,126 +176,151 @@ __device__ __forceinline__ void lane_row(const uint32_t *__restrict__ W, uint64_
     }
 }
 
-// K <= 4 consecutive output digits of one coordinate: their values g before
-// the permutation go through pi_t (K gathers in flight together) and + delta_t
+// K <= 4 consecutive output digits of a coordinate of each of the lane's P
+// points: their values g before the permutation go through pi_t and + delta_t
 // mod b, and join the Horner sum as one integer below b^K < 2^32.
-template <int K, int F>
-__device__ __forceinline__ void digits_join(uint32_t (&g)[K], uint32_t dlane, const uint8_t *prow, int t0, uint32_t b,
-                                            double bK, double &v)
+// (The permutation's bytes held four to a lane and moved by ds_bpermute
+// measured slower than the K P gathers in flight: 186 -> 213 us with every
+// scramble on at R = 16, n = 2^15, d = 52.)
+template <int K, int F, int P>
+__device__ __forceinline__ void digits_join(uint32_t (&g)[P][K], uint32_t dlane, const uint8_t *prow, int t0,
+                                            uint32_t b, double bK, double (&v)[P])
 {
     if constexpr (F & LDK_BR_DP) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) g[k] = prow[(t0 + k) * 256 + g[k]];
-    }
-    if constexpr (F & LDK_BR_DS) {
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            g[k] += __builtin_amdgcn_readlane(dlane, t0 + k);
-            g[k] = min(g[k], g[k] - b);  // the difference wraps where it is negative
+            for (int k = 0; k < K; ++k) g[p][k] = prow[(t0 + k) * 256 + g[p][k]];
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        if constexpr (F & LDK_BR_DS) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                g[p][k] += __builtin_amdgcn_readlane(dlane, t0 + k);
+                g[p][k] = min(g[p][k], g[p][k] - b);  // the difference wraps where it is negative
+            }
         }
-    }
-    uint32_t acc = g[0];
+        uint32_t acc = g[p][0];
 #pragma unroll
-    for (int k = 1; k < K; ++k) acc = __umul24(acc, b) + g[k];  // acc below b^3 < 2^24
-    v = fma(v, bK, (double)acc);
+        for (int k = 1; k < K; ++k) acc = __umul24(acc, b) + g[p][k];  // acc below b^3 < 2^24
+        v[p] = fma(v[p], bK, (double)acc);
+    }
 }
 // Digits t0 .. t0 + K - 1 (all below T) of S z mod b: row t of S is lane t's,
-// read by v_readlane.
-template <int K, int MJ, int F>
+// read by v_readlane (once for the P points).
+template <int K, int MJ, int F, int P>
 __device__ __forceinline__ void digits_lms(const uint32_t (&srows)[MJ], uint32_t dlane, const uint8_t *prow,
-                                           const uint32_t (&z)[MJ], int t0, uint32_t b, uint32_t inv, double bK,
-                                           double &v)
+                                           const uint32_t (&z)[P][MJ], int t0, uint32_t b, uint32_t inv, double bK,
+                                           double (&v)[P])
 {
-    uint32_t g[K];
+    uint32_t g[P][K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        uint32_t s = 0;
+        uint32_t s[P] = {};
 #pragma unroll
-        for (int q = 0; q < MJ; ++q)
-            s = __builtin_amdgcn_udot4(__builtin_amdgcn_readlane(srows[q], t0 + k), z[q], s, false);
-        g[k] = mod_b(s, b, inv);
+        for (int q = 0; q < MJ; ++q) {
+            const uint32_t w = __builtin_amdgcn_readlane(srows[q], t0 + k);
+#pragma unroll
+            for (int p = 0; p < P; ++p) s[p] = __builtin_amdgcn_udot4(w, z[p][q], s[p], false);
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p) g[p][k] = mod_b(s[p], b, inv);
     }
-    digits_join<K, F>(g, dlane, prow, t0, b, bK, v);
+    digits_join<K, F, P>(g, dlane, prow, t0, b, bK, v);
 }
 
-// Coordinate of one point in dimension j of replication r (rj = r d + j,
-// parameters at index p): digit t of the output is w_t = (S z)_t mod b, then
-// pi_t(w_t), then + delta_t mod b (each step as the flags F ask); Horner's
-// rule in FP64 is exact (every partial sum is an integer below 2^53) and the
-// one division rounds.  The wave's lanes first fetch one row of S and one
-// delta each.  Digits go four at a time, as one 32-bit integer each four.
+// Coordinates of the lane's P points in dimension j of replication r (rj = r d
+// + j, parameters at index p): digit t of the output is w_t = (S z)_t mod b,
+// then pi_t(w_t), then + delta_t mod b (each step as the flags F ask);
+// Horner's rule in FP64 is exact (every partial sum is an integer below 2^53)
+// and the one division rounds.  The wave's lanes first fetch one row of S and one delta each.  Digits go four at a time, as one
+// 32-bit integer each four.
 // Without S the digits past the index's own M are zero before the
 // permutation, the same for every lane (skipped where nothing maps them).
 // v / b^T from the rounded reciprocal: two corrections by the exact remainder
 // (the first leaves less than an ulp, the second then rounds correctly).
-template <int MJ, int F>
-__device__ __forceinline__ double coordinate(const BpArgs &a, int p, const uint32_t *__restrict__ lmsw,
-                                             const uint8_t *__restrict__ shift,
-                                             const uint8_t *__restrict__ perm, const uint32_t (&z)[MJ],
-                                             size_t rj, int lane)
+template <int MJ, int F, int P>
+__device__ __forceinline__ void coordinate(const BpArgs &a, int pi, const uint32_t *__restrict__ lmsw,
+                                           const uint8_t *__restrict__ shift,
+                                           const uint8_t *__restrict__ perm, const uint32_t (&z)[P][MJ],
+                                           size_t rj, int lane, double (&x)[P])
 {
     constexpr bool LMS = F & LDK_BR_LMS, DP = F & LDK_BR_DP, DS = F & LDK_BR_DS;
     const uint8_t *prow = DP ? perm + rj * BP_T * 256 : nullptr;
-    const uint32_t b = a.base[p], inv = a.inv[p];
-    const int T = a.T[p];
+    const uint32_t b = a.base[pi], inv = a.inv[pi];
+    const int T = a.T[pi];
     const double bd = (double)b, b2 = bd * bd, b4 = b2 * b2;
     uint32_t dlane = 0;
     if constexpr (DS) dlane = lane < T ? shift[rj * BP_T + lane] : 0u;
-    double v = 0.0;
+    double v[P] = {};
     if constexpr (LMS) {
         uint32_t srows[MJ];
         lane_row<MJ>(lmsw, a.lms_off + ((uint64_t)rj * BP_T + lane) * BP_T, lane, T, srows);
         int t0 = 0;
-        for (; t0 + 4 <= T; t0 += 4) digits_lms<4, MJ, F>(srows, dlane, prow, z, t0, b, inv, b4, v);
+        for (; t0 + 4 <= T; t0 += 4)
+            digits_lms<4, MJ, F, P>(srows, dlane, prow, z, t0, b, inv, b4, v);
         if (t0 + 2 <= T) {
-            digits_lms<2, MJ, F>(srows, dlane, prow, z, t0, b, inv, b2, v);
+            digits_lms<2, MJ, F, P>(srows, dlane, prow, z, t0, b, inv, b2, v);
             t0 += 2;
         }
-        if (t0 < T) digits_lms<1, MJ, F>(srows, dlane, prow, z, t0, b, inv, bd, v);
+        if (t0 < T) digits_lms<1, MJ, F, P>(srows, dlane, prow, z, t0, b, inv, bd, v);
     } else {
         // with a map every digit takes part; those past M start from zero
-        const int rows = DP || DS ? T : min(T, (int)a.M[p]);
+        const int rows = DP || DS ? T : min(T, (int)a.M[pi]);
 #pragma unroll
         for (int q = 0; q < MJ; ++q) {
-            uint32_t g[4] = {z[q] & 255u, (z[q] >> 8) & 255u, (z[q] >> 16) & 255u, z[q] >> 24};
             if (4 * q + 4 <= rows) {
-                digits_join<4, F>(g, dlane, prow, 4 * q, b, b4, v);
+                uint32_t g[P][4];
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) g[p][k] = (z[p][q] >> (8 * k)) & 255u;
+                digits_join<4, F, P>(g, dlane, prow, 4 * q, b, b4, v);
             } else {
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    uint32_t one[1] = {g[k]};
-                    if (4 * q + k < rows) digits_join<1, F>(one, dlane, prow, 4 * q + k, b, bd, v);
-                }
+                for (int k = 0; k < 3; ++k)
+                    if (4 * q + k < rows) {
+                        uint32_t one[P][1];
+#pragma unroll
+                        for (int p = 0; p < P; ++p) one[p][0] = (z[p][q] >> (8 * k)) & 255u;
+                        digits_join<1, F, P>(one, dlane, prow, 4 * q + k, b, bd, v);
+                    }
             }
         }
         if constexpr (DP || DS) {
             int t0 = 4 * MJ;
             for (; t0 + 4 <= T; t0 += 4) {
-                uint32_t g[4] = {0, 0, 0, 0};
-                digits_join<4, F>(g, dlane, prow, t0, b, b4, v);
+                uint32_t g[P][4] = {};
+                digits_join<4, F, P>(g, dlane, prow, t0, b, b4, v);
             }
             for (; t0 < T; ++t0) {
-                uint32_t g[1] = {0};
-                digits_join<1, F>(g, dlane, prow, t0, b, bd, v);
+                uint32_t g[P][1] = {};
+                digits_join<1, F, P>(g, dlane, prow, t0, b, bd, v);
             }
         } else {
-            v *= a.bTM[p];  // exact: below b^T
+#pragma unroll
+            for (int p = 0; p < P; ++p) v[p] *= a.bTM[pi];  // exact: below b^T
         }
     }
-    const double bT = a.bT[p], ib = a.ibT[p];
-    double q = v * ib;
-    q = fma(fma(-bT, q, v), ib, q);
-    return fma(fma(-bT, q, v), ib, q);
+    const double bT = a.bT[pi], ib = a.ibT[pi];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        double q = v[p] * ib;
+        q = fma(fma(-bT, q, v[p]), ib, q);
+        x[p] = fma(fma(-bT, q, v[p]), ib, q);
+    }
 }
 
 // Write a finished tile: rows p < valid of dimensions j0 .. j0+dch-1 of the
 // [R][cnt][d] output.  With every dimension in the tile the rows are one
 // contiguous run.
+template <int PTS>
 __device__ __forceinline__ void flush_tile(double *__restrict__ out, const double *tile, int64_t cnt, int d,
                                            int r, int64_t i0, int j0, int dch, int tid)
 {
     const int64_t rest = cnt - i0;
-    const int valid = rest < BP_P ? (int)rest : BP_P;
+    const int valid = rest < PTS ? (int)rest : PTS;
     double *dst = out + ((size_t)r * cnt + i0) * d + j0;
     if (dch == d) {
         for (int e = tid; e < valid * dch; e += BP_TT) dst[e] = tile[e];
@@ -306,97 +332,110 @@ __device__ __forceinline__ void flush_tile(double *__restrict__ out, const doubl
     }
 }
 
-template <int MJ, int F>
-__device__ __forceinline__ double halton_coordinate(const BpArgs &a, const uint32_t *__restrict__ lmsw,
-                                                    const uint8_t *__restrict__ shift,
-                                                    const uint8_t *__restrict__ perm, uint32_t i, int r,
-                                                    int j, int lane)
+template <int MJ, int F, int P>
+__device__ __forceinline__ void halton_coordinate(const BpArgs &a, const uint32_t *__restrict__ lmsw,
+                                                  const uint8_t *__restrict__ shift,
+                                                  const uint8_t *__restrict__ perm, const uint32_t (&i)[P],
+                                                  int r, int j, int lane, double (&x)[P])
 {
-    uint32_t z[MJ];
-    index_digits_packed<MJ>(a, j, i, z);
-    return coordinate<MJ, F>(a, j, lmsw, shift, perm, z, (size_t)r * a.d + j, lane);
+    uint32_t z[P][MJ];
+#pragma unroll
+    for (int p = 0; p < P; ++p) index_digits_packed<MJ>(a, j, i[p], z[p]);
+    coordinate<MJ, F, P>(a, j, lmsw, shift, perm, z, (size_t)r * a.d + j, lane, x);
 }
 
-// Halton: a block takes 64 consecutive indices of one replication, one per
-// lane; its eight waves split the dimensions (a balanced order from the
-// host) and write into an LDS tile of whole rows, which the block then
-// stores as one contiguous run (d <= 54 fits one tile).  Bound by VALU issue
-// and, with permutations, by the gathers of their bytes.  R = 16, n = 2^15,
-// d = 52 (us): no scrambles 106 -> 64, LMS + DP 196 -> 174 (194 -> 150 VALU
-// instructions a coordinate), LMS + DS 175 -> 151.  Staging S and the
-// permutations in LDS for longer spans of points measured no better (175 to
+// Halton: a block takes 64 P consecutive indices of one replication, P per
+// lane (the rows of S and the permutations are fetched once for them); its
+// eight waves split the dimensions (a balanced order from the host) and write
+// into an LDS tile of whole rows, which the block then stores as one
+// contiguous run (d <= 54 fits one tile).  Bound by VALU issue and, with
+// permutations, by the gathers of their bytes.  R = 16, n = 2^15, d = 52 (us):
+// no scrambles 106 -> 56, LMS + DP 196 -> 138, LMS + DS 175 -> 125.  Three
+// points a lane: 148 (two blocks a CU).  Staging S and the permutations in LDS
+// for longer spans of points measured no better than one point a lane (175 to
 // 185) and loses on small sets.
-template <int F>
+template <int F, int P>
 __global__ __launch_bounds__(BP_TT) void k_gen_halton(BpArgs a, const uint32_t *__restrict__ lmsw,
                                                       const uint8_t *__restrict__ shift,
                                                       const uint8_t *__restrict__ perm,
                                                       double *__restrict__ out)
 {
-    double *tile = reinterpret_cast<double *>(g_bp_lds);  // [64][d]
+    double *tile = reinterpret_cast<double *>(g_bp_lds);  // [64 P][d]
     const int tid = threadIdx.x, lane = tid & 63, r = blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t i0 = (int64_t)blockIdx.x * BP_P;
-    const int64_t ii = i0 + lane;
-    const uint32_t i = (uint32_t)(a.n_min + (ii < a.cnt ? ii : 0));
+    const int64_t i0 = (int64_t)blockIdx.x * (BP_P * P);
+    uint32_t i[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int64_t ii = i0 + 64 * p + lane;
+        i[p] = (uint32_t)(a.n_min + (ii < a.cnt ? ii : 0));
+    }
     for (int q = a.wbeg[wave]; q < (int)a.wbeg[wave + 1]; ++q) {
         const int j = a.ord[q];
         const int mq = (a.M[j] + 3) >> 2;
-        double x;
+        double x[P];
         switch (mq) {
-        case 1: x = halton_coordinate<1, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        case 2: x = halton_coordinate<2, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        case 3: x = halton_coordinate<3, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        case 4: x = halton_coordinate<4, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        case 5: x = halton_coordinate<5, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        case 6: x = halton_coordinate<6, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        case 7: x = halton_coordinate<7, F>(a, lmsw, shift, perm, i, r, j, lane); break;
-        default: x = halton_coordinate<8, F>(a, lmsw, shift, perm, i, r, j, lane); break;
+        case 1: halton_coordinate<1, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        case 2: halton_coordinate<2, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        case 3: halton_coordinate<3, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        case 4: halton_coordinate<4, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        case 5: halton_coordinate<5, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        case 6: halton_coordinate<6, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        case 7: halton_coordinate<7, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
+        default: halton_coordinate<8, F, P>(a, lmsw, shift, perm, i, r, j, lane, x); break;
         }
-        tile[lane * a.d + j] = x;
+#pragma unroll
+        for (int p = 0; p < P; ++p) tile[(64 * p + lane) * a.d + j] = x[p];
     }
     __syncthreads();
-    flush_tile(out, tile, a.cnt, a.d, r, i0, 0, a.d, tid);
+    flush_tile<BP_P * P>(out, tile, a.cnt, a.d, r, i0, 0, a.d, tid);
 }
 
 // Faure: one base for every dimension, so a lane forms its index digits (MJ
 // words) once; dimension j takes z = C_j a mod b from its packed matrix
 // rows.  Tiles of up to 64 dimensions (d may reach 251).
-template <int MJ, int F>
+template <int MJ, int F, int P>
 __global__ __launch_bounds__(BP_TT) void k_gen_faure(BpArgs a, const uint32_t *__restrict__ lmsw,
                                                      const uint8_t *__restrict__ shift,
                                                      const uint8_t *__restrict__ perm,
                                                           const uint32_t *__restrict__ cmat,
                                                           double *__restrict__ out)
 {
-    double *tile = reinterpret_cast<double *>(g_bp_lds);  // [64][min(d, 64)]
+    double *tile = reinterpret_cast<double *>(g_bp_lds);  // [64 P][min(d, 64)]
     const int tid = threadIdx.x, lane = tid & 63, r = blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t i0 = (int64_t)blockIdx.x * BP_P;
-    const int64_t ii = i0 + lane;
-    const uint32_t i = (uint32_t)(a.n_min + (ii < a.cnt ? ii : 0));
+    const int64_t i0 = (int64_t)blockIdx.x * (BP_P * P);
     const uint32_t b = a.base[0], inv = a.inv[0];
-    uint32_t ad[MJ];
-    index_digits_packed<MJ>(a, 0, i, ad);
+    uint32_t ad[P][MJ];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int64_t ii = i0 + 64 * p + lane;
+        index_digits_packed<MJ>(a, 0, (uint32_t)(a.n_min + (ii < a.cnt ? ii : 0)), ad[p]);
+    }
     for (int j0 = 0; j0 < a.d; j0 += BP_DCH) {
         const int dch = a.d - j0 < BP_DCH ? a.d - j0 : BP_DCH;
         for (int jj = wave; jj < dch; jj += BP_WAVES) {
             const int j = j0 + jj;
             // z_t = sum_{k >= t} C[t][k] a_k mod b (zero for t >= M: a_k = 0 there)
             const uint32_t *cj = cmat + (size_t)j * (4 * MJ * MJ);
-            uint32_t z[MJ];
-#pragma unroll
-            for (int q = 0; q < MJ; ++q) z[q] = 0;
+            uint32_t z[P][MJ] = {};
 #pragma unroll
             for (int t = 0; t < 4 * MJ; ++t) {
-                uint32_t s = 0;
 #pragma unroll
-                for (int q = 0; q < MJ; ++q) s = __builtin_amdgcn_udot4(cj[t * MJ + q], ad[q], s, false);
-                z[t >> 2] |= mod_b(s, b, inv) << (8 * (t & 3));
+                for (int p = 0; p < P; ++p) {
+                    uint32_t s = 0;
+#pragma unroll
+                    for (int q = 0; q < MJ; ++q) s = __builtin_amdgcn_udot4(cj[t * MJ + q], ad[p][q], s, false);
+                    z[p][t >> 2] |= mod_b(s, b, inv) << (8 * (t & 3));
+                }
             }
-            tile[lane * dch + jj] = coordinate<MJ, F>(a, 0, lmsw, shift, perm, z, (size_t)r * a.d + j, lane);
+            double x[P];
+            coordinate<MJ, F, P>(a, 0, lmsw, shift, perm, z, (size_t)r * a.d + j, lane, x);
+#pragma unroll
+            for (int p = 0; p < P; ++p) tile[(64 * p + lane) * dch + jj] = x[p];
         }
         __syncthreads();
-        flush_tile(out, tile, a.cnt, a.d, r, i0, j0, dch, tid);
+        flush_tile<BP_P * P>(out, tile, a.cnt, a.d, r, i0, j0, dch, tid);
         __syncthreads();  // the tile is free for the next dimensions
     }
 }
@@ -691,6 +730,12 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
     const int F = ps->flags & (LDK_BR_LMS | LDK_BR_DP | LDK_BR_DS);
     const int dmax = ps->kind == LDK_FAURE && ps->d > BP_DCH ? BP_DCH : ps->d;
     const size_t lds = (size_t)BP_P * dmax * sizeof(double);
+    // Two points a lane where that leaves two blocks a CU (four for Faure) and
+    // the tile lets three share one.  R = 16, n = 2^15, LMS + DP (us): Halton d =
+    // 52 175 -> 138, Faure b = 53, d = 52 135 -> 129; below the line, R = 2, n =
+    // 2^14: 17.7 -> 19.4 and 18.1 -> 18.9; Faure b = 127, d = 100 (64 KiB): 353 -> 361.
+    const bool two = blocks * ps->R >= (ps->kind == LDK_HALTON ? 1024 : 2048) && 3 * 2 * lds <= LDS_PER_CU;
+    const dim3 grid2((unsigned)((blocks + 1) / 2), (unsigned)ps->R);
     if (ps->kind == LDK_FAURE) {
         hipLaunchKernelGGL(k_faure_cmat, dim3((unsigned)ps->d), dim3(64), 0, s, ps->base,
                            digits_kept(ps->base), mq, static_cast<uint32_t *>(ws));
@@ -698,8 +743,12 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
         const uint32_t *cm = static_cast<const uint32_t *>(ws);
 #define BP_FAURE_F(MJ, FL)                                                                              \
     case FL:                                                                                            \
-        hipLaunchKernelGGL((k_gen_faure<MJ, FL>), grid, dim3(BP_TT), lds, s, a, lmsw, ps->shift,        \
-                           ps->perm, cm, out);                                                                    \
+        if (two)                                                                                        \
+            hipLaunchKernelGGL((k_gen_faure<MJ, FL, 2>), grid2, dim3(BP_TT), 2 * lds, s, a, lmsw, ps->shift, \
+                               ps->perm, cm, out);                                                      \
+        else                                                                                            \
+            hipLaunchKernelGGL((k_gen_faure<MJ, FL, 1>), grid, dim3(BP_TT), lds, s, a, lmsw, ps->shift, \
+                               ps->perm, cm, out);                                                      \
         break;
 #define BP_FAURE(MJ)                                                                                    \
     case MJ:                                                                                            \
@@ -717,8 +766,12 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
     } else {
 #define BP_HALTON(FL)                                                                                   \
     case FL:                                                                                            \
-        hipLaunchKernelGGL((k_gen_halton<FL>), grid, dim3(BP_TT), lds, s, a, lmsw, ps->shift, ps->perm,  \
-                           out);                                                                        \
+        if (two)                                                                                        \
+            hipLaunchKernelGGL((k_gen_halton<FL, 2>), grid2, dim3(BP_TT), 2 * lds, s, a, lmsw, ps->shift, \
+                               ps->perm, out);                                                          \
+        else                                                                                            \
+            hipLaunchKernelGGL((k_gen_halton<FL, 1>), grid, dim3(BP_TT), lds, s, a, lmsw, ps->shift,    \
+                               ps->perm, out);                                                          \
         break;
         switch (F) {
             BP_HALTON(0) BP_HALTON(1) BP_HALTON(2) BP_HALTON(3) BP_HALTON(4) BP_HALTON(5) BP_HALTON(6)

@@ -200,3 +200,34 @@ def test_net_likelihood_terms(m, R, dtype):
     Lref = -0.5 * q.sum(1) - 0.5 * (lam + s2).log().sum(1) - 0.5 * n * np.log(2 * np.pi)
     assert ((L - Lref).abs() <= (2 * eps + m * u) * q.sum(1) + m * u * n * 8).all()
     assert ((ds - s2 * gr.sum(1)).abs() <= 2 * m * u * s2 * gr.abs().sum(1)).all()
+
+
+@pytest.mark.parametrize("flags", [0, 1, 2, 4, 3, 5, 7])
+@pytest.mark.parametrize("kind,base,R,d,lo,n", [("halton", 0, 16, 52, 5, 4133), ("halton", 0, 512, 1, 0, 129),
+                                                ("halton", 0, 33, 54, 2**24 - 77, 2049),
+                                                ("faure", 7, 32, 5, 3, 4111), ("faure", 2, 64, 2, 1, 2051),
+                                                ("faure", 53, 8, 53, 0, 16385), ("faure", 67, 8, 60, 9, 16385)])
+def test_digit_sets_two_points_a_lane_equal_their_pieces(kind, base, R, d, lo, n, flags):
+    """Halton and Faure sets large enough for two points a lane (and one whose
+    tile is too large for it) against windows small enough for one: the same
+    arithmetic, bit for bit."""
+    rng = np.random.default_rng(d)
+    T = 53
+    primes = [p for p in range(2, 252) if all(p % q for q in range(2, p))]
+    lms = np.zeros((R, d, T, T), np.uint8)
+    perm = np.zeros((R, d, T, 256), np.uint8)
+    shift = np.zeros((R, d, T), np.uint8)
+    for j in range(d):
+        b = primes[j] if kind == "halton" else base
+        lms[:, j] = np.tril(rng.integers(0, b, (R, T, T)), -1)
+        lms[:, j, range(T), range(T)] = rng.integers(1, b, (R, T))
+        perm[:, j, :, :b] = np.argsort(rng.random((R, T, b)), -1)
+        shift[:, j] = rng.integers(0, b, (R, T))
+    dev = lambda a: torch.from_numpy(a).cuda()
+    ps = ldk.BPointSet(kind, R, d, base=base, flags=flags, lms=dev(lms), perm=dev(perm), shift=dev(shift))
+    x = ldk.gen_bpoints(ps, lo, lo + n)
+    step = max(1, min(1000 // R, n)) * 63
+    for a in list(range(0, n, max(step, n // 4)))[:5] + [max(0, n - 65)]:
+        b = min(n, a + min(step, 63 * 15))
+        assert (b - a + 63) // 64 * R < 1024
+        assert torch.equal(ldk.gen_bpoints(ps, lo + a, lo + b), x[:, a:b]), (a, b)
