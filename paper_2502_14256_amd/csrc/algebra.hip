@@ -786,7 +786,9 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
         hipStream_t s = as_stream(stream);
         const Plan pe = tuned_plan(LDK_LATTICE, LDK_F64, m, m - 1, R);
         const PassGeom &top = pe.pass[pe.P - 1];
-        double *partial = static_cast<double *>(ws);
+        // (a row of one tile: its partial sum is the log-det)
+        const bool one = top.b0 == top.logW;
+        double *partial = one ? logdet : static_cast<double *>(ws);
         void *rest = static_cast<unsigned char *>(ws) +
                      align256((size_t)R * ((size_t)1 << (top.b0 - top.logW)) * sizeof(double));
         int cb = 0;
@@ -794,9 +796,9 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
         if (st) return st;
         bool done = false;
         st = real_apply(dtype, PM_SOLVE, m, (int64_t)R * nrhs, nrhs, lam, sigma2, y, c, rest, s, partial, cb,
-                        logdet, R, &done);
+                        one ? nullptr : logdet, R, &done);
         if (st) return st;
-        if (!done) {
+        if (!one && !done) {
             hipLaunchKernelGGL(k_logdet_final, dim3(R), dim3(LOGDET_THREADS), 0, s, (const double *)partial,
                                cb, logdet);
             LDK_LAUNCH_CHECK();
@@ -824,7 +826,8 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
     const PassGeom top = one_top ? ftop : pl.pass[pl.P - 1];
     const int cb_count = 1 << (top.b0 - top.logW);
     unsigned char *w8 = static_cast<unsigned char *>(ws);
-    double *partial = reinterpret_cast<double *>(w8);
+    // (a row of one tile: its partial sum is the log-det)
+    double *partial = logdet && cb_count == 1 ? logdet : reinterpret_cast<double *>(w8);
     void *wsK = w8 + align256((size_t)B * cb_count * sizeof(double));
     void *wsY = static_cast<unsigned char *>(wsK) + (size_t)R * N * 16;
     PassArgs aK{}, aY{};
@@ -883,7 +886,7 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
     }
     // inverse passes of the right-hand sides; the first one also finishes
     // the log-det when it has a full wave per tile
-    bool ld_done = false;
+    bool ld_done = cb_count == 1;
     for (int p = pl.P - 2; p >= 0; --p) {
         PassArgs b = aY;
         b.lam = nullptr;
