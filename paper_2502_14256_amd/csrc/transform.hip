@@ -204,10 +204,10 @@ __global__ __launch_bounds__(CA >= 0 ? (1 << (CA + CLW - LOGE)) : 512) void k_pa
     else pass_body<T, LOGE, MODE, LD, ST, SRC_F32, CA, CLW>(a1, b - nb0);
 }
 
-// The passes of the default two-pass plans get kernels with their geometry
-// fixed at compile time: the lattice row passes (the packed half-length row in
-// contiguous tiles of 2^8 to 2^11 elements in FP64, 2^9 to 2^12 in FP32), and the
-// digital-net row passes (2^9 to 2^12) and top passes (4 to 8 axis bits).
+// Passes of the default two-pass plans with their geometry fixed at compile
+// time: the lattice's full-tile row passes (the packed half-length row in
+// contiguous tiles of 2^11 elements in FP64, 2^12 in FP32), and the digital
+// nets' row passes (2^9 to 2^12) and top passes (4 to 8 axis bits).
 template <typename T>
 constexpr int tile_log()
 {
@@ -294,7 +294,10 @@ __global__ __launch_bounds__(1 << (CA - 3)) void k_net_fit_rows(PassArgs aK, Pas
 // repeat the column tile.  lam holds the column's intermediate values and
 // then the eigenvalues, so the workgroup that has read the tile last stores
 // them (nobody waits: every part has them in registers), and the tile's sum of
-// log(lambda + sigma2) at ld_part (may be NULL).
+// log(lambda + sigma2) at ld_part (may be NULL).  Bound by memory where the
+// tiles fill the chip, by latency where they do not.  FP32, R = 5, n = 2^16, 3
+// right-hand sides: 9.9 us (eigenvalues 4.3, solve 7.2 and two log-det kernels
+// 6.2 before), the rows above 7.8 (6.1 + 4.3).
 template <typename T, int CA>
 __global__ __launch_bounds__(512) void k_net_fit_top(PassArgs aK, PassArgs aY, double *lam, double *ld_part,
                                                      unsigned *count, int parts)
@@ -775,7 +778,7 @@ int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, h
         return LDK_ENOTSUP;
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(double);
     // One workgroup per CU at most (256): R = 2, n = 4096, 8 right-hand sides
-    // 48.9 us in 2 workgroups.  A column that the eigenvalues or the solutions
+    // 48.9 us in 2 workgroups, 13.2 in 16.  A column that the eigenvalues or the solutions
     // overwrite is read by one workgroup only.
     const size_t row = (size_t)S * sizeof(double);
     int parts = 1;
