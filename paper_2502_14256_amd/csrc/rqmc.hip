@@ -5,8 +5,8 @@
 // (1 + s)^-(d+1) (the integrand of the paper's RQMC example) and the
 // oscillatory cos(2 pi u + s).  The points are regenerated in registers and
 // never written: a block takes KC_THREADS IT consecutive indices of one
-// replication (IT = 8 points per thread, or 2 when that leaves the grid
-// short of the chip's 256 compute units), accumulates s over the dimensions
+// replication (IT = 8 points per thread, 2 when that leaves the grid short of
+// the chip's 256 compute units, 16 for large nets), accumulates s over the dimensions
 // with the same point
 // recurrences as the regenerating kernel column (plus the randomization's
 // shift), applies the integrand and sums in FP64 in a fixed order.
@@ -339,14 +339,18 @@ void launch_pts(dim3 grid, hipStream_t s, const double *x, int d, int64_t n, con
 #undef RQ_PTS_K
 }
 
-constexpr int RQ_IT_FULL = 8, RQ_IT_SMALL = 2;
+constexpr int RQ_IT_FULL = 8, RQ_IT_SMALL = 2, RQ_IT_NET = 16;
 
 int64_t tiles_of(int64_t n, int it) { return (n + KC_THREADS * it - 1) / (KC_THREADS * it); }
 
 // Points per thread: 8, unless the grid would then hold fewer than two
-// blocks per compute unit.
-int rq_iters(int64_t n, int R)
+// blocks per compute unit; 16 for nets that still fill four a unit (the blocks'
+// tables and a dimension's constants serve twice the points).  Corner peak (us
+// a call, 8 / 16 points): R = 16, n = 2^18, d = 50: 67.2 / 64.4; 2^20: 213 /
+// 204; R = 21, n = 2^20, d = 25: 159 / 150; R = 1, n = 2^22, d = 8: 31.2 / 25.8.
+int rq_iters(int kind, int64_t n, int R)
 {
+    if (kind == LDK_DNET_B2 && tiles_of(n, RQ_IT_NET) * R >= 1024) return RQ_IT_NET;
     return tiles_of(n, RQ_IT_FULL) * R < 512 ? RQ_IT_SMALL : RQ_IT_FULL;
 }
 
@@ -357,12 +361,14 @@ void launch_tiles(const KcolArgs &a, const double *coef, double phase, int64_t n
     if (a.ps.kind == LDK_DNET_B2)
         hipLaunchKernelGGL((k_rqmc_tiles<LDK_DNET_B2, LDK_NATURAL, F, IT>), grid, dim3(KC_THREADS),
                            0, s, a, coef, phase, n, part);
-    else if (a.ps.order == LDK_LINEAR)
-        hipLaunchKernelGGL((k_rqmc_tiles<LDK_LATTICE, LDK_LINEAR, F, IT>), grid, dim3(KC_THREADS),
-                           0, s, a, coef, phase, n, part);
-    else
-        hipLaunchKernelGGL((k_rqmc_tiles<LDK_LATTICE, LDK_NATURAL, F, IT>), grid,
-                           dim3(KC_THREADS), 0, s, a, coef, phase, n, part);
+    else if constexpr (IT <= RQ_IT_FULL) {
+        if (a.ps.order == LDK_LINEAR)
+            hipLaunchKernelGGL((k_rqmc_tiles<LDK_LATTICE, LDK_LINEAR, F, IT>), grid, dim3(KC_THREADS),
+                               0, s, a, coef, phase, n, part);
+        else
+            hipLaunchKernelGGL((k_rqmc_tiles<LDK_LATTICE, LDK_NATURAL, F, IT>), grid,
+                               dim3(KC_THREADS), 0, s, a, coef, phase, n, part);
+    }
 }
 
 }  // namespace
@@ -408,7 +414,7 @@ extern "C" int ldk_rqmc(const ldk_pointset *ps, int64_t n, int integrand, const 
                             : ((int64_t)1 << a.ps.m_max);
     if (n < 1 || n > lim) return LDK_EINVAL;
     if (!coef || !mu_r || !stats || !ws) return LDK_EINVAL;
-    const int it = rq_iters(n, a.ps.R);
+    const int it = rq_iters(a.ps.kind, n, a.ps.R);
     const int64_t tiles = tiles_of(n, it);
     // the grid is tiles x R blocks of KC_THREADS work items; a dispatch's
     // work-item count along x must fit 32 bits
@@ -436,13 +442,13 @@ extern "C" int ldk_rqmc(const ldk_pointset *ps, int64_t n, int integrand, const 
     }
     const dim3 grid((unsigned)tiles, (unsigned)a.ps.R);
     const double phase = 6.283185307179586476925286766559 * u;
-    if (integrand == LDK_GENZ_CORNER_PEAK) {
-        if (it == RQ_IT_SMALL) launch_tiles<LDK_GENZ_CORNER_PEAK, RQ_IT_SMALL>(a, coef, phase, n, grid, s, part);
-        else launch_tiles<LDK_GENZ_CORNER_PEAK, RQ_IT_FULL>(a, coef, phase, n, grid, s, part);
-    } else {
-        if (it == RQ_IT_SMALL) launch_tiles<LDK_GENZ_OSCILLATORY, RQ_IT_SMALL>(a, coef, phase, n, grid, s, part);
-        else launch_tiles<LDK_GENZ_OSCILLATORY, RQ_IT_FULL>(a, coef, phase, n, grid, s, part);
-    }
+    auto tiles_f = [&](auto f) {
+        if (it == RQ_IT_SMALL) launch_tiles<f(), RQ_IT_SMALL>(a, coef, phase, n, grid, s, part);
+        else if (it == RQ_IT_FULL) launch_tiles<f(), RQ_IT_FULL>(a, coef, phase, n, grid, s, part);
+        else launch_tiles<f(), RQ_IT_NET>(a, coef, phase, n, grid, s, part);
+    };
+    if (integrand == LDK_GENZ_CORNER_PEAK) tiles_f(std::integral_constant<int, LDK_GENZ_CORNER_PEAK>());
+    else tiles_f(std::integral_constant<int, LDK_GENZ_OSCILLATORY>());
     LDK_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_rqmc_final, dim3(1), dim3(RQ_FINAL_THREADS), 0, s, (const double *)part,
                        (int)tiles, a.ps.R, (double)n, t, mu_r, stats);

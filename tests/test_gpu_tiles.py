@@ -231,3 +231,24 @@ def test_digit_sets_two_points_a_lane_equal_their_pieces(kind, base, R, d, lo, n
         b = min(n, a + min(step, 63 * 15))
         assert (b - a + 63) // 64 * R < 1024
         assert torch.equal(ldk.gen_bpoints(ps, lo + a, lo + b), x[:, a:b]), (a, b)
+
+
+@pytest.mark.parametrize("m,R,d,n", [(17, 16, 3, 2**17 - 3), (18, 16, 17, 2**18 - 4095), (18, 16, 9, 2**18),
+                                     (13, 512, 16, 2**12 + 1), (13, 1024, 5, 4096), (20, 4, 33, 2**20 - 1)])
+def test_rqmc_net_points_per_thread(m, R, d, n):
+    """Net tiles with 8 and 16 points per thread, d across the 16-dimension
+    table chunk, ragged n: the replication means against the points written
+    out (corner peak: relative error (d + 1) d u of a term for the sum in
+    another order, the power's (d + 10) u, then sums of depth log2 n)."""
+    w = _inst("dnet", m, d, R, 1)
+    ps = pointset(w)
+    coef = torch.full((d,), 1.0 / d, dtype=torch.float64, device="cuda")
+    mu, _ = ldk.rqmc(ps, n, "corner_peak", coef)
+    x = ldk.gen_points(ps, 0, n)
+    f = torch.empty((R, n), dtype=torch.float64, device="cuda")
+    for r in range(R):
+        u = ((x[r] >> 32) & 0xffffffff).double() * 2.0**-32 + (x[r] & 0xffffffff).double() * 2.0**-64
+        f[r] = (1 + u @ coef) ** -(d + 1.0)
+    ref = f.mean(1)
+    tol = 4 * (2 * d * (d + 1) + (d + 10) + 2 * m + 20) * 2.0**-52
+    assert ((mu - ref).abs() <= tol * ref).all()
