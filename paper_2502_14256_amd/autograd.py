@@ -30,14 +30,25 @@ from . import (Kernel, LdkError, PointSet, _kind, eig, kernel_column, kernel_gra
                mll_adjoint)
 
 
+def _gamma(log_gamma):
+    """exp in the parameter's own type, as float64[d]: the same bits in both
+    passes."""
+    return torch.exp(log_gamma.detach().reshape(-1)).to(torch.float64).contiguous()
+
+
 def _parameters(log_gamma, log_zeta, log_sigma2):
     """(gamma [d] on the device, zeta, sigma2): the two numbers the library
-    takes from the host come over in one copy, the call's one wait for the
-    device."""
-    theta = torch.exp(torch.cat([log_gamma.detach().reshape(-1), log_zeta.detach().reshape(1),
-                                 log_sigma2.detach().reshape(1)]))
-    zeta, sigma2 = theta[-2:].tolist()
-    return theta[:-2].contiguous(), zeta, sigma2
+    takes from the host, each the exp in its own type.  float64 parameters of
+    one device come over in one copy, the call's one wait for the device."""
+    log_gamma, log_zeta, log_sigma2 = (log_gamma.detach().reshape(-1),
+                                       log_zeta.detach().reshape(1),
+                                       log_sigma2.detach().reshape(1))
+    if all(t.dtype == torch.float64 and t.device == log_gamma.device
+           for t in (log_gamma, log_zeta, log_sigma2)):
+        theta = torch.exp(torch.cat([log_gamma, log_zeta, log_sigma2]))
+        zeta, sigma2 = theta[-2:].tolist()
+        return theta[:-2], zeta, sigma2
+    return _gamma(log_gamma), torch.exp(log_zeta).item(), torch.exp(log_sigma2).item()
 
 
 def _forward_parts(k: Kernel, ps: PointSet, sigma2: float, y, dtype):
@@ -73,8 +84,7 @@ class MarginalLogLikelihood(torch.autograd.Function):
     def backward(ctx, grad_L):
         saved = ctx.saved_tensors
         log_gamma, log_zeta, log_sigma2, y = saved[:4]
-        gamma = torch.exp(log_gamma.reshape(-1)).to(torch.float64).contiguous()
-        k = Kernel(ctx.kind, ctx.alpha, gamma, ctx.zeta)
+        k = Kernel(ctx.kind, ctx.alpha, _gamma(log_gamma), ctx.zeta)
         if ctx.recompute:
             k1, _, g, ds = _forward_parts(k, ctx.ps, ctx.sigma2, y, ctx.dtype)
         else:
