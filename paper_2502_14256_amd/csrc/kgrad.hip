@@ -62,22 +62,38 @@ __device__ __forceinline__ double wave_sum(double v)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Product of the other factors, P / f: FP32 multiplies by the hardware
-// reciprocal (1 ulp; |f| is 0, which never reaches here, or far above the
-// range where the reciprocal overflows), FP64 takes the correctly rounded
-// quotient.
+// Product of the other factors, P / f, f not 0 (the callers' case).  FP32
+// multiplies by the hardware reciprocal (1 ulp; |f| is far above the range
+// where it overflows).
 __device__ __forceinline__ float quot(float p, float f) { return p * __builtin_amdgcn_rcpf(f); }
-// FP64: the hardware's estimate (2^-24 relative), one Newton step (2^-48),
-// and one correction of the quotient from its exact remainder, which leaves
-// half an ulp and a 2^-96 term (the divide's own steps without its second
-// Newton step and its scaling of operands near the ends of the exponent
-// range: f is 0, handled by the callers, or at least an ulp of 1).
+// FP64: the hardware's estimate of 1 / f (2^-24 relative), one Newton step
+// (2^-48), and one correction of the quotient from its exact remainder, which
+// leaves half an ulp and a term of 2^-96.  Where P is infinite or P / f
+// overflows the correction is inf - inf: NaN, for which sum_terms below asks.
 __device__ __forceinline__ double quot(double p, double f)
 {
     double r = __builtin_amdgcn_rcp(f);
     r = fma_r(r, fma_r(-f, r, 1.0), r);
     const double q = p * r;
     return fma_r(fma_r(-f, q, p), r, q);
+}
+// Sum of a thread's KC_ITERS terms, term(l, divide), by quot; an FP64 sum that
+// is NaN is formed again with the full division (one test per KC_ITERS
+// quotients, and the branch is not taken for finite data).
+template <typename R, typename Term>
+__device__ __forceinline__ R sum_terms(Term &&term)
+{
+    R ps = (R)0;
+#pragma unroll
+    for (int l = 0; l < KC_ITERS; ++l) ps += term(l, [](R p, R f) { return quot(p, f); });
+    if constexpr (std::is_same<R, double>::value) {
+        if (__builtin_expect(ps != ps, 0)) {
+            ps = 0.0;
+#pragma unroll
+            for (int l = 0; l < KC_ITERS; ++l) ps += term(l, [](double p, double f) { return p / f; });
+        }
+    }
+    return ps;
 }
 
 // ---- dimension sweeps: call visit(j, l0, t[KC_ITERS], f[KC_ITERS]) for the
@@ -336,28 +352,22 @@ __global__ __launch_bounds__(KC_THREADS) void k_kernel_grad(KgradArgs g)
         // no zero factor at any valid point of the tile
         sweep<R, ALPHA, SRC, IT>(a, L, r, ja, jb, tile0,
                                  [&](int j, int l0, const R(&t)[KC_ITERS], const R(&f)[KC_ITERS]) {
-            R ps = (R)0;
-#pragma unroll
-            for (int l = 0; l < KC_ITERS; ++l) {
-                const R c = av[l0 + l] * (t[l] * quot(pnz[l0 + l], f[l]));
-                ps += ((valid >> (l0 + l)) & 1u) ? c : (R)0;
-            }
-            emit(j, l0, ps);
+            emit(j, l0, sum_terms<R>([&](int l, auto &&divide) {
+                const R c = av[l0 + l] * (t[l] * divide(pnz[l0 + l], f[l]));
+                return ((valid >> (l0 + l)) & 1u) ? c : (R)0;
+            }));
         });
     } else {
         sweep<R, ALPHA, SRC, IT>(a, L, r, ja, jb, tile0,
                                  [&](int j, int l0, const R(&t)[KC_ITERS], const R(&f)[KC_ITERS]) {
-            R ps = (R)0;
-#pragma unroll
-            for (int l = 0; l < KC_ITERS; ++l) {
+            emit(j, l0, sum_terms<R>([&](int l, auto &&divide) {
                 const int k = l0 + l;
-                const R q = quot(pnz[k], f[l]);
+                const R q = divide(pnz[k], f[l]);
                 const R one_zero = (nz[k] == 1 && f[l] == (R)0) ? pnz[k] : (R)0;
                 const R other = nz[k] == 0 ? q : one_zero;
                 const R c = av[k] * (t[l] * other);
-                ps += ((valid >> k) & 1u) ? c : (R)0;
-            }
-            emit(j, l0, ps);
+                return ((valid >> k) & 1u) ? c : (R)0;
+            }));
         });
     }
 }

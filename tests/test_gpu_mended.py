@@ -38,3 +38,49 @@ def test_likelihood_parameters_of_any_float_type(dg, dz, ds, dev):
     for a, b, t in zip(*grads, (lg, lz, ls)):
         assert a.dtype == t.dtype and a.device == t.device and torch.equal(a, b)
         assert a.isfinite().all()
+
+
+@pytest.mark.parametrize("kind", ["dnet", "lattice"])
+@pytest.mark.parametrize("given", ["column", "nothing"])
+def test_gradient_of_infinite_and_overflowing_products(kind, given):
+    """P / f with P infinite, or past the largest number: the quotient that IEEE
+    division gives (infinite), not NaN; a large f keeps its finite quotient."""
+    m, n = 10, 1024
+    gam = [0.5, 0.3, 0.2, 0.25] if given == "column" else [0.9, 0.8, 0.5, 0.4]
+    w = W.small_net(3, m, 4, 1) if kind == "dnet" else W.small_lattice(3, m, 4, 1)
+    w.update(alpha=[2, 1, 2, 1], gamma=gam, zeta=1.0)
+    ps, i = pointset(w), 517
+    a = torch.zeros((1, n), dtype=F64, device="cuda")
+    a[0, i] = 1.0
+    one = lambda j, g: ldk.kernel_column(
+        ldk.Kernel(kind, w["alpha"], torch.tensor([g if q == j else 0.0 for q in range(4)],
+                                                  dtype=F64, device="cuda"), 1.0), ps, 0, n)[0, i].item()
+    f = [one(j, gam[j]) for j in range(4)]
+    f = np.array(f)  # the four factors of point i
+    if given == "column":
+        k = kernel(w)
+        k1 = ldk.kernel_column(k, ps, 0, n)
+        for v in (np.inf, -np.inf, 1.7e308, np.nan):
+            k1[0, i] = v
+            with np.errstate(over="ignore", invalid="ignore"):
+                want = np.append((f - 1) * (v / f), v)
+            got = ldk.kernel_grad(k, ps, 0, n, a, k1=k1)[0].cpu().numpy()
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+            ok = np.isfinite(want)
+            assert np.allclose(got[ok], want[ok], rtol=1e-13)
+        return
+    # products formed by the gradient: one factor of 2^1020 or more overflows
+    # P, or leaves P finite at f >= 2^1022
+    for big in (4e307, 1.1e308):
+        gam = np.array([big, 0.8, 0.5, 0.4])
+        k = ldk.Kernel(kind, w["alpha"], torch.from_numpy(gam).cuda(), 1.0)
+        g = ldk.kernel_grad(k, ps, i, i + 1, a[:, i:i + 1].contiguous())[0].cpu().numpy()
+        f0 = one(0, big)  # a lattice's polynomial overflows itself here (NaN)
+        with np.errstate(over="ignore", invalid="ignore"):
+            P = f0 * f[1] * f[2] * f[3]
+            want = np.append(np.array([f0, *(f[1:] - 1)]) * (P / np.array([f0, *f[1:]])), P)
+        assert np.array_equal(np.isnan(g), np.isnan(want)), (g, want)
+        assert np.array_equal(g[np.isinf(want)], want[np.isinf(want)])
+        ok = np.isfinite(want)
+        assert np.allclose(g[ok], want[ok], rtol=1e-12)
