@@ -777,13 +777,17 @@ int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, h
     if (threads > 512 || threads < 1 || (threads & (threads - 1)) || aE.rows > 0x7fffffff)
         return LDK_ENOTSUP;
     const size_t lds = (size_t)(S + (S >> LDS_PAD_SHIFT)) * sizeof(double);
-    // One workgroup per CU at most (256): R = 2, n = 4096, 8 right-hand sides
-    // 48.9 us in 2 workgroups, 13.2 in 16.  A column that the eigenvalues or the solutions
-    // overwrite is read by one workgroup only.
+    // Solutions written over the column: only where a replication's lie over no
+    // other replication's column, which another workgroup may not have read yet.
     const size_t row = (size_t)S * sizeof(double);
+    const bool over = ranges_meet(aE.src, aE.rows * row, aS.dst, aS.rows * row);
+    if (over && aE.rows > 1 && (aS.nrhs > 1 || aS.dst != aE.src)) return LDK_ENOTSUP;
+    // One workgroup per CU at most (256): R = 2, n = 4096, 8 right-hand sides
+    // 48.9 us in 2 workgroups, 13.2 in 16.  One per replication where outputs lie
+    // over the column (it is read once) or over one another.
     int parts = 1;
-    if (!ranges_meet(aE.src, aE.rows * row, aE.dst, aE.rows * row) &&
-        !ranges_meet(aE.src, aE.rows * row, aS.dst, aS.rows * row))
+    if (!over && !ranges_meet(aE.src, aE.rows * row, aE.dst, aE.rows * row) &&
+        !ranges_meet(aE.dst, aE.rows * row, aS.dst, aS.rows * row))
         while (parts < aS.nrhs && aE.rows * (parts + 1) <= 256) ++parts;
     const dim3 grid((unsigned)(aE.rows * parts)), block(threads);
     switch (g.logE) {

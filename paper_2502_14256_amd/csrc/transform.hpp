@@ -196,7 +196,7 @@ int launch_filter_coef(int dtype, int mode, int mp, int64_t lam_rows, const doub
 // aY.scale / (lambda + aY.sigma2), in one launch.  Same geometry for both;
 // the geometry's logE is 2 or 3 and 2^(a + logW - logE) a multiple of 64, at
 // most 256.
-// The whole fit of a one-pass FP64 net, one workgroup per replication:
+// The whole fit of a one-pass FP64 net in one launch:
 // eigenvalue pass aE, then the solve passes aS (nrhs >= 1), then the
 // log-det.  LDK_ENOTSUP when the geometry is not one pass shared by both.
 int launch_fit_net_one(const PassArgs &aE, const PassArgs &aS, double *logdet, hipStream_t s);

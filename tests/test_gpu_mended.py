@@ -84,3 +84,26 @@ def test_gradient_of_infinite_and_overflowing_products(kind, given):
         assert np.array_equal(g[np.isinf(want)], want[np.isinf(want)])
         ok = np.isfinite(want)
         assert np.allclose(g[ok], want[ok], rtol=1e-12)
+
+
+@pytest.mark.parametrize("m", [3, 10, 12])
+@pytest.mark.parametrize("R,nrhs", [(1, 1), (1, 3), (4, 1), (4, 3), (300, 2)])
+@pytest.mark.parametrize("at", [0, 1])
+def test_one_pass_net_fit_over_its_column(m, R, nrhs, at):
+    """Solutions written over the column: every column row is read before any
+    solution lies over it, wherever in c the column begins (row 0, or the last
+    row it fits at)."""
+    n, s2 = 2**m, 1e-2
+    g = torch.Generator("cuda").manual_seed(m)
+    k1 = torch.rand((R, n), dtype=F64, device="cuda", generator=g)
+    k1[:, 0] += n
+    y = torch.randn((R, nrhs, n), dtype=F64, device="cuda", generator=g)
+    lam_ref = ldk.eig("dnet", k1)
+    c_ref, ld_ref = ldk.solve("dnet", lam_ref, s2, y), ldk.logdet(lam_ref, s2)
+    c = torch.empty((R, nrhs, n), dtype=F64, device="cuda")
+    first = at * (R * nrhs - R) * n
+    col = c.view(-1)[first:first + R * n].view(R, n)
+    col.copy_(k1)
+    lam, c, ld = ldk.fit("dnet", col, s2, y, c=c)
+    assert torch.equal(lam, lam_ref) and torch.equal(c, c_ref)
+    assert torch.allclose(ld, ld_ref, rtol=1e-13, atol=1e-13 * n)
