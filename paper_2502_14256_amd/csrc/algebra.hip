@@ -820,9 +820,12 @@ int ldk_fit(int kind, int R, int nrhs, int m, int dtype, const void *k1, double 
     const int mp = m - 1;
     const int64_t n = (int64_t)1 << m, N = n / 2;
     const Plan pl = tuned_plan(LDK_LATTICE, LDK_F64, m, mp, B);
-    // one rhs per column: both top passes in one launch (narrower tiles)
+    // one rhs per column: both top passes in one launch (narrower tiles), but
+    // where that launch also reads the column, not with solutions over another
+    // replication's row of it
     const PassGeom ftop = fit_top_geom(pl);
-    const bool one_top = nrhs == 1 && fit_top_supported(ftop);
+    const bool crossed = pl.P == 1 && R > 1 && c != k1 && ranges_meet(k1, R * n * 8, c, R * nrhs * n * 8);
+    const bool one_top = nrhs == 1 && !crossed && fit_top_supported(ftop);
     const PassGeom top = one_top ? ftop : pl.pass[pl.P - 1];
     const int cb_count = 1 << (top.b0 - top.logW);
     unsigned char *w8 = static_cast<unsigned char *>(ws);
