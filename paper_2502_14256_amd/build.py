@@ -19,7 +19,7 @@ SOURCES = ["core.hip", "points.hip", "kcol.hip", "kgrad.hip", "transform.hip", "
            "algebra.hip", "mll.hip", "fwht_mfma.hip", "rqmc.hip", "checked.hip", "batch.hip",
            "noalloc.hip", "bpoints.hip"]
 HEADERS = ["common.hpp", "pointset.hpp", "transform.hpp", "passkit.hpp", "kfactor.hpp",
-           "nettile.hpp"]
+           "launchrules.hpp", "nettile.hpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

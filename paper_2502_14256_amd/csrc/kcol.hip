@@ -276,22 +276,6 @@ void with_iters(int it, F &&f)
     }
 }
 
-// Points per thread, by the number of points R cnt: as many as still leave
-// about four blocks per compute unit (tables and per-dimension constants
-// serve more points), one where the launch would otherwise leave compute
-// units idle or hang on one block's chain of dimensions.  Measured (us for 1 /
-// 4 / 8 / 16 points per thread, order 2, FP64): net 2^16 x d = 16: 8.7 / 10.3
-// / 13.3 / 20.3; 2^18 x 32: 21.6 / 19.5 / 24.8 / 38.5; 2^20 x 32: 64 / 28.8 /
-// 26.9 / 40; 2^22 x 64: 401 / 168 / 140 / 139 (FP32 206 / 81 / 62 / 59);
-// lattice 2^16 x 16: 3.9 / 4.8 / 5.7 / 7.6; 2^18 x 32: 7.5 / 7.5 / 9.1 /
-// 12.4; 2^20 x 32: 18.6 / 13.4 / 12.7 / 13.5; 2^22 x 64: 107 / 70 / 64 / 62.
-// (Before: 8 always, with per-block scrambling in one thread per column.)
-int kcol_iters(const PointsetArgs &p, int64_t cnt)
-{
-    const int64_t pts = (int64_t)p.R * cnt, one = (int64_t)1 << (p.kind == LDK_LATTICE ? 19 : 18);
-    return pts < one ? 1 : pts < (1 << 20) ? 4 : pts < (1 << 22) ? 8 : 16;
-}
-
 }  // namespace ldk
 
 using namespace ldk;
@@ -369,10 +353,10 @@ extern "C" int ldk_kernel_column(const ldk_kernel *k, const ldk_pointset *ps, co
         return LDK_OK;
     }
     // tiles aligned to absolute multiples of their size
-    const int it = kcol_iters(p, n_max - n_min);
+    const int it = column_iters(p.kind == LDK_LATTICE, p.R, n_min, n_max);
     const int64_t tile = (int64_t)KC_THREADS * it;
     const int64_t tile_base = (n_min / tile) * tile;
-    const int64_t tiles = (n_max - tile_base + tile - 1) / tile;
+    const int64_t tiles = window_tiles(n_min, n_max, it);
     if (tiles > 0x7fffffff) return LDK_ENOTSUP;
     with_alpha(uniform, [&](auto al) {
         with_iters(it, [&](auto n) {
@@ -398,10 +382,10 @@ extern "C" int ldk_points_column(const ldk_kernel *k, const ldk_pointset *ps, in
     if (n_min < 0 || n_max < n_min || n_max > lim) return LDK_EINVAL;
     if (n_max == n_min) return LDK_OK;  // empty window: the outputs may be NULL
     if (!pts || !k1) return LDK_EINVAL;
-    const int it = kcol_iters(p, n_max - n_min);
+    const int it = column_iters(p.kind == LDK_LATTICE, p.R, n_min, n_max);
     const int64_t tile = (int64_t)KC_THREADS * it;
     const int64_t tile_base = (n_min / tile) * tile;
-    const int64_t kc_tiles = (n_max - tile_base + tile - 1) / tile;
+    const int64_t kc_tiles = window_tiles(n_min, n_max, it);
     const GenGrid g = gen_grid(p, n_min, n_max, pts);
     const int64_t blocks = kc_tiles * p.R + g.tiles * g.chunks * g.R;
     if (blocks > 0x7fffffff) return LDK_ENOTSUP;

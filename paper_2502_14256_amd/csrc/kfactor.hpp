@@ -4,15 +4,12 @@
 
 #include <type_traits>
 
+#include "launchrules.hpp"
 #include "pointset.hpp"
 
 namespace ldk {
 
 namespace {
-constexpr int KC_THREADS = 256;
-constexpr int KC_LOG_THREADS = 8;
-constexpr int KC_ITERS = 8;       // points per thread (spaced KC_THREADS apart) of the gradient
-constexpr int KC_TILE = KC_THREADS * KC_ITERS;
 constexpr int KC_CODE_WORDS = LDK_MAX_D / 32;  // 2-bit order codes, 32 per word
 }  // namespace
 

@@ -9,9 +9,9 @@
 // Given the forward column k1 (formed by the kernel column from bit-identical
 // factors), the product of the other factors is k1_i / f_ij, so a dimension
 // needs nothing of the others: the work is split over groups of dimensions as
-// well as over the points (k_kernel_grad_k1).  The sums over points are FP64:
-// per tile of KC_TILE points a thread adds its KC_ITERS terms in the factor
-// precision, the rest in FP64 in a fixed order.
+// well as over the points.  The sums over points are FP64: per tile a thread
+// adds its points' terms, KC_ITERS at a time, in the factor precision, the rest
+// in FP64 in a fixed order.
 #include <type_traits>
 
 #include "nettile.hpp"
@@ -28,7 +28,7 @@ struct KgradArgs {
     double *part;     // [R][parts][d + 1]
     int64_t tile_base;
     int64_t tiles;
-    int dims_per_block;  // k_kernel_grad_k1
+    int dims_per_block;  // given the forward column
 };
 
 // One DPP lane move of a double (both halves), lanes the control leaves
@@ -372,28 +372,6 @@ __global__ __launch_bounds__(KC_THREADS) void k_kernel_grad(KgradArgs g)
     }
 }
 
-// Points per thread and dimensions per block given the forward column.  The
-// dimensions are independent then, so a grid short of three blocks per
-// compute unit is split over them; a large one takes twice the points per
-// thread in FP32 (the dimension's setup and reduction serve more factors; in
-// FP64, where it would change the order of the sums, nets lose their
-// occupancy to it and lattices gain 5 %).  Measured (us, D = 16 / 8 / 4 / 2
-// dimensions per block): FP64 net 2^16 points x d = 16: 21.0 / 13.8 / 10.2 /
-// 8.8; 2^18 x 32: 22.0 / 18.2 / 17.0 / 20.5; 2^20 x 32: 42.4 / 43.8 / 48.3 /
-// 63.6; 16 instead of 8 points per thread at 2^22 x 64: lattice FP32 133 ->
-// 127, net FP32 132 -> 130, net FP64 268 -> 272.
-void grad_split(const PointsetArgs &p, int64_t cnt, int dtype, int *it, int *dims)
-{
-    auto blocks = [&](int n, int dd) {
-        return (cnt + KC_THREADS * n - 1) / (KC_THREADS * n) * p.R * ((p.d + dd - 1) / dd);
-    };
-    *it = KC_ITERS;
-    *dims = NT_DIMS;
-    if (dtype == LDK_F32 && blocks(2 * KC_ITERS, NT_DIMS) >= 1024)
-        *it = 2 * KC_ITERS;
-    while (*dims > 2 && blocks(*it, *dims) < 768) *dims /= 2;
-}
-
 // grad[r][j] = sum over tiles of the partials in a fixed order: four
 // interleaved sums, tile by tile, then (s0 + s1) + (s2 + s3).  A block takes 64
 // components: its threads bring KG_FINAL_TILES tiles' partials into LDS
@@ -532,7 +510,11 @@ extern "C" int ldk_kernel_grad(const ldk_kernel *k, const ldk_pointset *ps, cons
     const bool given = pts != nullptr;
     int it = KC_ITERS;
     g.dims_per_block = p.d;
-    if (k1 && !given) grad_split(p, n_max - n_min, dtype, &it, &g.dims_per_block);
+    if (k1 && !given) {
+        const GradSplit sp = grad_split(dtype == LDK_F32, p.R, p.d, n_min, n_max);
+        it = sp.it;
+        g.dims_per_block = sp.dims;
+    }
     grad_tiles(given, it, n_min, n_max, &g.tile_base, &g.tiles);
     if (g.tiles > 0x7fffffff) return LDK_ENOTSUP;
     g.a = a;

@@ -1,0 +1,104 @@
+// Launch shapes of the kernels that regenerate points, as functions of the
+// problem's sizes alone (plain host C++).
+//
+// A block takes KC_THREADS consecutive indices per point of a thread, in tiles
+// aligned to absolute multiples of the tile; indices outside the window are
+// formed and dropped.
+#pragma once
+
+#include <cstdint>
+
+namespace ldk {
+
+constexpr int KC_THREADS = 256;
+constexpr int KC_LOG_THREADS = 8;
+constexpr int KC_ITERS = 8;  // points per thread (spaced KC_THREADS apart) of the gradient
+constexpr int NT_DIMS = 16;  // dimensions whose net tables sit in LDS at once
+
+// Tiles of KC_THREADS it indices that cover [n_min, n_max).
+inline int64_t window_tiles(int64_t n_min, int64_t n_max, int it)
+{
+    const int64_t tile = (int64_t)KC_THREADS * it;
+    return (n_max - (n_min / tile) * tile + tile - 1) / tile;
+}
+
+// The points per thread, of `its` (descending, the first is the most that the
+// size of the whole problem suggests), whose tiles of one replication cost
+// least.  A tile costs its points and `setup` points' worth of per-dimension
+// constants and tables, so a replication that does not fill a large tile takes
+// a smaller one (column, lattice FP64, d = 16, us for 16 points per thread / by
+// this rule: R = 2048, n = 2^11 38.5 / 22.9; R = 16384, n = 2^8 243 / 34.2).
+template <int N>
+inline int least_work(const int (&its)[N], int most, int setup, int64_t n_min, int64_t n_max)
+{
+    int best = most;
+    int64_t cost = window_tiles(n_min, n_max, most) * (setup + most);
+    for (int it : its) {
+        const int64_t c = window_tiles(n_min, n_max, it) * (setup + it);
+        if (it < most && c < cost) {
+            cost = c;
+            best = it;
+        }
+    }
+    return best;
+}
+
+// Kernel column: by the number of points R cnt, more points per thread (tables
+// and per-dimension constants serve more of them) where that leaves one (nets,
+// 4 points) to four (16 points) blocks per compute unit, one point where the
+// launch would otherwise leave compute units idle or hang on one block's chain
+// of dimensions.  Measured (us
+// for 1 / 4 / 8 / 16 points per thread, order 2, FP64): net 2^16 x d = 16: 8.7 /
+// 10.3 / 13.3 / 20.3; 2^18 x 32: 21.6 / 19.5 / 24.8 / 38.5; 2^20 x 32: 64 /
+// 28.8 / 26.9 / 40; 2^22 x 64: 401 / 168 / 140 / 139 (FP32 206 / 81 / 62 / 59);
+// lattice 2^16 x 16: 3.9 / 4.8 / 5.7 / 7.6; 2^18 x 32: 7.5 / 7.5 / 9.1 / 12.4;
+// 2^20 x 32: 18.6 / 13.4 / 12.7 / 13.5; 2^22 x 64: 107 / 70 / 64 / 62.  From
+// the 2^22 rows a tile's setup is worth 3.5 points (nets; FP32 4.3) and 0.85
+// (lattices).
+inline int column_iters(bool lattice, int R, int64_t n_min, int64_t n_max)
+{
+    constexpr int its[] = {16, 8, 4, 1};
+    const int64_t pts = (int64_t)R * (n_max - n_min), one = (int64_t)1 << (lattice ? 19 : 18);
+    const int most = pts < one ? 1 : pts < (1 << 20) ? 4 : pts < (1 << 22) ? 8 : 16;
+    return least_work(its, most, lattice ? 1 : 4, n_min, n_max);
+}
+
+// Gradient given the forward column, points regenerated.  The dimensions are
+// independent then, so a grid short of three blocks per compute unit is split
+// over them; a large one takes twice the points per thread in FP32 (the
+// dimension's setup and reduction serve more factors; in FP64, where it would
+// change the order of the sums, nets lose their occupancy to it and lattices
+// gain 5 %).  Measured (us, D = 16 / 8 / 4 / 2 dimensions per block): FP64 net
+// 2^16 points x d = 16: 21.0 / 13.8 / 10.2 / 8.8; 2^18 x 32: 22.0 / 18.2 /
+// 17.0 / 20.5; 2^20 x 32: 42.4 / 43.8 / 48.3 / 63.6; 16 instead of 8 points per
+// thread at 2^22 x 64: lattice FP32 133 -> 127, net FP32 132 -> 130, net FP64
+// 268 -> 272: a tile's setup is worth less than a point.
+struct GradSplit {
+    int it, dims;
+};
+inline GradSplit grad_split(bool f32, int R, int d, int64_t n_min, int64_t n_max)
+{
+    constexpr int its[] = {2 * KC_ITERS, KC_ITERS};
+    auto blocks = [&](int it, int dims) {
+        return window_tiles(n_min, n_max, it) * R * ((d + dims - 1) / dims);
+    };
+    GradSplit s{KC_ITERS, NT_DIMS};
+    if (f32 && blocks(2 * KC_ITERS, NT_DIMS) >= 1024) s.it = least_work(its, 2 * KC_ITERS, 1, n_min, n_max);
+    while (s.dims > 2 && blocks(s.it, s.dims) < 768) s.dims /= 2;
+    return s;
+}
+
+// RQMC sums: 8 points per thread, 2 where the grid would then hold fewer than
+// two blocks per compute unit; 16 for nets that still fill four a unit (the
+// blocks' tables and a dimension's constants serve twice the points).  Corner
+// peak (us a call, 8 / 16 points): R = 16, n = 2^18, d = 50: 67.2 / 64.4; 2^20:
+// 213 / 204; R = 21, n = 2^20, d = 25: 159 / 150; R = 1, n = 2^22, d = 8: 31.2 /
+// 25.8: a tile's setup is worth about a point.
+inline int rqmc_iters(bool net, int R, int64_t n)
+{
+    constexpr int its[] = {16, 8, 2};
+    const int most = net && window_tiles(0, n, 16) * R >= 1024 ? 16 : window_tiles(0, n, 8) * R < 512 ? 2 : 8;
+    return least_work(its, most, 1, 0, n);
+}
+
+}  // namespace ldk

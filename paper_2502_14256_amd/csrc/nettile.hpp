@@ -40,8 +40,6 @@ constexpr uint32_t brev_const(uint32_t v, int bits)
     return r;
 }
 
-constexpr int NT_DIMS = 16;  // dimensions whose tables sit in LDS at once
-
 // Tables of a chunk of dimensions.  w[jj][q]: z of index bit q for
 // q < NW - 1, then z(tile0).
 template <typename Z, int NW>

@@ -5,11 +5,10 @@
 // (1 + s)^-(d+1) (the integrand of the paper's RQMC example) and the
 // oscillatory cos(2 pi u + s).  The points are regenerated in registers and
 // never written: a block takes KC_THREADS IT consecutive indices of one
-// replication (IT = 8 points per thread, 2 when that leaves the grid short of
-// the chip's 256 compute units, 16 for large nets), accumulates s over the dimensions
-// with the same point
-// recurrences as the regenerating kernel column (plus the randomization's
-// shift), applies the integrand and sums in FP64 in a fixed order.
+// replication (IT = 2, 8 or 16 points per thread, rqmc_iters), accumulates s
+// over the dimensions with the same point recurrences as the regenerating
+// kernel column (plus the randomization's shift), applies the integrand and
+// sums in FP64 in a fixed order.
 #include "nettile.hpp"
 
 namespace ldk {
@@ -341,19 +340,6 @@ void launch_pts(dim3 grid, hipStream_t s, const double *x, int d, int64_t n, con
 
 constexpr int RQ_IT_FULL = 8, RQ_IT_SMALL = 2, RQ_IT_NET = 16;
 
-int64_t tiles_of(int64_t n, int it) { return (n + KC_THREADS * it - 1) / (KC_THREADS * it); }
-
-// Points per thread: 8, unless the grid would then hold fewer than two
-// blocks per compute unit; 16 for nets that still fill four a unit (the blocks'
-// tables and a dimension's constants serve twice the points).  Corner peak (us
-// a call, 8 / 16 points): R = 16, n = 2^18, d = 50: 67.2 / 64.4; 2^20: 213 /
-// 204; R = 21, n = 2^20, d = 25: 159 / 150; R = 1, n = 2^22, d = 8: 31.2 / 25.8.
-int rq_iters(int kind, int64_t n, int R)
-{
-    if (kind == LDK_DNET_B2 && tiles_of(n, RQ_IT_NET) * R >= 1024) return RQ_IT_NET;
-    return tiles_of(n, RQ_IT_FULL) * R < 512 ? RQ_IT_SMALL : RQ_IT_FULL;
-}
-
 template <int F, int IT>
 void launch_tiles(const KcolArgs &a, const double *coef, double phase, int64_t n, dim3 grid,
                   hipStream_t s, double *part)
@@ -385,7 +371,7 @@ size_t align256_rq(size_t b) { return (b + 255) & ~(size_t)255; }
 // formed once instead of in every block of the grid.
 size_t rqmc_ws(const PointsetArgs &a, int64_t n)
 {
-    size_t b = align256_rq((size_t)a.R * (size_t)tiles_of(n, RQ_IT_SMALL) * sizeof(double));
+    size_t b = align256_rq((size_t)a.R * (size_t)window_tiles(0, n, RQ_IT_SMALL) * sizeof(double));
     if (a.kind == LDK_DNET_B2 && a.lms)
         b += (size_t)a.R * (size_t)a.d * (size_t)a.m_max * sizeof(uint64_t);
     return b;
@@ -414,8 +400,8 @@ extern "C" int ldk_rqmc(const ldk_pointset *ps, int64_t n, int integrand, const 
                             : ((int64_t)1 << a.ps.m_max);
     if (n < 1 || n > lim) return LDK_EINVAL;
     if (!coef || !mu_r || !stats || !ws) return LDK_EINVAL;
-    const int it = rq_iters(a.ps.kind, n, a.ps.R);
-    const int64_t tiles = tiles_of(n, it);
+    const int it = rqmc_iters(a.ps.kind == LDK_DNET_B2, a.ps.R, n);
+    const int64_t tiles = window_tiles(0, n, it);
     // the grid is tiles x R blocks of KC_THREADS work items; a dispatch's
     // work-item count along x must fit 32 bits
     if (tiles > 0x7fffffff || (uint64_t)tiles * KC_THREADS > 0xffffffffull) return LDK_ENOTSUP;
@@ -433,7 +419,7 @@ extern "C" int ldk_rqmc(const ldk_pointset *ps, int64_t n, int integrand, const 
         // their own columns as they build their step tables.
         uint64_t *cols = reinterpret_cast<uint64_t *>(
             static_cast<unsigned char *>(ws) +
-            align256_rq((size_t)a.ps.R * (size_t)tiles_of(n, RQ_IT_SMALL) * sizeof(double)));
+            align256_rq((size_t)a.ps.R * (size_t)window_tiles(0, n, RQ_IT_SMALL) * sizeof(double)));
         st = ldk_interlace(ps, 1, cols, stream);
         if (st) return st;
         a.ps.gen = cols;
