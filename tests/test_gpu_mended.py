@@ -128,3 +128,25 @@ def test_one_pass_lattice_fit_over_another_row_of_its_column(m):
     assert torch.allclose(lam, lam_ref, rtol=0, atol=1e-13 * n * m)
     assert torch.allclose(c, c_ref, rtol=0, atol=1e-12 * y.abs().max().item())
     assert torch.allclose(ld, ld_ref, rtol=1e-12, atol=1e-12 * n)
+
+
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 8, 15, 16, 17, 19, 64, 66])
+@pytest.mark.parametrize("kind,d,R", [("lattice", 2, 300), ("dnet", 70, 2)])
+@pytest.mark.parametrize("with_k1", [False, True])
+def test_gradient_tile_sums(kind, d, R, tiles, with_k1):
+    """The gradient is the sum over tiles of 2048 points in the stated order (four
+    interleaved sums, the tiles past the last multiple of four in the first),
+    bit for bit, by either of the two summing kernels."""
+    n = 2048 * tiles
+    w = W.small_lattice(7, 1, d, R, m_max=18) if kind == "lattice" else W.small_net(7, 1, d, R, m_max=18)
+    w.update(alpha=[2] * d, gamma=0.3 * 0.8 ** np.arange(d), zeta=1.1)
+    k, ps = kernel(w), pointset(w)
+    g = torch.Generator("cuda").manual_seed(tiles)
+    a = torch.randn((R, n), dtype=F64, device="cuda", generator=g)
+    k1 = ldk.kernel_column(k, ps, 0, n) if with_k1 else None
+    part = lambda t, q: None if t is None else t[:, 2048 * q:2048 * (q + 1)].contiguous()
+    s = [torch.zeros((R, d + 1), dtype=F64, device="cuda") for _ in range(4)]
+    for q in range(tiles):
+        s[q % 4 if q < tiles // 4 * 4 else 0] += ldk.kernel_grad(k, ps, 2048 * q, 2048 * (q + 1), part(a, q),
+                                                                  k1=part(k1, q))
+    assert torch.equal(ldk.kernel_grad(k, ps, 0, n, a, k1=k1), (s[0] + s[1]) + (s[2] + s[3]))
