@@ -63,6 +63,23 @@ inline int column_iters(bool lattice, int R, int64_t n_min, int64_t n_max)
     return least_work(its, most, lattice ? 1 : 4, n_min, n_max);
 }
 
+// The column beside the point words in one launch: column blocks share the
+// chip with the stores, so one point per thread only while the launch is short.
+// Measured (us for 1 / 4 / 8 / 16 points per thread, FP64): lattice 2^16 x d =
+// 16: 5.6 / 5.6 / 7.2 / 9.2; 2^17 x 2: 4.6 / 4.4 / 4.4 / 4.4, x 32: 9.7 / 11.3 /
+// 13.1 / 16.5; 160000 x 16: 7.5 / 8.4 / 8.2 / 10.4, x 64: 20.6 / 17.9 / 21.2 /
+// 27.8; 2^18 x 6: 7.1 / 6.3 / 6.4 / 6.6, x 64: 30.4 / 22.8 / 22.7 / 27.8; 2^19 x
+// 16: 14.2 / 17.3 / 13.7 / 13.5; 2^22 x 6: 37.6 / 39.1 / 47.2 / 38.2, x 16: 106 /
+// 111 / 105 / 107.  Net 2^16 x 64: 32.2 / 33.9 / 47.1 / 74.5; 2^17 x 4: 15.1 /
+// 14.1 / 14.2 / 14.3, x 32: 30.0 / 26.3 / 26.2 / 40.8; above as the column alone.
+inline int points_column_iters(bool lattice, int R, int64_t n_min, int64_t n_max)
+{
+    constexpr int its[] = {16, 8, 4, 1};
+    const int64_t pts = (int64_t)R * (n_max - n_min), eight = (int64_t)1 << (lattice ? 18 : 20);
+    const int most = pts < (1 << 17) ? 1 : pts < eight ? 4 : pts < (1 << 22) ? 8 : 16;
+    return least_work(its, most, lattice ? 1 : 4, n_min, n_max);
+}
+
 // Gradient given the forward column, points regenerated.  The dimensions are
 // independent then, so a grid short of three blocks per compute unit is split
 // over them; a large one takes twice the points per thread in FP32 (the
