@@ -467,12 +467,14 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t f, uint32_t w) { return __
 // NUS.  Bound by the 64 mixing functions a coordinate (VALU): the first
 // NUS_B digits have at most 2^NUS_B prefixes, so a block forms their flips
 // once per dimension, as a table over the top NUS_B digits, and a point mixes
-// the remaining 64 - NUS_B.  Block: NUS_D dimensions (one wave each), one
-// replication, `span` consecutive indices (a multiple of 64), 64 at a time,
-// one per lane; the word of an index is a lane word (its low 6 bits) XOR a
-// wave-uniform one.  The tile of 64 points x NUS_D coordinates goes out in
-// runs of 8 NUS_D bytes per point (less than a tenth of the store
-// bandwidth is in use).  R = 16, d = 52, n = 2^16: 2.10 -> 1.14 ms.
+// the remaining 64 - NUS_B.  Block: up to NUS_D dimensions (a wave each; the
+// dimensions go to the blocks as evenly as they can), one replication, `span`
+// consecutive indices (a multiple of 64), 64 at a time, one per lane; the word
+// of an index is a lane word (its low 6 bits) XOR a wave-uniform one.  The
+// tile's coordinates go out in runs of up to 8 NUS_D bytes per point (less than
+// a tenth of the store bandwidth is in use).  Measured: R = 16, n = 2^16, d = 52
+// 2.00 -> 1.13 ms; d = 1 90 -> 36 us (always four waves a block: 114), d = 5
+// 206 -> 169 (199).
 constexpr int NUS_B = 12;  // table digits: 8 KiB per dimension, 2^12 mixing functions per block
 constexpr int NUS_D = 4;
 constexpr int NUS_T = 64 * NUS_D;
@@ -483,24 +485,27 @@ __global__ __launch_bounds__(NUS_T) void k_gen_nus(int d, int m, int B, int span
                                                    const uint64_t *__restrict__ seed,
                                                    double *__restrict__ out)
 {
-    __shared__ uint16_t table[NUS_D][1 << NUS_B];  // [top B digits] -> their flips
+    uint16_t *const table = reinterpret_cast<uint16_t *>(g_bp_lds);  // [NUS_D][top B digits] -> their flips
     __shared__ double tile[64][NUS_D + 1];
     const int tid = threadIdx.x, lane = tid & 63, r = blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // blocks of the same points are neighbours: their runs share cache lines
     const int groups = (d + NUS_D - 1) / NUS_D;
-    const int j0 = (int)(blockIdx.x % groups) * NUS_D, dims = d - j0 < NUS_D ? d - j0 : NUS_D;
-    const int j = j0 + (wave < dims ? wave : 0);  // idle waves repeat dimension j0
+    const int gj = (int)(blockIdx.x % groups);
+    const int j0 = gj * d / groups, dims = (gj + 1) * d / groups - j0;  // as even as they go
+    const int W = blockDim.x >> 6;       // waves: the most dimensions of a group
+    const bool live = wave < dims;       // the last wave of a smaller group only stores
+    const int j = j0 + (live ? wave : 0);
     const uint64_t s = seed[(size_t)r * d + j];
     const uint64_t *__restrict__ col = gen + (size_t)j * m;
-    uint16_t *const tab = table[wave];
+    uint16_t *const tab = table + (wave << B);
     const uint64_t cs = mix_first(s);
     // flips of the top b digits from those of the top b - 1: entry q becomes
     // 2 q and 2 q + 1.  The wave goes from the last entries down, so that an
     // entry is read before it is overwritten: a step reads entries q0 .. q0 +
     // 63 and then writes 2 q0 .. 2 q0 + 127.
     if (lane == 0) tab[0] = 0;
-    for (int b = 1; b <= B; ++b) {
+    for (int b = 1; b <= B && live; ++b) {
         const int half = 1 << (b - 1);
         for (int q0 = (half - 1) & ~63; q0 >= 0; q0 -= 64) {
             const int q = q0 + lane;
@@ -525,21 +530,25 @@ __global__ __launch_bounds__(NUS_T) void k_gen_nus(int d, int m, int B, int span
     for (int k = 6; k < m; ++k) zu ^= col[k] & -(uint64_t)((lo >> k) & 1);
     const int64_t end = first + span < n_min + cnt ? first + span : n_min + cnt;
     for (int64_t i0 = lo; i0 < end; i0 += 64) {
-        const uint64_t z = zl ^ zu, zz = mix_first(z);
-        // c's XORs with the 52 constants stay in the loop, on the scalar unit
-        // (hoisted, they spill the scalar registers)
-        uint64_t c = cs;
-        asm volatile("" : "+s"(c));
-        uint32_t fh = B ? tab[z >> (64 - B)] : 0, fl = 0;
-        for (int t = B + 1; t <= NUS_B; ++t) fh = shift_in(fh, nus_flip_word(zz, c, t));
+        uint64_t z = zl ^ zu;
+        if (live) {
+            const uint64_t zz = mix_first(z);
+            // c's XORs with the 52 constants stay in the loop, on the scalar unit
+            // (hoisted, they spill the scalar registers)
+            uint64_t c = cs;
+            asm volatile("" : "+s"(c));
+            uint32_t fh = B ? tab[z >> (64 - B)] : 0, fl = 0;
+            for (int t = B + 1; t <= NUS_B; ++t) fh = shift_in(fh, nus_flip_word(zz, c, t));
 #pragma unroll
-        for (int t = NUS_B + 1; t <= 32; ++t) fh = shift_in(fh, nus_flip_word(zz, c, t));
+            for (int t = NUS_B + 1; t <= 32; ++t) fh = shift_in(fh, nus_flip_word(zz, c, t));
 #pragma unroll
-        for (int t = 33; t <= 64; ++t) fl = shift_in(fl, nus_flip_word(zz, c, t));
+            for (int t = 33; t <= 64; ++t) fl = shift_in(fl, nus_flip_word(zz, c, t));
+            z ^= ((uint64_t)fh << 32) | fl;
+        }
         __syncthreads();  // the previous tile is out
-        tile[lane][wave] = unit_f64(z ^ (((uint64_t)fh << 32) | fl));
+        if (live) tile[lane][wave] = unit_f64(z);
         __syncthreads();
-        const int p = tid / NUS_D, q = tid % NUS_D;
+        const int p = tid / W, q = tid % W;
         const int64_t i = i0 + p;
         if (q < dims && i >= first && i < end)
             out[((size_t)r * cnt + (i - n_min)) * d + j0 + q] = tile[p][q];
@@ -553,9 +562,9 @@ __global__ __launch_bounds__(NUS_T) void k_gen_nus(int d, int m, int B, int span
 
 // Indices per NUS block and table digits: the longest span that leaves about
 // ten blocks per compute unit (the tail of the last round of blocks is a
-// tenth of the launch), 64 at least, and a table of at most a sixteenth of
-// the span's points, so that forming it costs a thousandth of using it per
-// digit saved.
+// tenth of the launch), 64 at least, and a table of at most half the span's
+// points, so that forming it (2^B - 1 mixing functions) costs 4 % (a span of
+// 8192) to 10 % (64) of the B span that it saves.
 struct NusSplit {
     int span, B;
 };
@@ -651,11 +660,14 @@ extern "C" int ldk_gen_bpoints(const ldk_bpointset *ps, int64_t n_min, int64_t n
     hipStream_t s = as_stream(stream);
     if (ps->kind == LDK_DNET_NUS) {
         const int64_t groups = (ps->d + NUS_D - 1) / NUS_D;
+        const unsigned waves = (unsigned)((ps->d + groups - 1) / groups);
         const NusSplit sp = nus_split(cnt, groups * ps->R);
         const int64_t blocks = (cnt + sp.span - 1) / sp.span * groups;
-        if ((uint64_t)blocks * NUS_T > 0xffffffffull) return LDK_ENOTSUP;
-        hipLaunchKernelGGL(k_gen_nus, dim3((unsigned)blocks, (unsigned)ps->R), dim3(NUS_T),
-                           0, s, ps->d, ps->m, sp.B, sp.span, n_min, cnt, ps->gen, ps->seed, out);
+        if ((uint64_t)blocks * waves * 64 > 0xffffffffull) return LDK_ENOTSUP;
+        // (the table's size in LDS by its digits: short spans keep eight blocks a CU)
+        const size_t lds = (size_t)waves * sizeof(uint16_t) << sp.B;
+        hipLaunchKernelGGL(k_gen_nus, dim3((unsigned)blocks, (unsigned)ps->R), dim3(64 * waves),
+                           lds, s, ps->d, ps->m, sp.B, sp.span, n_min, cnt, ps->gen, ps->seed, out);
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }

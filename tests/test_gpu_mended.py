@@ -6,7 +6,7 @@ import torch
 
 import paper_2502_14256_amd as ldk
 import workloads as W
-from ldk_dev import kernel, pointset
+from ldk_dev import dev_u64, kernel, pointset
 from paper_2502_14256_amd.autograd import MarginalLogLikelihood
 
 pytestmark = pytest.mark.gpu
@@ -150,3 +150,38 @@ def test_gradient_tile_sums(kind, d, R, tiles, with_k1):
         s[q % 4 if q < tiles // 4 * 4 else 0] += ldk.kernel_grad(k, ps, 2048 * q, 2048 * (q + 1), part(a, q),
                                                                   k1=part(k1, q))
     assert torch.equal(ldk.kernel_grad(k, ps, 0, n, a, k1=k1), (s[0] + s[1]) + (s[2] + s[3]))
+
+
+@pytest.mark.parametrize("R,d,m,lo,hi", [(1, 1, 16, 0, 2**16), (16, 1, 15, 3, 2**15), (2, 2, 13, 65, 8000),
+                                         (7, 3, 12, 0, 4096), (5, 6, 14, 1, 2**14 - 1), (3, 7, 10, 0, 1000),
+                                         (4, 9, 13, 100, 101), (1, 13, 12, 0, 64)])
+def test_nus_dimensions_that_do_not_fill_a_block(orc, R, d, m, lo, hi):
+    """One to four dimensions a block, uneven groups: bit-exact at both ends."""
+    t = W.small_net(m, m, d)
+    seed = W.nus_seeds(m, R, d)
+    ps = ldk.BPointSet("nus", R, d, gen=dev_u64(t["gen"]), seed=dev_u64(seed), m=m)
+    x = ldk.gen_bpoints(ps, lo, hi).cpu().numpy()
+    for a, b in ((lo, min(lo + 130, hi)), (max(lo, hi - 130), hi)):
+        ref = orc.unit_points(orc.nus_points(t["gen"], seed, m, a, b))
+        assert np.array_equal(x[:, a - lo:b - lo], ref), (a, b)
+
+
+def test_nus_work_goes_with_the_dimensions():
+    """One dimension costs well below four (a third measured, the same when the
+    block's other waves repeat it)."""
+    us = {}
+    for d in (1, 4):
+        t = W.small_net(5, 16, d)
+        ps = ldk.BPointSet("nus", 16, d, gen=dev_u64(t["gen"]), seed=dev_u64(W.nus_seeds(5, 16, d)), m=16)
+        out = torch.empty((16, 2**16, d), dtype=F64, device="cuda")
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ldk.gen_bpoints(ps, 0, 2**16, out=out)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        us[d] = min(times)
+    assert us[1] < 0.7 * us[4], us
