@@ -110,7 +110,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int64_t bid, double
         double l[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) l[i] = REGLAM ? regl[i] : lam[gidx(t + Tn * i)];
-        if constexpr (!REGLAM && !FFT) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!REGLAM && !FFT && CA >= 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < E; ++i) {
             const double f = MODE == PM_SOLVE ? a.scale / (l[i] + a.sigma2) : a.scale * l[i];
