@@ -6,6 +6,7 @@
 // and the update that doubles n (eq. ft_next_parts).
 #include <cmath>
 
+#include "launchrules.hpp"
 #include "transform.hpp"
 
 namespace ldk {
@@ -955,7 +956,7 @@ int ldk_update_double(int kind, int B, int m, int dtype, const void *yt_old, con
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }
-    if (real_path(kind, m)) {
+    if (lat && packed_update(dtype == LDK_F32, B, m)) {
         // the new half is real: packed rows of n/2 (in the second halves of
         // the output rows), and the top pass meets the old half's transform.
         // A tile of the top pass reads the elements n + k, k < n/2, that it
@@ -1017,7 +1018,7 @@ int ldk_eig_update_double(int kind, int R, int m, int dtype, const double *lam_o
         LDK_LAUNCH_CHECK();
         return LDK_OK;
     }
-    if (real_path(kind, m)) {
+    if (lat && packed_update(false, R, m)) {
         PassArgs a{};
         a.rows = R;
         return real_update(LDK_F64, PM_UPDATE_EIG, m, a, k1_new, dtype == LDK_F32, lam_old, lam_full, ws, n / 2, s);

@@ -118,4 +118,19 @@ inline int rqmc_iters(bool net, int R, int64_t n)
     return least_work(its, most, 1, 0, n);
 }
 
+// The n -> 2n update of a lattice on its real new half: packed rows of n / 2
+// complex entries, or rows of n.  Packed halves the transform and lengthens each
+// workgroup's chain (untangling, two twiddles), so it loses where many short rows
+// are a workgroup of one or a few lanes each, and for a few rows of FP32 in two
+// passes.  Measured (us, rows of n / packed): FP64 m = 3, 1 row 4.2 / 3.5; m = 5,
+// 256 rows 5.9 / 6.1, 2048 rows 9.9 / 14.5; m = 7, 2048 rows 9.5 / 16.3; m = 8
+// 10.3 / 11.4; m = 9 14.7 / 13.9; FP32 m = 9, 256 rows 6.3 / 6.7, m = 10 7.2 / 6.2;
+// m = 15, 1 row 12.9 / 14.3, 16 rows 14.3 / 15.5; m = 17, 1 row 14.3 / 15.0, 16
+// rows 25.4 / 20.5; m = 19, 1 row 17.0 / 16.7.
+inline bool packed_update(bool f32, int64_t rows, int m)
+{
+    if (m < 2 || (m >= 4 && m <= (f32 ? 9 : 8))) return false;
+    return !(f32 && m >= 14 && rows << (m - 13) <= 64);
+}
+
 }  // namespace ldk

@@ -215,6 +215,31 @@ __device__ __forceinline__ void real_top_body(const PassArgs &a, double *lam_out
         lds_write(v, lds, t, LOGE, logW + top_s, Tn);
         __syncthreads();
     }
+    // The update reads the old half's values and W_{2n}^k for UB elements at a
+    // time: its stores may lie over the old half (in place), so no load passes
+    // them, and element by element every one waited for the one before (us by
+    // element / by four: eigenvalues 2^13 -> 2^14 10.7 / 10.2, 2048 x 2^10 17.6 /
+    // 16.6; all eight at once, or held from the data loads on, take the registers
+    // of a second workgroup: 2048 x 2^11 49.5 against 28.4).
+    constexpr int UB = E < 4 ? E : 4;
+    T w2v[UB], o1v[UB], o2v[UB];
+    auto fetch_old = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            const int q = t + Tn * (i0 + u);
+            const int64_t k = col_of(q & (W - 1)) + N1 * (int64_t)(q >> logW);
+            w2v[u] = tw_any<R>((uint64_t)k, mp + 2);  // W_{2n}^k
+            if constexpr (MODE == PM_UPDATE_EIG) {
+                const double *od = static_cast<const double *>(a.old) + row * n;
+                f1[u] = od[k];
+                f2[u] = od[k + N];
+            } else {
+                const T *od = static_cast<const T *>(a.old) + row * n;
+                o1v[u] = od[k];
+                o2v[u] = od[k + N];
+            }
+        }
+    };
     LogProd lsum;       // PM_FWD with ld_part: sum of log(lambda + s2)
     double qacc = 0.0;  // PM_QFORM: weighted sum of |Y|^2
 #pragma unroll
@@ -261,6 +286,9 @@ __device__ __forceinline__ void real_top_body(const PassArgs &a, double *lam_out
             continue;
         }
         const int64_t k = k1 + N1 * k2;
+        if constexpr (UPDATE) {
+            if (i % UB == 0) fetch_old(i);
+        }
         const T ev{(zk.re + zm.re) * (R)0.5, (zk.im - zm.im) * (R)0.5};
         const T dv{(zk.re - zm.re) * (R)0.5, (zk.im + zm.im) * (R)0.5};
         const T od{dv.im, -dv.re};  // -i (Z_k - conj Z_{N-k}) / 2
@@ -280,22 +308,19 @@ __device__ __forceinline__ void real_top_body(const PassArgs &a, double *lam_out
             lam_out[row * n + k + N] =
                 (double)ykn.re * (double)ykn.re + (double)ykn.im * (double)ykn.im;
         } else if constexpr (UPDATE) {
-            // the old half's values were not needed before: read here
-            const T w2 = tw_any<R>((uint64_t)k, mp + 2);  // W_{2n}^k
+            const T w2 = w2v[i % UB];
             const T o1 = cmul(yk, w2), o2 = cmul(ykn, T{w2.im, -w2.re});
             if constexpr (MODE == PM_UPDATE_EIG) {
-                const double *od = static_cast<const double *>(a.old) + row * n;
                 double *full = static_cast<double *>(a.dst) + row * a.dst_row;
-                const double d1 = od[k], d2 = od[k + N];
+                const double d1 = f1[i % UB], d2 = f2[i % UB];
                 full[k] = d1 + (double)o1.re;
                 full[n + k] = d1 - (double)o1.re;
                 full[k + N] = d2 + (double)o2.re;
                 full[n + k + N] = d2 - (double)o2.re;
             } else {
                 const R h = (R)0.70710678118654752440, sc = (R)a.scale;
-                const T *od = static_cast<const T *>(a.old) + row * n;
                 T *full = static_cast<T *>(a.dst) + row * a.dst_row;
-                const T d1 = od[k], d2 = od[k + N];
+                const T d1 = o1v[i % UB], d2 = o2v[i % UB];
                 const T p1 = scl(o1, sc), p2 = scl(o2, sc);
                 full[k] = scl(add(d1, p1), h);
                 full[n + k] = scl(sub(d1, p1), h);

@@ -185,3 +185,33 @@ def test_nus_work_goes_with_the_dimensions():
             times.append(a.elapsed_time(b))
         us[d] = min(times)
     assert us[1] < 0.7 * us[4], us
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("B,m", [(1, 2), (5, 3), (3, 4), (1000, 5), (2, 9), (3, 10), (1, 14), (65, 14), (2, 16),
+                                 (1, 18), (3, 18), (1, 20), (2, 20), (1, 21), (1, 22)])
+def test_lattice_update_plans(B, m, dtype):
+    """Every plan of the n -> 2n update (rows of n and packed rows; one, two and
+    three passes; every top pass of a fixed geometry; several rows), against the
+    transform and the eigenvalues of the whole, also in place (the old half's
+    values at the start of the output)."""
+    n = 2**m
+    g = torch.Generator("cuda").manual_seed(m)
+    cdt = torch.complex128 if dtype == F64 else torch.complex64
+    y = torch.randn((B, 2 * n), dtype=F64, device="cuda", generator=g).to(dtype)
+    old, new = y[:, :n].contiguous(), y[:, n:].contiguous()
+    whole = ldk.transform("lattice", y.to(torch.complex128))
+    yt = ldk.transform("lattice", old.to(torch.complex128)).to(cdt)
+    got = ldk.update_double("lattice", yt, new)
+    rel = lambda a, b: ((a - b).norm() / b.norm()).item()
+    assert rel(got.to(torch.complex128), whole) < (1e-14 * (m + 10) if dtype == F64 else 3e-7 * (m + 10))
+    lam_old, lam = ldk.eig("lattice", old.double()), ldk.eig("lattice", y.double())
+    lam_got = ldk.eig_update_double("lattice", lam_old, new)
+    assert rel(lam_got, lam) < 1e-14 * (m + 10)
+    if B == 1:
+        buf = torch.empty((1, 2 * n), dtype=cdt, device="cuda")
+        buf[:, :n] = yt
+        assert torch.equal(ldk.update_double("lattice", buf[:, :n], new, out=buf), got)
+        buf = torch.empty((1, 2 * n), dtype=F64, device="cuda")
+        buf[:, :n] = lam_old
+        assert torch.equal(ldk.eig_update_double("lattice", buf[:, :n], new, out=buf), lam_got)

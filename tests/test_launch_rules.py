@@ -17,6 +17,7 @@ int column(int lattice, int R, long long lo, long long hi) { return ldk::column_
 int points(int lattice, int R, long long lo, long long hi) { return ldk::points_column_iters(lattice, R, lo, hi); }
 int grad(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).it; }
 int grad_dims(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).dims; }
+int packed(int f32, long long rows, int m) { return ldk::packed_update(f32, rows, m); }
 int rqmc(int net, int R, long long n) { return ldk::rqmc_iters(net, R, n); }
 }
 '''
@@ -34,6 +35,7 @@ def rules(tmp_path_factory):
     L.column.argtypes = L.points.argtypes = [i, i, q, q]
     L.grad.argtypes = L.grad_dims.argtypes = [i, i, i, q, q]
     L.rqmc.argtypes = [i, i, q]
+    L.packed.argtypes = [i, q, i]
     return L
 
 
@@ -80,3 +82,12 @@ def test_column_beside_the_point_words(rules):
     assert [rules.points(1, 1, 0, 2**m) for m in (16, 17, 18, 19, 20, 22)] == [1, 4, 8, 8, 8, 16]
     assert [rules.points(0, 1, 0, 2**m) for m in (16, 17, 18, 19, 20, 22)] == [1, 4, 4, 4, 8, 16]
     assert rules.points(1, 10, 0, 2**15) == 8 and rules.points(1, 4096, 0, 2**10) == 4
+
+
+def test_packed_update(rules):
+    """Short rows, and a few rows of FP32 in two passes, transform rows of n."""
+    for f32, short in ((0, {4, 5, 6, 7, 8}), (1, {4, 5, 6, 7, 8, 9})):
+        assert {m for m in range(2, 26) if not rules.packed(f32, 2048, m)} == short
+    assert not rules.packed(0, 1, 1) and rules.packed(0, 1, 14)
+    assert [m for m in range(10, 26) if not rules.packed(1, 1, m)] == [14, 15, 16, 17, 18, 19]
+    assert [rules.packed(1, R, 15) for R in (16, 17)] == [0, 1]
