@@ -118,6 +118,16 @@ inline int rqmc_iters(bool net, int R, int64_t n)
     return least_work(its, most, 1, 0, n);
 }
 
+// Lattice solves by precomputed coefficients, FP64: whether a workgroup runs the
+// same tile of two right-hand sides in turn (the coefficients then come from the
+// L2 lines that the first one brought in; the same bits).  It needs two
+// workgroups a CU after the halving.  Measured (solve, us, paired / not, blocks
+// after the halving): n = 2^13 19.4 / 16.2 (2), 28.1 / 25.2 (128); 2^16 33.6 / 32.3
+// (256), 50.0 / 51.0 (512); 2^19 51.9 / 53.1 (512), 173 / 182 (2048); 2^20 42.2 /
+// 40.4 (256), 56.3 / 58.0 (512).  FP32: 0.97 to 1.02 of each other from 512 on,
+// and 104 against 116 unpaired at 2^20: never paired.
+inline bool pair_rows(int nrhs, int64_t blocks) { return nrhs % 2 == 0 && blocks >= 1024; }
+
 // The n -> 2n update of a lattice on its real new half: packed rows of n / 2
 // complex entries, or rows of n.  Packed halves the transform and lengthens each
 // workgroup's chain (untangling, two twiddles), so it loses where many short rows

@@ -43,6 +43,7 @@
 //   PM_UPDATE      dst[k], dst[n+k] = (old_k +- scale w_k Y_k) / sqrt 2 (complex),
 //   PM_UPDATE_EIG  dst[k], dst[n+k] = old_k +- Re(w_k Y_k)              (FP64),
 // with dst rows of 2n and w_{k+N} = -i w_k.
+#include "launchrules.hpp"
 #include "passkit.hpp"
 
 namespace ldk {
@@ -695,8 +696,8 @@ int launch_rt(const PassArgs &a, double *lam_out, hipStream_t s, double *ld_part
         constexpr int ONE = TILE == 11 ? 8 : 7;
         const bool fixed = (ANY || a.g.a == ONE) && with_top_geometry<TILE>(a.g, [&](auto ca) {
             constexpr int A = ANY ? ca() : ONE;
-            if constexpr (CF) {
-                if (a.nrhs % 2 == 0) {
+            if constexpr (CF && TILE == 11) {
+                if (pair_rows(a.nrhs, blocks)) {
                     hipLaunchKernelGGL((k_real_top<T, LOGE, MODE, LD, ST, SRC_F32, CF, A, TILE - A, 2>),
                                        dim3((unsigned)(blocks / 2)), dim3(threads), lds, s, a,
                                        lam_out, ld_part);

@@ -18,6 +18,7 @@ int points(int lattice, int R, long long lo, long long hi) { return ldk::points_
 int grad(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).it; }
 int grad_dims(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).dims; }
 int packed(int f32, long long rows, int m) { return ldk::packed_update(f32, rows, m); }
+int pair(int nrhs, long long blocks) { return ldk::pair_rows(nrhs, blocks); }
 int rqmc(int net, int R, long long n) { return ldk::rqmc_iters(net, R, n); }
 }
 '''
@@ -36,6 +37,7 @@ def rules(tmp_path_factory):
     L.grad.argtypes = L.grad_dims.argtypes = [i, i, i, q, q]
     L.rqmc.argtypes = [i, i, q]
     L.packed.argtypes = [i, q, i]
+    L.pair.argtypes = [i, q]
     return L
 
 
@@ -91,3 +93,8 @@ def test_packed_update(rules):
     assert not rules.packed(0, 1, 1) and rules.packed(0, 1, 14)
     assert [m for m in range(10, 26) if not rules.packed(1, 1, m)] == [14, 15, 16, 17, 18, 19]
     assert [rules.packed(1, R, 15) for R in (16, 17)] == [0, 1]
+
+
+def test_right_hand_sides_paired_in_a_full_grid_only(rules):
+    assert [rules.pair(q, b) for q, b in ((2, 4), (2, 1022), (2, 1024), (8, 4096), (3, 3000), (1, 4096))] == \
+        [0, 0, 1, 1, 0, 0]
