@@ -81,15 +81,18 @@ inline int points_column_iters(bool lattice, int R, int64_t n_min, int64_t n_max
 }
 
 // Gradient given the forward column, points regenerated.  The dimensions are
-// independent then, so a grid short of three blocks per compute unit is split
-// over them; a large one takes twice the points per thread in FP32 (the
-// dimension's setup and reduction serve more factors; in FP64, where it would
-// change the order of the sums, nets lose their occupancy to it and lattices
-// gain 5 %).  Measured (us, D = 16 / 8 / 4 / 2 dimensions per block): FP64 net
-// 2^16 points x d = 16: 21.0 / 13.8 / 10.2 / 8.8; 2^18 x 32: 22.0 / 18.2 /
-// 17.0 / 20.5; 2^20 x 32: 42.4 / 43.8 / 48.3 / 63.6; 16 instead of 8 points per
-// thread at 2^22 x 64: lattice FP32 133 -> 127, net FP32 132 -> 130, net FP64
-// 268 -> 272: a tile's setup is worth less than a point.
+// independent then, so a grid short of two to three blocks per compute unit is
+// split over them, sooner the more dimensions a block keeps (FP64 net, whole /
+// split, us: d = 3, 384 tiles 11.3 / 10.4, 640 13.4 / 14.4, 758 13.5 / 18.7; d =
+// 6, 512 15.9 / 14.6, 758 19.2 / 23.3; d = 16, 640 36.0 / 31.6, 758 37.3 / 38.6).
+// A large grid takes twice the points per thread in FP32 (the dimension's setup
+// and reduction serve more factors; in FP64, where it would change the order of
+// the sums, nets lose their occupancy to it and lattices gain 5 %).  Measured
+// (us, D = 16 / 8 / 4 / 2 dimensions per block): FP64 net 2^16 points x d = 16:
+// 21.0 / 13.8 / 10.2 / 8.8; 2^18 x 32: 22.0 / 18.2 / 17.0 / 20.5; 2^20 x 32: 42.4 /
+// 43.8 / 48.3 / 63.6; 16 instead of 8 points per thread at 2^22 x 64: lattice FP32
+// 133 -> 127, net FP32 132 -> 130, net FP64 268 -> 272: a tile's setup is worth
+// less than a point.
 struct GradSplit {
     int it, dims;
 };
@@ -101,7 +104,7 @@ inline GradSplit grad_split(bool f32, int R, int d, int64_t n_min, int64_t n_max
     };
     GradSplit s{KC_ITERS, NT_DIMS};
     if (f32 && blocks(2 * KC_ITERS, NT_DIMS) >= 1024) s.it = least_work(its, 2 * KC_ITERS, 1, n_min, n_max);
-    while (s.dims > 2 && blocks(s.it, s.dims) < 768) s.dims /= 2;
+    while (s.dims > 2 && blocks(s.it, s.dims) < (s.dims > 8 ? 704 : s.dims > 4 ? 640 : 512)) s.dims /= 2;
     return s;
 }
 

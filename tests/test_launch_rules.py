@@ -76,6 +76,10 @@ def test_small_replications_and_full_tiles(rules):
     assert rules.rqmc(1, 1024, 2**11) == 8 and rules.rqmc(1, 16, 2**18) == 16
     assert rules.rqmc(0, 16, 2**18) == 8 and rules.rqmc(1, 2048, 512) == 2
     assert rules.grad_dims(0, 1, 16, 0, 2**10) == 2
+    # a grid of nearly three blocks a compute unit stays whole
+    blocks = lambda tiles, d: -(-d // rules.grad_dims(0, tiles, d, 0, 2**11))
+    assert [blocks(758, d) for d in (2, 3, 6, 16)] == [1, 1, 1, 1]
+    assert [blocks(640, d) for d in (3, 6, 16)] == [1, 1, 2] and [blocks(500, d) for d in (3, 6)] == [2, 2]
 
 
 def test_column_beside_the_point_words(rules):
