@@ -382,7 +382,7 @@ extern "C" int ldk_points_column(const ldk_kernel *k, const ldk_pointset *ps, in
     if (n_min < 0 || n_max < n_min || n_max > lim) return LDK_EINVAL;
     if (n_max == n_min) return LDK_OK;  // empty window: the outputs may be NULL
     if (!pts || !k1) return LDK_EINVAL;
-    const int it = points_column_iters(p.kind == LDK_LATTICE, p.R, n_min, n_max);
+    const int it = points_column_iters(p.kind == LDK_LATTICE, p.R, p.d, n_min, n_max);
     const int64_t tile = (int64_t)KC_THREADS * it;
     const int64_t tile_base = (n_min / tile) * tile;
     const int64_t kc_tiles = window_tiles(n_min, n_max, it);

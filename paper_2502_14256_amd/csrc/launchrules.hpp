@@ -71,11 +71,13 @@ inline int column_iters(bool lattice, int R, int64_t n_min, int64_t n_max)
 // 27.8; 2^18 x 6: 7.1 / 6.3 / 6.4 / 6.6, x 64: 30.4 / 22.8 / 22.7 / 27.8; 2^19 x
 // 16: 14.2 / 17.3 / 13.7 / 13.5; 2^22 x 6: 37.6 / 39.1 / 47.2 / 38.2, x 16: 106 /
 // 111 / 105 / 107.  Net 2^16 x 64: 32.2 / 33.9 / 47.1 / 74.5; 2^17 x 4: 15.1 /
-// 14.1 / 14.2 / 14.3, x 32: 30.0 / 26.3 / 26.2 / 40.8; above as the column alone.
-inline int points_column_iters(bool lattice, int R, int64_t n_min, int64_t n_max)
+// 14.1 / 14.2 / 14.3, x 32: 30.0 / 26.3 / 26.2 / 40.8; 2^18 x 16: 29.4 / 22.0 / 21.1
+// / 21.6; 2^19 x 6: 25.0 / 18.6 / 18.3 / 17.7, x 32: 60.5 / 38.8 / 44.7 / 49.1.
+inline int points_column_iters(bool lattice, int R, int d, int64_t n_min, int64_t n_max)
 {
     constexpr int its[] = {16, 8, 4, 1};
-    const int64_t pts = (int64_t)R * (n_max - n_min), eight = (int64_t)1 << (lattice ? 18 : 20);
+    const int64_t pts = (int64_t)R * (n_max - n_min);
+    const int64_t eight = (int64_t)1 << (lattice || d <= NT_DIMS ? 18 : 20);
     const int most = pts < (1 << 17) ? 1 : pts < eight ? 4 : pts < (1 << 22) ? 8 : 16;
     return least_work(its, most, lattice ? 1 : 4, n_min, n_max);
 }

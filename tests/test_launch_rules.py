@@ -14,7 +14,7 @@ SRC = '''
 extern "C" {
 long long tiles(long long lo, long long hi, int it) { return ldk::window_tiles(lo, hi, it); }
 int column(int lattice, int R, long long lo, long long hi) { return ldk::column_iters(lattice, R, lo, hi); }
-int points(int lattice, int R, long long lo, long long hi) { return ldk::points_column_iters(lattice, R, lo, hi); }
+int points(int lattice, int R, int d, long long lo, long long hi) { return ldk::points_column_iters(lattice, R, d, lo, hi); }
 int grad(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).it; }
 int grad_dims(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).dims; }
 int packed(int f32, long long rows, int m) { return ldk::packed_update(f32, rows, m); }
@@ -33,8 +33,8 @@ def rules(tmp_path_factory):
     L = C.CDLL(str(d / "r.so"))
     i, q = C.c_int, C.c_longlong
     L.tiles.argtypes, L.tiles.restype = [q, q, i], q
-    L.column.argtypes = L.points.argtypes = [i, i, q, q]
-    L.grad.argtypes = L.grad_dims.argtypes = [i, i, i, q, q]
+    L.column.argtypes = [i, i, q, q]
+    L.points.argtypes = L.grad.argtypes = L.grad_dims.argtypes = [i, i, i, q, q]
     L.rqmc.argtypes = [i, i, q]
     L.packed.argtypes = [i, q, i]
     L.pair.argtypes = [i, q]
@@ -54,8 +54,9 @@ def test_points_formed(rules, R, lo, hi):
     for lattice in (0, 1):
         it = rules.column(lattice, R, lo, hi)
         assert it * rules.tiles(lo, hi, it) <= (1.1 if lattice else 1.25) * eight
-        it = rules.points(lattice, R, lo, hi)
-        assert it * rules.tiles(lo, hi, it) <= (1.1 if lattice else 1.25) * eight
+        for d in (4, 40):
+            it = rules.points(lattice, R, d, lo, hi)
+            assert it * rules.tiles(lo, hi, it) <= (1.1 if lattice else 1.25) * eight
     for d in (1, 16, 33, 100):
         assert rules.grad(0, R, d, lo, hi) == 8
         it = rules.grad(1, R, d, lo, hi)
@@ -83,11 +84,13 @@ def test_small_replications_and_full_tiles(rules):
 
 
 def test_column_beside_the_point_words(rules):
-    """One point per thread only while the launch is short; a lattice takes 8
-    from 2^18 points on, where fewer measured slower."""
-    assert [rules.points(1, 1, 0, 2**m) for m in (16, 17, 18, 19, 20, 22)] == [1, 4, 8, 8, 8, 16]
-    assert [rules.points(0, 1, 0, 2**m) for m in (16, 17, 18, 19, 20, 22)] == [1, 4, 4, 4, 8, 16]
-    assert rules.points(1, 10, 0, 2**15) == 8 and rules.points(1, 4096, 0, 2**10) == 4
+    """One point per thread only while the launch is short; lattices and nets of
+    one chunk of dimensions take 8 from 2^18 points on, where fewer measured
+    slower."""
+    pts = lambda lattice, d: [rules.points(lattice, 1, d, 0, 2**m) for m in (16, 17, 18, 19, 20, 22)]
+    assert pts(1, 4) == pts(1, 40) == pts(0, 16) == [1, 4, 8, 8, 8, 16]
+    assert pts(0, 17) == [1, 4, 4, 4, 8, 16]
+    assert rules.points(1, 10, 4, 0, 2**15) == 8 and rules.points(1, 4096, 4, 0, 2**10) == 4
 
 
 def test_packed_update(rules):
