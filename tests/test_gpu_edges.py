@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2502_14256_amd as ldk
+import test_gpu_cubature as cub
 import workloads as W
 from ldk_dev import dev_u64, kernel, pointset
 from paper_2502_14256_amd.autograd import MarginalLogLikelihood
@@ -215,3 +216,39 @@ def test_lattice_update_plans(B, m, dtype):
         buf = torch.empty((1, 2 * n), dtype=F64, device="cuda")
         buf[:, :n] = lam_old
         assert torch.equal(ldk.eig_update_double("lattice", buf[:, :n], new, out=buf), lam_got)
+
+
+@pytest.mark.parametrize("m", [15, 17, 18, 19])
+@pytest.mark.parametrize("dtype", [F64, F32])
+def test_cubature_top_passes(orc, m, dtype):
+    """The sizes whose top passes (5 to 8 axis bits) the cubature's own tests leave
+    out, with their oracle and bounds."""
+    cub.test_wce(orc, "lattice", m, dtype)
+    cub.test_bayes_cubature(orc, "lattice", m, dtype)
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("m,nrhs", [(13, 1), (13, 20), (16, 3), (18, 2)])
+def test_two_pass_net_fit_of_bad_rows(m, nrhs, dtype):
+    """A row with some lambda + s2 <= 0 (log-det NaN), columns with an infinity and
+    a NaN, and responses with an infinity, beside a good row: eigenvalues and
+    solutions as the separate calls give them, bit for bit."""
+    n, R, s2 = 2**m, 5, 1e-2
+    g = torch.Generator("cuda").manual_seed(m)
+    k1 = torch.rand((R, n), dtype=F64, device="cuda", generator=g)
+    k1[:, 0] += n
+    k1[1, 0] -= 1.2 * n  # lambda of about -0.2 n, the sum row apart
+    k1[2, 5], k1[3, n - 1] = float("inf"), float("nan")
+    k1 = k1.to(dtype)
+    y = torch.randn((R, nrhs, n), dtype=F64, device="cuda", generator=g).to(dtype)
+    y[4, 0, 7] = float("-inf")
+    lam_ref = ldk.eig("dnet", k1)
+    c_ref, ld_ref = ldk.solve("dnet", lam_ref, s2, y), ldk.logdet(lam_ref, s2)
+    assert ld_ref[[0, 4]].isfinite().all() and ld_ref[1:4].isnan().all()
+    same = lambda a, b: torch.equal(a.isnan(), b.isnan()) and torch.equal(a[~a.isnan()], b[~b.isnan()])
+    for logdet in (True, False):
+        lam, c, ld = ldk.fit("dnet", k1, s2, y, logdet=logdet)
+        assert same(lam, lam_ref) and same(c, c_ref)
+        if logdet:
+            assert ld[1:4].isnan().all()
+            assert torch.allclose(ld[[0, 4]], ld_ref[[0, 4]], rtol=1e-13, atol=1e-13 * n)
