@@ -492,7 +492,7 @@ size_t ws_bytes(int op, int kind, int64_t B, int m, int dtype)
         return (size_t)B * chunks * sizeof(double);
     }
     case LDK_OP_UPDATE_DOUBLE: return 0;
-    case LDK_OP_EIG_UPDATE_DOUBLE: return lat ? cplx_rows_bytes(B, m, LDK_F64) : 0;
+    case LDK_OP_EIG_UPDATE_DOUBLE: return lat ? cplx_rows_bytes(B, m > 1 ? m - 1 : 1, LDK_F64) : 0;
     default: return 0;
     }
 }
@@ -1023,18 +1023,19 @@ int ldk_eig_update_double(int kind, int R, int m, int dtype, const double *lam_o
         a.rows = R;
         return real_update(LDK_F64, PM_UPDATE_EIG, m, a, k1_new, dtype == LDK_F32, lam_old, lam_full, ws, n / 2, s);
     }
-    // FP64 transform of the new half (k1 widened when FP32); intermediates of
-    // a multi-pass plan in the workspace (lattice, complex) or in the output
-    // rows' second halves (net), and the last pass stores through the
-    // doubling step lambda_m +- Re(w_k u_k) into both halves (PIO_COMBINE)
+    // FP64 transform of the new half (k1 widened when FP32), a lattice's in one
+    // pass; a net's intermediates live in the output rows' second halves, and
+    // the last pass stores through the doubling step lambda_m +- Re(w_k u_k)
+    // into both halves (PIO_COMBINE)
     const Plan pl = make_plan(m, log_tile_for(kind, LDK_F64));
+    if (lat && pl.P > 1) return LDK_ENOTSUP;
     for (int p = 0; p < pl.P; ++p) {
         const bool first = p == 0, last = p == pl.P - 1;
         PassArgs a{};
-        a.src = first ? k1_new : (lat ? (const void *)ws : (const void *)(lam_full + n));
-        a.src_row = first ? n : (lat ? n : 2 * n);
-        a.dst = last ? (void *)lam_full : (lat ? ws : (void *)(lam_full + n));
-        a.dst_row = last ? 2 * n : (lat ? n : 2 * n);
+        a.src = first ? k1_new : (const void *)(lam_full + n);
+        a.src_row = first ? n : 2 * n;
+        a.dst = last ? lam_full : lam_full + n;
+        a.dst_row = 2 * n;
         a.rows = R;
         a.m = m;
         a.g = pl.pass[p];

@@ -437,11 +437,13 @@ int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
                 constexpr int A = ca(), W = TILE - A;
                 if constexpr (MODE == PM_FWD) {
                     if (st == IO_POWER) {
-                        hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_POWER, false, A, W>), grid, block, lds, s, a);
+                        hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_POWER, false, A, W>), grid, block,
+                                           lds, s, a);
                         return LDK_OK;
                     }
                     if (st == IO_COMBINE) {
-                        hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_COMBINE, false, A, W>), grid, block, lds, s, a);
+                        hipLaunchKernelGGL((k_pass<T, LOGE, MODE, IO_SAME, IO_COMBINE, false, A, W>), grid, block,
+                                           lds, s, a);
                         return LDK_OK;
                     }
                 }
@@ -472,11 +474,20 @@ int launch_t(int ld, int st, const PassArgs &a, hipStream_t s)
         else return LDK_ENOTSUP;
     } else if constexpr (MODE == PM_FWD) {
         if (st == IO_COMBINE) {
-            if (ld == IO_SAME) LDK_PASS(IO_SAME, IO_COMBINE);
-            else if (ld == IO_REAL) LDK_PASS(IO_REAL, IO_COMBINE);
-            else return LDK_ENOTSUP;
-            LDK_LAUNCH_CHECK();
-            return LDK_OK;
+            // (rows of more than one pass run packed in FP64, packed_update)
+            if (ld == IO_REAL) {
+                LDK_PASS(IO_REAL, IO_COMBINE);
+                LDK_LAUNCH_CHECK();
+                return LDK_OK;
+            }
+            if constexpr (std::is_same<T, cplx<float>>::value) {
+                if (ld == IO_SAME) {
+                    LDK_PASS(IO_SAME, IO_COMBINE);
+                    LDK_LAUNCH_CHECK();
+                    return LDK_OK;
+                }
+            }
+            return LDK_ENOTSUP;
         }
         if (st == IO_PACKED || st == IO_POWER) return LDK_ENOTSUP;
         if (ld == IO_SAME && st == IO_SAME) LDK_PASS(IO_SAME, IO_SAME);
