@@ -291,10 +291,12 @@ int ldk_logdet_checked(int R, int m, const double *lam, double sigma2, double *o
  * column's and the right-hand sides' forward passes run as one launch, and
  * the pass that forms the eigenvalues also sums their logarithms per tile,
  * so the log-det costs one small reduction instead of a pass over lambda.
- * Digital nets of up to 2^20 points with nrhs >= 1 share launches in the same
- * way (one launch up to 2^12 points in FP64).  Other cases run the three entry points in turn.  lam and c equal the
- * separate calls bit for bit; the log-det to rounding (another fixed
- * summation order).
+ * Digital nets with nrhs >= 1 share launches too: FP64 nets of up to 2^12
+ * points run as one launch, nets of 2^13 to 2^20 points as three (FP32: not on
+ * the split-FP16 engine).  Other cases, and solutions written over the column
+ * of more than their own replication, run the three entry points in turn.
+ * lam and c equal the separate calls bit for bit; the log-det to rounding
+ * (another fixed summation order).
  * k1 = dtype[R][n]; y, c = dtype[R][nrhs][n]; lam = double[R][n];
  * logdet = device double[R].
  * ws: ldk_workspace_bytes(LDK_OP_FIT, kind, R * (nrhs + 1), m, dtype) bytes. */

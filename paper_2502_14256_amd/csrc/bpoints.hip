@@ -15,13 +15,13 @@
 // the integer v = sum_t z_t b^(T-1-t) < 2^53 divided by b^T, rounded once.
 //
 // A block takes 64 or 128 consecutive indices of one replication, one or two
-// per lane; its eight waves split the dimensions.  The digits of an index live in registers,
-// four to a 32-bit word, so a row of S (or of Faure's C) times the digit
-// vector is one v_dot4_u32_u8 per word; the sum stays below 2^21 and is
-// reduced mod b by a 32-bit reciprocal (32-bit products run at full rate
-// here).  Four output digits make one 32-bit integer before they join the
-// FP64 Horner sum.  The Faure matrices come packed from a small kernel, formed
-// once per call into the workspace.
+// per lane; its eight waves split the dimensions.  The digits of an index live
+// in registers, four to a 32-bit word, so a row of S (or of Faure's C) times the
+// digit vector is one v_dot4_u32_u8 per word; the sum stays below 2^21 and is
+// reduced mod b by a 32-bit reciprocal (32-bit products run at full rate here).
+// Four output digits make one 32-bit integer before they join the FP64 Horner
+// sum.  The Faure matrices come packed from a small kernel, formed once per call
+// into the workspace.
 //
 // Nested uniform scrambling of a base-2 net (Sec. 4.3, NUS): the point word
 // z = C i (64 digits), then digit t = 1..64 is flipped when the top bit of
@@ -234,8 +234,8 @@ __device__ __forceinline__ void digits_lms(const uint32_t (&srows)[MJ], uint32_t
 // + j, parameters at index p): digit t of the output is w_t = (S z)_t mod b,
 // then pi_t(w_t), then + delta_t mod b (each step as the flags F ask);
 // Horner's rule in FP64 is exact (every partial sum is an integer below 2^53)
-// and the one division rounds.  The wave's lanes first fetch one row of S and one delta each.  Digits go four at a time, as one
-// 32-bit integer each four.
+// and the one division rounds.  The wave's lanes first fetch one row of S and
+// one delta each.  Digits go four at a time, as one 32-bit integer each four.
 // Without S the digits past the index's own M are zero before the
 // permutation, the same for every lane (skipped where nothing maps them).
 // v / b^T from the rounded reciprocal: two corrections by the exact remainder

@@ -97,13 +97,13 @@ __device__ __forceinline__ R sum_terms(Term &&term)
 }
 
 // ---- dimension sweeps: call visit(j, l0, t[KC_ITERS], f[KC_ITERS]) for the
-// dimensions ja .. jb - 1 in order and l0 = 0, KC_ITERS, .. below IT, t[l] = gamma_j K_j(delta) and f[l] = 1 + t[l] of point
-// tile0 + threadIdx.x + KC_THREADS l, f formed exactly as the kernel column
-// forms it ----
+// dimensions ja .. jb - 1 in order and l0 = 0, KC_ITERS, .. below IT, t[l] =
+// gamma_j K_j(delta) and f[l] = 1 + t[l] of point tile0 + threadIdx.x +
+// KC_THREADS (l0 + l), f formed exactly as the kernel column forms it ----
 
 // t and f of the KC_ITERS points l0 .. l0 + KC_ITERS - 1 of a thread (its
 // points are first + KC_THREADS l, l < IT, first = tile0 + threadIdx.x with
-// tile0 a multiple of KC_THREADS IT).  Sg / Sc: the t and f polynomials.
+// tile0 a multiple of KC_THREADS IT).
 template <typename R, int ALPHA, int ORDER, int IT>
 struct LatticeDim {
     R e0, c0, c1, c2, c3, lo_p;
