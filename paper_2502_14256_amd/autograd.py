@@ -33,19 +33,17 @@ from . import (Kernel, LdkError, PointSet, _kind, eig, kernel_column, kernel_gra
 def _gamma(log_gamma):
     """exp in the parameter's own type, as float64[d]: the same bits in both
     passes."""
-    return torch.exp(log_gamma.detach().reshape(-1)).to(torch.float64).contiguous()
+    return torch.exp(log_gamma.reshape(-1)).to(torch.float64).contiguous()
 
 
 def _parameters(log_gamma, log_zeta, log_sigma2):
     """(gamma [d] on the device, zeta, sigma2): the two numbers the library
     takes from the host, each the exp in its own type.  float64 parameters of
     one device come over in one copy, the call's one wait for the device."""
-    log_gamma, log_zeta, log_sigma2 = (log_gamma.detach().reshape(-1),
-                                       log_zeta.detach().reshape(1),
-                                       log_sigma2.detach().reshape(1))
-    if all(t.dtype == torch.float64 and t.device == log_gamma.device
-           for t in (log_gamma, log_zeta, log_sigma2)):
-        theta = torch.exp(torch.cat([log_gamma, log_zeta, log_sigma2]))
+    if (log_gamma.dtype == log_zeta.dtype == log_sigma2.dtype == torch.float64
+            and log_gamma.device == log_zeta.device == log_sigma2.device):
+        theta = torch.exp(torch.cat([log_gamma.reshape(-1), log_zeta.reshape(1),
+                                     log_sigma2.reshape(1)]))
         zeta, sigma2 = theta[-2:].tolist()
         return theta[:-2], zeta, sigma2
     return _gamma(log_gamma), torch.exp(log_zeta).item(), torch.exp(log_sigma2).item()
@@ -66,7 +64,9 @@ class MarginalLogLikelihood(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, log_gamma, log_zeta, log_sigma2, ps, kind, alpha, y, dtype, recompute):
-        gamma, zeta, sigma2 = _parameters(log_gamma, log_zeta, log_sigma2)
+        # (detached: no graph is recorded in here, and the saved tensors are too)
+        gamma, zeta, sigma2 = _parameters(log_gamma.detach(), log_zeta.detach(),
+                                          log_sigma2.detach())
         k1, L, g, ds = _forward_parts(Kernel(kind, alpha, gamma, zeta), ps, sigma2, y, dtype)
         ctx.ps, ctx.kind, ctx.alpha, ctx.dtype, ctx.recompute = ps, kind, alpha, dtype, recompute
         ctx.n = y.shape[-1]
