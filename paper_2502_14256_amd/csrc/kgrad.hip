@@ -546,7 +546,7 @@ extern "C" int ldk_kernel_grad(const ldk_kernel *k, const ldk_pointset *ps, cons
     int it = KC_ITERS;
     g.dims_per_block = p.d;
     if (k1 && !given) {
-        const GradSplit sp = grad_split(dtype == LDK_F32, p.R, p.d, n_min, n_max);
+        const GradSplit sp = grad_split(p.kind == LDK_LATTICE, dtype == LDK_F32, p.R, p.d, n_min, n_max);
         it = sp.it;
         g.dims_per_block = sp.dims;
     }

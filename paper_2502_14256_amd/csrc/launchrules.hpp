@@ -94,18 +94,24 @@ inline int points_column_iters(bool lattice, int R, int d, int64_t n_min, int64_
 // 21.0 / 13.8 / 10.2 / 8.8; 2^18 x 32: 22.0 / 18.2 / 17.0 / 20.5; 2^20 x 32: 42.4 /
 // 43.8 / 48.3 / 63.6; 16 instead of 8 points per thread at 2^22 x 64: lattice FP32
 // 133 -> 127, net FP32 132 -> 130, net FP64 268 -> 272: a tile's setup is worth
-// less than a point.
+// less than a point.  A lattice of a few dimensions is bound by its column and
+// weights, and in a grid of more than one round of blocks fewer of its reads are
+// in flight then (895 x 2^13, 8 / 16 points: d = 2 25.0 / 28.2, d = 8 42.3 / 42.1,
+// d = 12 55.2 / 53.3; but 64 x 2^16, d = 2: 20.0 / 18.6), unless a replication has
+// so many tiles that their sum is the longer part (2^22, d = 2: 77 / 46).
 struct GradSplit {
     int it, dims;
 };
-inline GradSplit grad_split(bool f32, int R, int d, int64_t n_min, int64_t n_max)
+inline GradSplit grad_split(bool lattice, bool f32, int R, int d, int64_t n_min, int64_t n_max)
 {
     constexpr int its[] = {2 * KC_ITERS, KC_ITERS};
     auto blocks = [&](int it, int dims) {
         return window_tiles(n_min, n_max, it) * R * ((d + dims - 1) / dims);
     };
     GradSplit s{KC_ITERS, NT_DIMS};
-    if (f32 && blocks(2 * KC_ITERS, NT_DIMS) >= 1024) s.it = least_work(its, 2 * KC_ITERS, 1, n_min, n_max);
+    const int64_t b2 = blocks(2 * KC_ITERS, NT_DIMS);
+    const bool twice = !lattice || d >= 12 || b2 <= 1280 || window_tiles(n_min, n_max, KC_ITERS) >= 256;
+    if (f32 && twice && b2 >= 1024) s.it = least_work(its, 2 * KC_ITERS, 1, n_min, n_max);
     while (s.dims > 2 && blocks(s.it, s.dims) < (s.dims > 8 ? 704 : s.dims > 4 ? 640 : 512)) s.dims /= 2;
     return s;
 }

@@ -15,8 +15,8 @@ extern "C" {
 long long tiles(long long lo, long long hi, int it) { return ldk::window_tiles(lo, hi, it); }
 int column(int lattice, int R, long long lo, long long hi) { return ldk::column_iters(lattice, R, lo, hi); }
 int points(int lattice, int R, int d, long long lo, long long hi) { return ldk::points_column_iters(lattice, R, d, lo, hi); }
-int grad(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).it; }
-int grad_dims(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(f32, R, d, lo, hi).dims; }
+int grad(int lattice, int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(lattice, f32, R, d, lo, hi).it; }
+int grad_dims(int f32, int R, int d, long long lo, long long hi) { return ldk::grad_split(false, f32, R, d, lo, hi).dims; }
 int packed(int f32, long long rows, int m) { return ldk::packed_update(f32, rows, m); }
 int pair(int nrhs, long long blocks) { return ldk::pair_rows(nrhs, blocks); }
 int rqmc(int net, int R, long long n) { return ldk::rqmc_iters(net, R, n); }
@@ -34,7 +34,8 @@ def rules(tmp_path_factory):
     i, q = C.c_int, C.c_longlong
     L.tiles.argtypes, L.tiles.restype = [q, q, i], q
     L.column.argtypes = [i, i, q, q]
-    L.points.argtypes = L.grad.argtypes = L.grad_dims.argtypes = [i, i, i, q, q]
+    L.points.argtypes = L.grad_dims.argtypes = [i, i, i, q, q]
+    L.grad.argtypes = [i, i, i, i, q, q]
     L.rqmc.argtypes = [i, i, q]
     L.packed.argtypes = [i, q, i]
     L.pair.argtypes = [i, q]
@@ -58,9 +59,10 @@ def test_points_formed(rules, R, lo, hi):
             it = rules.points(lattice, R, d, lo, hi)
             assert it * rules.tiles(lo, hi, it) <= (1.1 if lattice else 1.25) * eight
     for d in (1, 16, 33, 100):
-        assert rules.grad(0, R, d, lo, hi) == 8
-        it = rules.grad(1, R, d, lo, hi)
-        assert it * rules.tiles(lo, hi, it) <= 1.1 * eight
+        for lattice in (0, 1):
+            assert rules.grad(lattice, 0, R, d, lo, hi) == 8
+            it = rules.grad(lattice, 1, R, d, lo, hi)
+            assert it * rules.tiles(lo, hi, it) <= 1.1 * eight
     for net in (0, 1):
         it = rules.rqmc(net, R, hi)
         assert it * rules.tiles(0, hi, it) <= 1.1 * 8 * rules.tiles(0, hi, 8)
@@ -73,7 +75,12 @@ def test_small_replications_and_full_tiles(rules):
     assert [rules.column(k, 1024, 0, 2**12) for k in (0, 1)] == [16, 16]
     assert [rules.column(0, 1, 0, 2**m) for m in (17, 18, 20, 22)] == [1, 4, 8, 16]
     assert [rules.column(1, 1, 0, 2**m) for m in (18, 19, 20, 22)] == [1, 4, 8, 16]
-    assert rules.grad(1, 1024, 16, 0, 2**11) == 8 and rules.grad(1, 64, 64, 0, 2**16) == 16
+    assert rules.grad(0, 1, 1024, 16, 0, 2**11) == 8 and rules.grad(0, 1, 64, 64, 0, 2**16) == 16
+    # a lattice of few dimensions takes 8 in more than one round of blocks, but
+    # for a long sum over its tiles
+    assert [rules.grad(1, 1, 895, d, 0, 2**13) for d in (2, 11, 12)] == [8, 8, 16]
+    assert rules.grad(1, 1, 64, 2, 0, 2**16) == 16 and rules.grad(1, 1, 4, 2, 0, 2**22) == 16
+    assert rules.grad(1, 1, 1, 2, 0, 2**22) == 16 and rules.grad(0, 1, 895, 2, 0, 2**13) == 16
     assert rules.rqmc(1, 1024, 2**11) == 8 and rules.rqmc(1, 16, 2**18) == 16
     assert rules.rqmc(0, 16, 2**18) == 8 and rules.rqmc(1, 2048, 512) == 2
     assert rules.grad_dims(0, 1, 16, 0, 2**10) == 2
