@@ -412,11 +412,11 @@ __global__ __launch_bounds__(KG_FINAL_THREADS) void k_grad_final(const double *_
         grad[(size_t)r * (d + 1) + j] = (v[0][lane] + v[1][lane]) + (v[2][lane] + v[3][lane]);
 }
 
-// The same sums for up to KG_FEW tiles: a thread per component of every
+// The same sums for up to FEW tiles: a thread per component of every
 // replication, its partials loaded before any is added.  Gradients of 2000
 // lattices, n = 32, d = 2, FP64: 21.4 us with a block of 1024 threads per
-// replication, 17.7 here; 16 tiles (10 x 2^14 and 1 x 2^15, d = 20) the same.
-constexpr int KG_FEW = 16;
+// replication, 17.7 here.
+template <int FEW>
 __global__ __launch_bounds__(KC_THREADS) void k_grad_few(const double *__restrict__ part, int tiles, int d,
                                                          uint32_t count, double *__restrict__ grad)
 {
@@ -424,13 +424,13 @@ __global__ __launch_bounds__(KC_THREADS) void k_grad_few(const double *__restric
     if (id >= count) return;
     const uint32_t r = id / (uint32_t)(d + 1), j = id % (uint32_t)(d + 1);
     const double *p = part + (size_t)r * tiles * (d + 1) + j;
-    double v[KG_FEW], s[4] = {};
+    double v[FEW], s[4] = {};
 #pragma unroll
-    for (int q = 0; q < KG_FEW; ++q)
+    for (int q = 0; q < FEW; ++q)
         if (q < tiles) v[q] = p[(size_t)q * (d + 1)];
     const int whole = tiles & ~3;
 #pragma unroll
-    for (int q = 0; q < KG_FEW; ++q)
+    for (int q = 0; q < FEW; ++q)
         if (q < whole) s[q & 3] += v[q];
         else if (q < tiles) s[0] += v[q];
     grad[id] = (s[0] + s[1]) + (s[2] + s[3]);
@@ -440,9 +440,11 @@ int launch_grad_final(const double *part, int64_t tiles, int R, int d, double *g
 {
     static_assert(65536ull * (LDK_MAX_D + 1) < 0x100000000ull, "R is a grid's y extent: 32-bit components");
     const uint32_t count = (uint32_t)R * (uint32_t)(d + 1);
-    if (tiles <= KG_FEW)
-        hipLaunchKernelGGL(k_grad_few, dim3((count + KC_THREADS - 1) / KC_THREADS), dim3(KC_THREADS), 0, s, part,
-                           (int)tiles, d, count, grad);
+    const dim3 few((count + KC_THREADS - 1) / KC_THREADS);
+    if (tiles <= 4)
+        hipLaunchKernelGGL(k_grad_few<4>, few, dim3(KC_THREADS), 0, s, part, (int)tiles, d, count, grad);
+    else if (tiles <= 16)
+        hipLaunchKernelGGL(k_grad_few<16>, few, dim3(KC_THREADS), 0, s, part, (int)tiles, d, count, grad);
     else
         hipLaunchKernelGGL(k_grad_final, dim3((d + 1 + 63) / 64, R), dim3(KG_FINAL_THREADS), 0, s, part, tiles, d,
                            grad);
