@@ -189,8 +189,8 @@ def test_nus_work_goes_with_the_dimensions():
 
 
 @pytest.mark.parametrize("dtype", [F64, F32])
-@pytest.mark.parametrize("B,m", [(1, 2), (5, 3), (3, 4), (1000, 5), (2, 9), (3, 10), (1, 14), (65, 14), (2, 16),
-                                 (1, 18), (3, 18), (1, 20), (2, 20), (1, 21), (1, 22)])
+@pytest.mark.parametrize("B,m", [(1, 2), (5, 3), (3, 4), (1000, 5), (2, 9), (3, 10), (1, 14), (65, 14), (2, 16), (2, 17),
+                                 (1, 18), (3, 18), (1, 19), (1, 20), (2, 20), (1, 21), (1, 22)])
 def test_lattice_update_plans(B, m, dtype):
     """Every plan of the n -> 2n update (rows of n and packed rows; one, two and
     three passes; every top pass of a fixed geometry; several rows), against the
